@@ -40,7 +40,7 @@ template <typename E> __device__ __forceinline__ const E *byte_at(const void *ba
 
 // backward_block runs workgroup w (0 <= w < nbx * nby * nbz) of the
 // backprojection into one volume; its partial sum goes to partials[w].
-// s_pix / s_col: LDS for ch_rows(TZB) x CHC staged pixels (plus two zero rows and a
+// s_pix / s_col: LDS for ch_rows(TZB) x CHC staged pixels (plus a zero row and a
 // spare record) and CHC columns.
 template <typename T, int EPI, int TZB, int CHC>
 __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *__restrict__ proj,
@@ -108,54 +108,34 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
                 unsigned tid = __builtin_amdgcn_workitem_id_x();
                 asm volatile("" : "+v"(tid));
                 // 2. stage the chunk: per pixel the z-parameters of its ray and L * e,
-                //    per column the in-plane parameters
-                //    (pixel t = r * ncol + c; t steps by 256: r by dr, c by dc, with carry)
+                //    per column the in-plane parameters.  Thread t keeps column
+                //    t % ncol (its ray parameters are read once per chunk) and takes
+                //    the rows t / ncol, + step, ... of it; the threads past the last
+                //    whole step of rows have nothing to stage.
                 {
                     // tid / ncol through a reciprocal: (t + 0.5) / ncol lies at least
                     // 0.5 / ncol >= 0.01 from an integer, the product's rounding below 1e-4
                     const float rn = __builtin_amdgcn_rcpf((float)ncol);
-                    int r = (int)(((float)tid + 0.5f) * rn), c = (int)tid - r * ncol;
-                    const int dr = 256 / ncol, dc = 256 - dr * ncol;
-                    for (int t = (int)tid; t < ncol * nrow; t += 256) {
-                        // the projection value first: its load overlaps the parameter loads.
-                        // All three are addressed as a uniform base plus a 32-bit byte offset
-                        // (one view's projection values span < 2^31 bytes: a detector has
+                    const int step = __builtin_amdgcn_readfirstlane((int)(256.5f * rn));
+                    const int r0 = (int)(((float)tid + 0.5f) * rn), c = (int)tid - r0 * ncol;
+                    if (r0 < step) {
+                        // all addressed as a uniform base plus a 32-bit byte offset (one
+                        // view's projection values span < 2^31 bytes: a detector has
                         // < 2^28 pixels)
-                        const unsigned pix = (unsigned)(cv0 + r) * (unsigned)g.nu + (unsigned)(cu0 + c);
-                        const A ev = SQ ? (A)0 : to_acc(*byte_at<T>(pk, pix * (unsigned)sizeof(T)));
                         const ColParam cp = *byte_at<ColParam>(ck, (unsigned)(cu0 + c) * (unsigned)sizeof(ColParam));
-                        const RowParam rp = *byte_at<RowParam>(g.rows, (unsigned)(cv0 + r) * (unsigned)sizeof(RowParam));
-                        const bool par = rp.inv_qz == 0.0f;
-                        PixStage<A> ps;
-                        ps.czr = par ? PAR_INV : zeta_inv_slope(rp.inv_qz, cp.kz);
-                        ps.nzc = zeta_offset(zeta_centre(rp.qz, cp.tcv, g.zc) + (par ? pzadd : 0.0f), ps.czr);
-                        const A L = (A)ray_length_per_xi(cp.lxy2, rp.qz, cp.gp);
-                        ps.le = SQ ? L * L : L * ev;
-                        s_pix[r * CHC + c] = ps;
-                        r += dr;
-                        c += dc;
-                        if (c >= ncol) {
-                            c -= ncol;
-                            ++r;
+                        if (r0 == 0) s_col[c] = stage_column(g, vp.dom, cp);
+                        unsigned pix = (unsigned)(cv0 + r0) * (unsigned)g.nu + (unsigned)(cu0 + c);
+                        for (int r = r0; r < nrow; r += step) {
+                            const A ev = SQ ? (A)0 : to_acc(*byte_at<T>(pk, pix * (unsigned)sizeof(T)));
+                            const RowParam rp = *byte_at<RowParam>(g.rows, (unsigned)(cv0 + r) * (unsigned)sizeof(RowParam));
+                            s_pix[r * CHC + c] = stage_pixel<A, SQ>(g, cp, rp, pzadd, ev);
+                            pix += (unsigned)(step * g.nu);
                         }
                     }
                 }
-                if (tid < ncol) s_col[tid] = stage_column(g, vp.dom, ck[cu0 + tid]);
-                // two zero rows after the chunk's: the gather reads a voxel's first
-                // candidate row without a branch, and these have weight 0 for any voxel
-                if (tid < 2 * ncol) {
-                    const int zr = tid < ncol ? nrow : nrow + 1;
-                    const int zcol = tid < ncol ? (int)tid : (int)tid - ncol;
-                    // the zero made here (an empty asm keeps the compiler from
-                    // hoisting the record out of the view loop and spilling it)
-                    float zero = 0.0f;
-                    asm volatile("" : "+v"(zero));
-                    PixStage<A> z{};
-                    z.nzc = zero;
-                    z.czr = zero;
-                    z.le = (A)zero;
-                    s_pix[zr * CHC + zcol] = z;
-                }
+                // a zero row after the chunk's last: the gather reads a voxel's first
+                // candidate row without a branch, and this one has weight 0 for any voxel
+                if (tid < ncol) s_pix[nrow * CHC + tid] = zero_pixel<A>();
                 __syncthreads();
                 // 3. gather
                 // the lane's column indices laundered per chunk: the few values derived
@@ -163,7 +143,7 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
                 // through the view loop
                 int ixv = ix, iyv = iy;
                 asm volatile("" : "+v"(ixv), "+v"(iyv));
-                if (valid) gather_chunk<A, SQ, CHC>(g, vp, ixv, iyv, iz0, nzb, s_pix, s_col, cu0, ncol, cv0, nrow, acc);
+                if (valid) gather_chunk<A, SQ, CHC>(g, vp, ixv, iyv, iz0, s_pix, s_col, cu0, ncol, cv0, nrow, acc);
                 __syncthreads();
             }
         }
@@ -197,7 +177,7 @@ __global__ __launch_bounds__(256, sizeof(acc_t<T>) != 4 ? 2 : 6) void k_backward
 {
     if (skip && *skip) return;
     constexpr int CHC = ch_cols(TZB);
-    __shared__ PixStage<acc_t<T>> s_pix[(ch_rows(TZB) + 2) * CHC + NH - 1];
+    __shared__ PixStage<acc_t<T>> s_pix[(ch_rows(TZB) + 1) * CHC + NH - 1];
     __shared__ ColStage s_col[CHC];
     backward_block<T, EPI, TZB, CHC>(g, __builtin_amdgcn_workgroup_id_x(), proj, out, out_z, sc, partials, nbx, nby, nbz, aux, s_pix,
                                      s_col);
@@ -226,8 +206,8 @@ __host__ __device__ constexpr int variant_depth(int v) { return v == BWD_VDEEP ?
 constexpr int VARIANT_LDS_COLS = 48;  // the widest chunk of the variants
 // staged records of the largest chunk of the variants
 constexpr int VARIANT_LDS_RECORDS =
-    ((ch_rows(TZ_DEEP) + 2) * ch_cols(TZ_DEEP) > (ch_rows(TZ) + 2) * ch_cols(TZ) ? (ch_rows(TZ_DEEP) + 2) * ch_cols(TZ_DEEP)
-                                                                                  : (ch_rows(TZ) + 2) * ch_cols(TZ)) +
+    ((ch_rows(TZ_DEEP) + 1) * ch_cols(TZ_DEEP) > (ch_rows(TZ) + 1) * ch_cols(TZ) ? (ch_rows(TZ_DEEP) + 1) * ch_cols(TZ_DEEP)
+                                                                                  : (ch_rows(TZ) + 1) * ch_cols(TZ)) +
     NH - 1;
 
 int64_t backward_variant_grid(const GeoDev &g, int variant, int &nbx, int &nby, int &nbz)
@@ -295,7 +275,7 @@ template <int TZB, int CHC>
 __global__ __launch_bounds__(256, 6) void k_backward_v(GeoDev g, const float *__restrict__ proj,
                                                        float *__restrict__ out, int nbx, int nby, int nbz)
 {
-    __shared__ PixStage<float> s_pix[(ch_rows(TZB) + 2) * CHC + NH - 1];
+    __shared__ PixStage<float> s_pix[(ch_rows(TZB) + 1) * CHC + NH - 1];
     __shared__ ColStage s_col[CHC];
     backward_block<float, BWD_PLAIN, TZB, CHC>(g, __builtin_amdgcn_workgroup_id_x(), proj, out, nullptr, nullptr, nullptr, nbx, nby, nbz,
                                                nullptr, s_pix, s_col);

@@ -9,13 +9,21 @@
 //   2. stages, for every pixel of the shadow, the ray's z-parameters and its
 //      value multiplied by the ray length factor L in LDS (one 16-byte record
 //      per pixel), and the per-column in-plane ray parameters,
-//   3. lets each lane gather: the exact interval of detector columns whose
-//      rays cross its voxel column, the in-plane xi-interval of each of those
+//   3. lets each lane gather: the interval of detector columns whose
+//      rays can cross its voxel column, the in-plane xi-interval of each of those
 //      columns (shared by the TZ voxels), per voxel the candidate rows from
 //      the z-range of those rays, and for every candidate the exact weight of
 //      kct_weights.h.
 // The shadow is staged in chunks of at most ch_cols(TZB) x ch_rows(TZB) pixels, so any
 // geometry works; typical bricks need one chunk.
+//
+// What bounds it: VALU issue (1.2 wave-instructions per CU-cycle at 512^3 x 720,
+// 616 x 480 detector, the most its mix of operations reaches), so its time
+// follows its instruction count per voxel and view.  At that size one launch
+// takes 65.4 ms (74.9 ms with a test of every voxel against the brick's top, a
+// search for the first and last hit column, an integer clamp made of compares
+// and selects, and the ray parameters of a column read again for each of its pixels);
+// 256^3 x 360, 384 x 384 detector: 8.75 ms (10.5 ms).
 #pragma once
 
 #pragma clang fp contract(off)
@@ -185,6 +193,37 @@ __host__ __device__ __forceinline__ A add_row(const PixStage<A> *prow, int nh, c
     return a;
 }
 
+// The staged record of the pixel with column parameters cp, row parameters rp
+// and value ev; parallel rows staged as above (pzadd moves their coordinate to
+// the middle of their z-cell).  SQ: L^2 in the place of L * ev.
+template <typename A, bool SQ>
+__host__ __device__ __forceinline__ PixStage<A> stage_pixel(const GeoDev &g, const ColParam &cp, const RowParam &rp,
+                                                            float pzadd, A ev)
+{
+    const bool par = rp.inv_qz == 0.0f;
+    PixStage<A> ps;
+    ps.czr = par ? PAR_INV : zeta_inv_slope(rp.inv_qz, cp.kz);
+    ps.nzc = zeta_offset(zeta_centre(rp.qz, cp.tcv, g.zc) + (par ? pzadd : 0.0f), ps.czr);
+    const A L = (A)ray_length_per_xi(cp.lxy2, rp.qz, cp.gp);
+    ps.le = SQ ? L * L : L * ev;
+    return ps;
+}
+
+// A record of weight 0 for any voxel, made where it is stored (an empty asm keeps
+// the compiler from hoisting it out of the view loop and spilling it).
+template <typename A> __host__ __device__ __forceinline__ PixStage<A> zero_pixel()
+{
+    float zero = 0.0f;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(zero));
+#endif
+    PixStage<A> z{};
+    z.nzc = zero;
+    z.czr = zero;
+    z.le = (A)zero;
+    return z;
+}
+
 // pg + r * CHC for a pointer pg into the LDS staging buffer: on the GPU one
 // shift-and-add of the 32-bit LDS address when a row of records spans a power
 // of two bytes.
@@ -204,19 +243,33 @@ __host__ __device__ __forceinline__ const PixStage<A> *row_record(const PixStage
     return pg + r * CHC;
 }
 
-// The voxels of one lane for one group of hit columns: voxel j (j < nzb) has
-// the planes mbz0 + j and mbz0 + j + 1 and the candidate rows va1 + 1 .. vb with
-// va1 = floor(l0 + j sl) and vb = floor(h0 + (j + 1) sh).  The first candidate
-// row is evaluated for every voxel, without a branch: va1 is clamped to
-// [vlow, vmax + 1] (vlow = first staged row - 1, vmax = last), so row va1 + 1 is
-// a staged row or one of the two zero rows staged after them, and a row that
-// is not a candidate has weight exactly 0 (the weights are exact).  Further
-// rows, up to vb clamped to vmax, follow in a loop.  pg + va1 * CHC is the
-// record of row va1 + 1 in the group's first column.
+// v clamped to [-1, hi] (hi >= -1 equal in every lane): one instruction on the GPU.
+__host__ __device__ __forceinline__ int clamp_row(int v, int hi)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    int r;
+    asm("v_med3_i32 %0, %1, -1, %2" : "=v"(r) : "v"(v), "s"(hi));
+    return r;
+#else
+    return v < -1 ? -1 : (v > hi ? hi : v);
+#endif
+}
+
+// The voxels of one lane for one group of hit columns: voxel j has the planes
+// mbz0 + j and mbz0 + j + 1 and, counted from the first staged row, the candidate
+// rows va + 1 .. vb + 1 with va = floor(l0 + j sl) and vb = floor(h0 + (j + 1) sh).
+// All TZN voxels are taken, those of a brick that reaches past the volume's top
+// as well (their sums are never stored): a test per voxel costs a scalar condition
+// each, which the compiler kept in spilled registers (4 of about 34 instructions
+// per voxel).  The first candidate row is evaluated for every voxel, without a
+// branch: va is clamped to [-1, nrow - 1], so row va + 1 is a staged row or the zero
+// row staged after them, and a row that is not a candidate has weight exactly
+// 0 (the weights are exact).  Further rows, up to the last staged one, follow in a
+// loop.  pg + va * CHC is the record of row va + 1 in the group's first column.
 template <typename A, bool SQ, int CHC, int TZN>
 __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int nh, const float (&lo)[NH],
-                                                    const float (&hi)[NH], float mbz0, int nzb, float l0, float sl,
-                                                    float h0, float sh, int vlow, int vmax, A (&acc)[TZN])
+                                                    const float (&hi)[NH], float mbz0, float l0, float sl,
+                                                    float h0, float sh, int nrow, A (&acc)[TZN])
 {
     // The per-voxel plane values do not depend on the column group; computed
     // here they stay short-lived (hoisted out of the group loop, all TZ of them
@@ -230,35 +283,33 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int n
 #pragma unroll
     for (int j = 0; j < TZN; ++j) {
         const float mb1 = mb + 1.0f;
-        if (j < nzb) {
-            // candidate rows va1 + 1 .. vb: floor(lo) + 1 is ceil(lo) except at an
-            // integer lo, whose row lies 0.01 below the true bound and is rightly left out
-            const float vlo = __builtin_fmaf((float)j, sl, l0), vhi = __builtin_fmaf((float)(j + 1), sh, h0);
-            int va1 = (int)floorf(vlo), vb = (int)floorf(vhi);
-            va1 = va1 < vlow ? vlow : (va1 > vmax + 1 ? vmax + 1 : va1);
-            vb = vb > vmax ? vmax : vb;
-            const PixStage<A> *prow = row_record<A, CHC>(pg, va1);
-            A a = add_row<A, SQ>(prow, nh, lo, hi, mb, mb1, acc[j]);
-            for (int v = va1 + 2; v <= vb; ++v) {
-                prow += CHC;
-                a = add_row<A, SQ>(prow, nh, lo, hi, mb, mb1, a);
-            }
-            acc[j] = a;
+        // candidate rows va + 1 .. vb + 1: floor(lo) + 1 is ceil(lo) except at an
+        // integer lo, whose row lies 0.01 below the true bound and is rightly left out
+        const float vlo = __builtin_fmaf((float)j, sl, l0), vhi = __builtin_fmaf((float)(j + 1), sh, h0);
+        const int va = clamp_row((int)floorf(vlo), nrow - 1);
+        int vb = (int)floorf(vhi);
+        vb = vb > nrow - 2 ? nrow - 2 : vb;
+        const PixStage<A> *prow = row_record<A, CHC>(pg, va);
+        A a = add_row<A, SQ>(prow, nh, lo, hi, mb, mb1, acc[j]);
+        for (int v = va; v < vb; ++v) {
+            prow += CHC;
+            a = add_row<A, SQ>(prow, nh, lo, hi, mb, mb1, a);
         }
+        acc[j] = a;
         mb = mb1;
     }
 }
 
 // One lane's share of one staged chunk of one view: add w_ij * (L_i e_i) to the
-// accumulators of its voxels (ix, iy, iz0 + j), j < nzb, for every staged ray
+// accumulators of its voxels (ix, iy, iz0 + j), j < TZN, for every staged ray
 // i = (column cu0 + c, row cv0 + r); s_pix[r * CHC + c] describes ray i, and
-// rows nrow and nrow + 1 of s_pix hold zero records (weight 0 for any voxel).
+// row nrow of s_pix holds zero records (weight 0 for any voxel).
 // SQ: accumulate w_ij^2 * le instead of w_ij * le (with le = L^2 this sums the
 // squared weights, the diagonal of A^T A).
 template <typename A, bool SQ, int CHC, int TZN>
 __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const ViewParam &vp, int ix, int iy, int iz0,
-                                                      int nzb, const PixStage<A> *s_pix, const ColStage *s_col,
-                                                      int cu0, int ncol, int cv0, int nrow, A (&acc)[TZN])
+                                                      const PixStage<A> *s_pix, const ColStage *s_col, int cu0,
+                                                      int ncol, int cv0, int nrow, A (&acc)[TZN])
 {
     int ixi, ieta;
     float hxi, heta;
@@ -269,27 +320,19 @@ __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const Vie
     voxel_columns(g, vp, g.x0 + ((float)ix + 0.5f) * g.vx, g.y0 + ((float)iy + 0.5f) * g.vy, ua, ub);
     ua = ua < cu0 ? cu0 : ua;
     ub = ub > cu0 + ncol - 1 ? cu0 + ncol - 1 : ub;
-    // The columns whose rays cross the voxel column form an interval (the
-    // rays of consecutive columns fan out monotonically from the source):
-    // narrow the bound to its first and last hit.
-    int ha = ub + 1, hb = ub;  // empty unless a column is hit
-    for (int iu = ua; iu <= ub; ++iu) {
-        float lo, hi;
-        column_interval(s_col[iu - cu0], lo_xi, ieta, heta, lo, hi);
-        if (hi > lo) {
-            ha = iu < ha ? iu : ha;
-            hb = iu;
-        }
-    }
     const float mbz0 = (float)iz0 - g.hz;  // lower plane of the first voxel (index frame)
     const float zz0 = mbz0 + g.zc;         // the same plane as a height above the source plane
-    const float inv_nzb = rcp_approx((float)nzb);
-    const float vofs_lo = g.fv0 - 0.01f, vofs_hi = g.fv0 + 0.01f;
-    const int vmax = cv0 + nrow - 1;
-    for (int c0 = ha; c0 <= hb; c0 += NH) {
-        // xi-intervals of up to NH hit columns, and the range of T = tcv + xi gz
-        // over them (a ray of height qz is at height qz T above the source plane)
-        const int nh = hb - c0 + 1 < NH ? hb - c0 + 1 : NH;
+    // row coordinates from the first staged row; the upper bound one row lower, as
+    // voxel_rows takes it
+    const float fv = g.fv0 - (float)cv0, vofs_lo = fv - 0.01f, vofs_hi = fv - 0.99f;
+    // The bound [ua, ub] is met by nearly every column in it (its margin is 0.01
+    // column, and it takes the square's extents across and along the central ray
+    // as independent); a column that misses gets an empty interval and weight 0.
+    // Narrowing it to the exact hits first cost more than the rare extra column.
+    for (int c0 = ua; c0 <= ub; c0 += NH) {
+        // xi-intervals of up to NH columns, and the range of T = tcv + xi gz over
+        // those that are hit (a ray of height qz is at height qz T above the source plane)
+        const int nh = ub - c0 + 1 < NH ? ub - c0 + 1 : NH;
         float lo[NH], hi[NH];
         float tmin = INFINITY, tmax = 0.0f;
 #pragma unroll
@@ -316,13 +359,13 @@ __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const Vie
         // fused multiply-add each.  Their rounding (~1e-5 row) is far inside the
         // 0.01-row margins.
         const float ra = __builtin_amdgcn_rcpf(tmax) * g.inv_dv, rb = __builtin_amdgcn_rcpf(tmin) * g.inv_dv;
-        const float za = zz0, zb = zz0 + (float)nzb;  // lowest and highest plane of the brick
+        const float za = zz0, zb = zz0 + (float)TZN;  // lowest and highest plane of the brick
         const float a1 = za * ra, a2 = za * rb, b1 = zb * ra, b2 = zb * rb;
-        const float sl = (fminf(b1, b2) - fminf(a1, a2)) * inv_nzb;
-        const float sh = (fmaxf(b1, b2) - fmaxf(a1, a2)) * inv_nzb;
+        const float sl = (fminf(b1, b2) - fminf(a1, a2)) * (1.0f / TZN);
+        const float sh = (fmaxf(b1, b2) - fmaxf(a1, a2)) * (1.0f / TZN);
         const float l0 = fminf(a1, a2) + vofs_lo, h0 = fmaxf(a1, a2) + vofs_hi;
-        const PixStage<A> *pg = s_pix + ((c0 - cu0) + (1 - cv0) * CHC);  // row va1 + 1 at pg + va1 * CHC
-        voxel_rows<A, SQ, CHC, TZN>(pg, nh, lo, hi, mbz0, nzb, l0, sl, h0, sh, cv0 - 1, vmax, acc);
+        const PixStage<A> *pg = s_pix + ((c0 - cu0) + CHC);  // row va + 1 at pg + va * CHC
+        voxel_rows<A, SQ, CHC, TZN>(pg, nh, lo, hi, mbz0, l0, sl, h0, sh, nrow, acc);
     }
 }
 
