@@ -265,8 +265,8 @@ kct_status kct_batch_workspace_size(kct_batch b, size_t *bytes);
 
 /* Autotuner: for each instance, time its forward projection with one and with
  * two detector rows per lane, and its backprojection with each brick shape
- * (16-deep bricks staged in 48-column chunks, 20-deep bricks in 32-column
- * chunks), 3 launches each after a warm-up (HIP events), and keep the faster of
+ * (0: the single solve's form for the instance without the 32-deep bricks, 1: the
+ * 32-deep bricks), 3 launches each after a warm-up (HIP events), and keep the faster of
  * each for the batch's solves (a tuned instance may then differ from its own
  * kct_cgls_solve by the rounding of regrouped partial sums).  cache_path
  * (host, optional): a text file of "<sizes> <rows per lane> <brick shape>"

@@ -35,7 +35,7 @@ def flags():
     ]
 
 
-PROJECTOR_SOURCES = {"projector.hip", "backproject.hip", "tt.hip"}
+PROJECTOR_SOURCES = {"projector.hip", "backproject.hip", "backproject_wave.hip", "tt.hip"}
 
 
 def source_flags(src):

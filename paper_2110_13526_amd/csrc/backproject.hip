@@ -14,6 +14,7 @@
 #include "kct_epilogue.h"
 #include "kct_gather.h"
 #include "kct_internal.h"
+#include "kct_wave.h"
 #include "kct_weights.h"
 
 namespace kct {
@@ -30,12 +31,6 @@ __device__ __forceinline__ double bwd_block_sum(double v)
     double r = 0.0;
     if (__builtin_amdgcn_workitem_id_x() == 0) r = (red[0] + red[1]) + (red[2] + red[3]);
     return r;
-}
-
-// The element of type E at byte offset off from base.
-template <typename E> __device__ __forceinline__ const E *byte_at(const void *base, unsigned off)
-{
-    return reinterpret_cast<const E *>(static_cast<const char *>(base) + off);
 }
 
 // backward_block runs workgroup w (0 <= w < nbx * nby * nbz) of the
@@ -68,11 +63,6 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
     const int sbi = __builtin_amdgcn_readfirstlane(by * g.sbx + bx);  // uniform: the table row stays scalar
     const size_t sbxy = (size_t)g.sbx * g.sby;
     const float wz0 = g.z0 + (float)iz0 * g.vz, wz1 = g.z0 + (float)(iz0 + nzb) * g.vz;
-
-    // rays parallel to the z-planes lie in z-cell pcell; their staged zc is
-    // that cell's middle (see PixStage)
-    const int pcell = parallel_cell(-g.zc, g.hz);
-    const float pzadd = ((float)pcell - g.hz + 0.5f) + g.zc;
 
     A acc[TZB];
 #pragma unroll
@@ -124,12 +114,15 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
                         // < 2^28 pixels)
                         const ColParam cp = *byte_at<ColParam>(ck, (unsigned)(cu0 + c) * (unsigned)sizeof(ColParam));
                         if (r0 == 0) s_col[c] = stage_column(g, vp.dom, cp);
-                        unsigned pix = (unsigned)(cv0 + r0) * (unsigned)g.nu + (unsigned)(cu0 + c);
+                        unsigned pix = ((unsigned)(cv0 + r0) * (unsigned)g.nu + (unsigned)(cu0 + c)) * (unsigned)sizeof(T);
+                        unsigned row = (unsigned)(cv0 + r0) * (unsigned)sizeof(RowParam);
+                        PixStage<A> *rec = s_pix + (r0 * CHC + c);
                         for (int r = r0; r < nrow; r += step) {
-                            const A ev = SQ ? (A)0 : to_acc(*byte_at<T>(pk, pix * (unsigned)sizeof(T)));
-                            const RowParam rp = *byte_at<RowParam>(g.rows, (unsigned)(cv0 + r) * (unsigned)sizeof(RowParam));
-                            s_pix[r * CHC + c] = stage_pixel<A, SQ>(g, cp, rp, pzadd, ev);
-                            pix += (unsigned)(step * g.nu);
+                            const A ev = SQ ? (A)0 : to_acc(*byte_at<T>(pk, pix));
+                            *rec = stage_pixel<A, SQ>(cp, *byte_at<RowParam>(g.rows, row), ev);
+                            pix += (unsigned)(step * g.nu) * (unsigned)sizeof(T);
+                            row += (unsigned)step * (unsigned)sizeof(RowParam);
+                            rec += step * CHC;
                         }
                     }
                 }
@@ -143,7 +136,7 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
                 // through the view loop
                 int ixv = ix, iyv = iy;
                 asm volatile("" : "+v"(ixv), "+v"(iyv));
-                if (valid) gather_chunk<A, SQ, CHC>(g, vp, ixv, iyv, iz0, s_pix, s_col, cu0, ncol, cv0, nrow, acc);
+                if (valid) gather_chunk<A, SQ, CHC, NH>(g, vp, ixv, iyv, iz0, s_pix, s_col, cu0, ncol, cv0, nrow, acc);
                 __syncthreads();
             }
         }
@@ -183,64 +176,131 @@ __global__ __launch_bounds__(256, sizeof(acc_t<T>) != 4 ? 2 : 6) void k_backward
                                      s_col);
 }
 
-// Brick depth of a single backprojection: TZ_DEEP voxels per lane when the
-// volume still gives at least 5120 such bricks (over three rounds of six workgroups
-// per compute unit), else TZ (small volumes need the workgroups more than the
-// shared setup).
-static int bwd_depth(const GeoDev &g)
+static BwdPlan brick_plan(const GeoDev &g, int form)
 {
-    const int64_t deep = (int64_t)((g.nx + BX - 1) / BX) * ((g.ny + BY - 1) / BY) * ((g.nz + TZ_DEEP - 1) / TZ_DEEP);
-    return deep >= 5120 ? TZ_DEEP : TZ;
+    BwdPlan p{};
+    p.form = form;
+    p.tz = form == BWD_DEEP ? TZ_DEEP : TZ;
+    p.sets = 1;
+    p.nbx = (g.nx + BX - 1) / BX;
+    p.nby = (g.ny + BY - 1) / BY;
+    p.nbz = (g.nz + p.tz - 1) / p.tz;
+    p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
+    return p;
 }
 
-static void bwd_grid(const GeoDev &g, int tz, int &nbx, int &nby, int &nbz)
+// Expected shadow of n voxel columns a side and tz layers, in pixels at the
+// isocentre's magnification: columns over the diagonal, rows, each with a little
+// for the nearer half of the orbit and for the ends.
+static float shadow_cols(const GeoDev &g, int n)
 {
-    nbx = (g.nx + BX - 1) / BX;
-    nby = (g.ny + BY - 1) / BY;
-    nbz = (g.nz + tz - 1) / tz;
+    return 1.05f * 1.4142f * (float)n * fmaxf(g.vx, g.vy) * g.ku / g.sid + 2.0f;
+}
+static float shadow_rows(const GeoDev &g, int tz) { return 1.1f * (float)tz * g.vz * g.kv / g.sid + 3.0f; }
+
+// Wave form: the deepest brick whose shadow is expected to fit one chunk and that
+// leaves enough bricks, and as many view subsets as fill the chip.  Measured (us,
+// cube of n voxels, q detector pixels per voxel at the isocentre, depth 32 / 16 / 8 / 4):
+// n 128, q 0.7: 287 / 338 / 413 / -; n 192, q 1.25: - / 1405 / 1493 / 2800;
+// n 192, q 1.6: - / - / 2125 / 2480; n 192, q 2.2: - / - / 4700 / 4258; n 64, q 2: - / - / 96 / 110.
+// Subsets 4 / 8 / 16: 64^3, q 0.7 (256 bricks): - / 49 / 35; 128^3, q 1.25 (2048): 702 / 680 / 703;
+// 192^3, q 1.25 (6912): 1405 / 1566 / 1592.
+static BwdPlan wave_plan(const GeoDev &g)
+{
+    BwdPlan p{};
+    p.form = BWD_WAVES;
+    p.nbx = (g.nx + WX - 1) / WX;
+    p.nby = (g.ny + WY - 1) / WY;
+    const float cols = shadow_cols(g, WX);
+    for (p.tz = 32; p.tz > 4; p.tz /= 2) {
+        const float records = cols * (shadow_rows(g, p.tz) + 1.0f);
+        p.nbz = (g.nz + p.tz - 1) / p.tz;
+        p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
+        // a second chunk now and then costs less than bricks of 4
+        if (records <= (p.tz == 8 ? 1.3f : 1.0f) * (float)W_CAP && p.nblocks >= (p.tz == 32 ? 1024 : 192)) break;
+    }
+    p.nbz = (g.nz + p.tz - 1) / p.tz;
+    p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
+    // (bricks of 32: one subset per wavefront of the batched form, whose second set of
+    // sums would not fit its registers)
+    p.sets = p.tz == 32 || p.nblocks > 2048 ? 4 : (p.nblocks > 512 ? 8 : 16);
+    return p;
 }
 
-// Backprojection variants of the batched form (BwdVariant): brick depth and
-// staged chunk width.
-__host__ __device__ constexpr int variant_depth(int v) { return v == BWD_VDEEP ? TZ_DEEP : TZ; }
-constexpr int VARIANT_LDS_COLS = 48;  // the widest chunk of the variants
-// staged records of the largest chunk of the variants
-constexpr int VARIANT_LDS_RECORDS =
-    ((ch_rows(TZ_DEEP) + 1) * ch_cols(TZ_DEEP) > (ch_rows(TZ) + 1) * ch_cols(TZ) ? (ch_rows(TZ_DEEP) + 1) * ch_cols(TZ_DEEP)
-                                                                                  : (ch_rows(TZ) + 1) * ch_cols(TZ)) +
-    NH - 1;
-
-int64_t backward_variant_grid(const GeoDev &g, int variant, int &nbx, int &nby, int &nbz)
+// A single backprojection's form.  Workgroup bricks where there are enough of them
+// to fill the chip two and a half times over (six workgroups per compute unit)
+// and the shadow is expected to fit one staged chunk; wave form elsewhere.
+// Measured (us, wave form / 16-deep / 32-deep bricks; n and q as above):
+//   q 0.7:  n 192 657 / 788 / 694, n 256 1100 / 1013 / 982, n 400 2826 / 2429 / 2064
+//   q 1.25: n 192 1405 / 1672 / -, n 256 2398 / 2126 / 2700, n 400 5775 / 4821 / 6692
+//   q 1.6:  n 192 2124 / 2632 / -, n 256 3733 / 3488 / 6903, n 400 9219 / 7545 / 12683
+//   q 2.2:  n 256 7528 / 8673 / -, n 400 19068 / 19626 / 30666
+static BwdPlan plan(const GeoDev &g, bool deep_allowed)
 {
-    bwd_grid(g, variant_depth(variant), nbx, nby, nbz);
-    return (int64_t)nbx * nby * nbz;
+    const BwdPlan deep = brick_plan(g, BWD_DEEP), shallow = brick_plan(g, BWD_BRICKS);
+    const float cols = shadow_cols(g, BX);
+    if (deep_allowed && deep.nblocks >= 2048 && cols <= (float)ch_cols(TZ_DEEP) &&
+        shadow_rows(g, TZ_DEEP) <= (float)ch_rows(TZ_DEEP))
+        return deep;
+    if (shallow.nblocks >= 4096 && cols <= (float)ch_cols(TZ) && shadow_rows(g, TZ) <= (float)ch_rows(TZ)) return shallow;
+    return wave_plan(g);
+}
+
+BwdPlan backward_plan(const GeoDev &g) { return plan(g, true); }
+
+BwdPlan backward_plan_variant(const GeoDev &g, int variant)
+{
+    return variant == BWD_VDEEP ? brick_plan(g, BWD_DEEP) : plan(g, false);
 }
 
 // The variant a single solve would use: its block decomposition (and so its
 // partial sums) is that of kct_cgls_solve.
-int backward_default_variant(const GeoDev &g) { return bwd_depth(g) == TZ_DEEP ? BWD_VDEEP : BWD_VSHALLOW; }
+int backward_default_variant(const GeoDev &g) { return backward_plan(g).form == BWD_DEEP ? BWD_VDEEP : BWD_VSHALLOW; }
 
-// One tile (brick) of variant v of instance bi's r = A^T e with |r|^2 partials.
-__device__ __forceinline__ void batch_backward_tile(const BatchInst *bi, int lw, PixStage<float> *s_pix,
-                                                    ColStage *s_col)
+constexpr int BRICK_LDS_COLS = 48;  // the widest chunk of the workgroup bricks
+constexpr int BRICK_LDS_RECORDS =
+    ((ch_rows(TZ_DEEP) + 1) * ch_cols(TZ_DEEP) > (ch_rows(TZ) + 1) * ch_cols(TZ) ? (ch_rows(TZ_DEEP) + 1) * ch_cols(TZ_DEEP)
+                                                                                  : (ch_rows(TZ) + 1) * ch_cols(TZ)) +
+    NH - 1;
+constexpr size_t BATCH_LDS = wave_lds_bytes(W_GROUPS) > BRICK_LDS_RECORDS * sizeof(PixStage<float>) + BRICK_LDS_COLS * sizeof(ColStage)
+                                 ? wave_lds_bytes(W_GROUPS)
+                                 : BRICK_LDS_RECORDS * sizeof(PixStage<float>) + BRICK_LDS_COLS * sizeof(ColStage);
+
+// One tile (brick) of instance bi's r = A^T e with |r|^2 partials.  Wave form: the
+// four wavefronts take the view subsets of the single solve in turns.
+__device__ __forceinline__ void batch_backward_tile(const BatchInst *bi, int lw, char *lds)
 {
-    if (bi->bwd_v == BWD_VDEEP)
-        backward_block<float, BWD_NORM, TZ_DEEP, 32>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, bi->nbx,
-                                                    bi->nby, bi->nbz, nullptr, s_pix, s_col);
+    const BwdPlan p = bi->bwd;
+    PixStage<float> *s_pix = reinterpret_cast<PixStage<float> *>(lds);
+    ColStage *s_col = reinterpret_cast<ColStage *>(s_pix + BRICK_LDS_RECORDS);
+    if (p.form == BWD_DEEP)
+        backward_block<float, BWD_NORM, TZ_DEEP, ch_cols(TZ_DEEP)>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part,
+                                                                   p.nbx, p.nby, p.nbz, nullptr, s_pix, s_col);
+    else if (p.form == BWD_BRICKS)
+        backward_block<float, BWD_NORM, TZ, ch_cols(TZ)>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
+                                                         p.nbz, nullptr, s_pix, s_col);
+    else if (p.tz == 32)
+        backward_wave_block<float, BWD_NORM, 32, false>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
+                                                        p.nbz, nullptr, W_GROUPS, 1, lds);
+    else if (p.tz == 16)
+        backward_wave_block<float, BWD_NORM, 16, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
+                                                       p.nbz, nullptr, W_GROUPS, p.sets / W_GROUPS, lds);
+    else if (p.tz == 8)
+        backward_wave_block<float, BWD_NORM, 8, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
+                                                      p.nbz, nullptr, W_GROUPS, p.sets / W_GROUPS, lds);
     else
-        backward_block<float, BWD_NORM, TZ, 48>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, bi->nbx, bi->nby,
-                                               bi->nbz, nullptr, s_pix, s_col);
+        backward_wave_block<float, BWD_NORM, 4, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
+                                                      p.nbz, nullptr, W_GROUPS, p.sets / W_GROUPS, lds);
 }
 
 // Persistent batched r = A^T e: every workgroup takes items from the queue
 // until it is empty (see BatchInst); each item is up to BATCH_ITEM_BWD bricks
 // of one instance.
-__global__ __launch_bounds__(256, 6) void kp_backward(const BatchInst *__restrict__ B,
+__global__ __launch_bounds__(256, 5) void kp_backward(const BatchInst *__restrict__ B,
                                                       const int64_t *__restrict__ off, int count,
                                                       BatchQueue *__restrict__ q)
 {
-    __shared__ PixStage<float> s_pix[VARIANT_LDS_RECORDS];
-    __shared__ ColStage s_col[VARIANT_LDS_COLS];
+    __shared__ __align__(16) char lds[BATCH_LDS];
     const int64_t total = off[count];
     for (;;) {
         const int64_t item = batch_pop(q);
@@ -251,7 +311,7 @@ __global__ __launch_bounds__(256, 6) void kp_backward(const BatchInst *__restric
         const int64_t t0 = (item - off[i]) * BATCH_ITEM_BWD;
         const int64_t t1 = t0 + BATCH_ITEM_BWD < bi->nbk ? t0 + BATCH_ITEM_BWD : bi->nbk;
         for (int64_t t = t0; t < t1; ++t) {
-            batch_backward_tile(bi, (int)t, s_pix, s_col);
+            batch_backward_tile(bi, (int)t, lds);
             __syncthreads();  // the tile's block sum is read before the next tile writes it
         }
     }
@@ -270,53 +330,35 @@ hipError_t launch_batch_backward(const BatchInst *B, const int64_t *off, int cou
     return hipGetLastError();
 }
 
-// A single plain backprojection with batched-form variant v (the tuner times these).
-template <int TZB, int CHC>
-__global__ __launch_bounds__(256, 6) void k_backward_v(GeoDev g, const float *__restrict__ proj,
-                                                       float *__restrict__ out, int nbx, int nby, int nbz)
+template <typename T, int EPI>
+static void launch_bricks(const GeoDev &g, const BwdPlan &p, const T *proj, T *out, T *out_z, const Scalars *sc,
+                          double *partials, const int *skip, const float *aux, hipStream_t st)
 {
-    __shared__ PixStage<float> s_pix[(ch_rows(TZB) + 1) * CHC + NH - 1];
-    __shared__ ColStage s_col[CHC];
-    backward_block<float, BWD_PLAIN, TZB, CHC>(g, __builtin_amdgcn_workgroup_id_x(), proj, out, nullptr, nullptr, nullptr, nbx, nby, nbz,
-                                               nullptr, s_pix, s_col);
+    const dim3 grid((unsigned)p.nblocks);
+    if (p.form == BWD_DEEP)
+        hipLaunchKernelGGL((k_backward<T, EPI, TZ_DEEP>), grid, dim3(256), 0, st, g, proj, out, out_z, sc, partials,
+                           skip, p.nbx, p.nby, p.nbz, aux);
+    else
+        hipLaunchKernelGGL((k_backward<T, EPI, TZ>), grid, dim3(256), 0, st, g, proj, out, out_z, sc, partials, skip,
+                           p.nbx, p.nby, p.nbz, aux);
 }
 
+// A single plain backprojection with batched-form variant v (the tuner times these).
 hipError_t launch_backward_variant(const GeoDev &g, int variant, const float *proj, float *out, hipStream_t st)
 {
-    int nbx, nby, nbz;
-    const int64_t nb = backward_variant_grid(g, variant, nbx, nby, nbz);
-    if (variant == BWD_VDEEP)
-        hipLaunchKernelGGL((k_backward_v<TZ_DEEP, 32>), dim3((unsigned)nb), dim3(256), 0, st, g, proj, out, nbx, nby,
-                           nbz);
-    else
-        hipLaunchKernelGGL((k_backward_v<TZ, 48>), dim3((unsigned)nb), dim3(256), 0, st, g, proj, out, nbx, nby, nbz);
+    const BwdPlan p = backward_plan_variant(g, variant);
+    if (p.form == BWD_WAVES)
+        return launch_backward_waves<float>(g, p, proj, out, nullptr, BWD_PLAIN, nullptr, nullptr, nullptr, st, nullptr);
+    launch_bricks<float, BWD_PLAIN>(g, p, proj, out, nullptr, nullptr, nullptr, nullptr, nullptr, st);
     return hipGetLastError();
 }
 
-// Workgroups (and partial sums) of a single backprojection with g: at most the
-// count of TZ-deep bricks.
+// Workgroups (and partial sums) of a single backprojection with g.
 int64_t backward_num_blocks(const GeoDev &g)
 {
     int nbx, nby, nbz;
     if (g.projector == KCT_PROJECTOR_TT) return tt_backward_grid_dims(g, nbx, nby, nbz);
-    bwd_grid(g, bwd_depth(g), nbx, nby, nbz);
-    return (int64_t)nbx * nby * nbz;
-}
-
-template <typename T, int EPI>
-static void launch_bwd(const GeoDev &g, const T *proj, T *out, T *out_z, const Scalars *sc, double *partials,
-                       const int *skip, const float *aux, hipStream_t st)
-{
-    const int tz = bwd_depth(g);
-    int nbx, nby, nbz;
-    bwd_grid(g, tz, nbx, nby, nbz);
-    const dim3 grid((unsigned)(nbx * nby * nbz));
-    if (tz == TZ_DEEP)
-        hipLaunchKernelGGL((k_backward<T, EPI, TZ_DEEP>), grid, dim3(256), 0, st, g, proj, out, out_z, sc, partials,
-                           skip, nbx, nby, nbz, aux);
-    else
-        hipLaunchKernelGGL((k_backward<T, EPI, TZ>), grid, dim3(256), 0, st, g, proj, out, out_z, sc, partials, skip,
-                           nbx, nby, nbz, aux);
+    return backward_plan(g).nblocks;
 }
 
 template <typename T>
@@ -324,25 +366,27 @@ hipError_t launch_backward(const GeoDev &g, const T *proj, T *out, T *out_z, int
                            double *partials, const int *skip, hipStream_t st, const float *aux)
 {
     if (g.projector == KCT_PROJECTOR_TT) return launch_backward_tt<T>(g, proj, out, out_z, epi, sc, partials, skip, st, aux);
+    const BwdPlan p = backward_plan(g);
+    if (p.form == BWD_WAVES) return launch_backward_waves<T>(g, p, proj, out, out_z, epi, sc, partials, skip, st, aux);
     if constexpr (std::is_same<T, double>::value) {  // double storage: plain backprojection only
         if (epi != BWD_PLAIN) return hipErrorInvalidValue;
-        launch_bwd<T, BWD_PLAIN>(g, proj, out, out_z, sc, partials, skip, aux, st);
+        launch_bricks<T, BWD_PLAIN>(g, p, proj, out, out_z, sc, partials, skip, aux, st);
     } else {
         switch (epi) {
-        case BWD_PLAIN: launch_bwd<T, BWD_PLAIN>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        case BWD_NORM: launch_bwd<T, BWD_NORM>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        case BWD_LSQR0: launch_bwd<T, BWD_LSQR0>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        case BWD_LSQR: launch_bwd<T, BWD_LSQR>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        case BWD_TIK: launch_bwd<T, BWD_TIK>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        case BWD_JACOBI: launch_bwd<T, BWD_JACOBI>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
+        case BWD_PLAIN: launch_bricks<T, BWD_PLAIN>(g, p, proj, out, out_z, sc, partials, skip, aux, st); break;
+        case BWD_NORM: launch_bricks<T, BWD_NORM>(g, p, proj, out, out_z, sc, partials, skip, aux, st); break;
+        case BWD_LSQR0: launch_bricks<T, BWD_LSQR0>(g, p, proj, out, out_z, sc, partials, skip, aux, st); break;
+        case BWD_LSQR: launch_bricks<T, BWD_LSQR>(g, p, proj, out, out_z, sc, partials, skip, aux, st); break;
+        case BWD_TIK: launch_bricks<T, BWD_TIK>(g, p, proj, out, out_z, sc, partials, skip, aux, st); break;
+        case BWD_JACOBI: launch_bricks<T, BWD_JACOBI>(g, p, proj, out, out_z, sc, partials, skip, aux, st); break;
         default:
             if constexpr (std::is_same<T, float>::value) {  // the diagonal of A^T A is single precision
                 if (epi == BWD_DIAG) {
-                    launch_bwd<T, BWD_DIAG>(g, proj, out, out_z, sc, partials, skip, aux, st);
+                    launch_bricks<T, BWD_DIAG>(g, p, proj, out, out_z, sc, partials, skip, aux, st);
                     break;
                 }
                 if (epi == BWD_DIAG_INV) {
-                    launch_bwd<T, BWD_DIAG_INV>(g, proj, out, out_z, sc, partials, skip, aux, st);
+                    launch_bricks<T, BWD_DIAG_INV>(g, p, proj, out, out_z, sc, partials, skip, aux, st);
                     break;
                 }
             }

@@ -13,8 +13,8 @@
 // latency of every instance inside the batch is measured.
 //
 // The autotuner picks, per instance, the forward variant (1 or 2 detector rows
-// per lane) and the backprojection variant (brick depth and staged chunk
-// width) by timing them on the instance's geometry, and can keep its choices
+// per lane) and the backprojection variant (with or without the deep bricks) by
+// timing them on the instance's geometry, and can keep its choices
 // in a text file keyed by the instance's sizes.
 #include <algorithm>
 #include <cstdio>
@@ -64,9 +64,8 @@ int64_t inst_ndir(const Geometry *g)
 int64_t inst_partials(const Geometry *g)
 {
     int64_t a = std::max(forward_num_blocks_r(g->dev, 1), forward_num_blocks_r(g->dev, 2));
-    int nbx, nby, nbz;
     int64_t bmax = 0;
-    for (int v = 0; v < BWD_VARIANTS; ++v) bmax = std::max(bmax, backward_variant_grid(g->dev, v, nbx, nby, nbz));
+    for (int v = 0; v < BWD_VARIANTS; ++v) bmax = std::max(bmax, backward_plan_variant(g->dev, v).nblocks);
     return std::max(std::max(a, bmax), stream_num_blocks());
 }
 
@@ -358,8 +357,8 @@ kct_status kct_batch_cgls_solve(kct_batch h, const float *const *bs, float *cons
         t.n = inst_n(g);
         t.m = inst_m(g);
         t.fwd_r = b->fwd_r[i];
-        t.bwd_v = b->bwd_v[i];
-        t.nbk = backward_variant_grid(g->dev, t.bwd_v, t.nbx, t.nby, t.nbz);
+        t.bwd = backward_plan_variant(g->dev, b->bwd_v[i]);
+        t.nbk = t.bwd.nblocks;
         t.nf = forward_num_blocks_r(g->dev, t.fwd_r);
         t.ndir = inst_ndir(g);
         t.b = bs[i];

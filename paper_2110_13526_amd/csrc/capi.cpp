@@ -75,7 +75,7 @@ int64_t num_partials(const Geometry *g)
 {
     // the largest forward grid of every projector and variant (the workspace may
     // be sized before the projector is chosen)
-    int64_t a = forward_num_blocks_r(g->dev, 1), b = backward_num_blocks(g->dev), c = stream_num_blocks();
+    int64_t a = forward_num_blocks_r(g->dev, 1), b = backward_plan(g->dev).nblocks, c = stream_num_blocks();
     const int64_t t = tt_forward_num_blocks(g->dev);
     if (t > a) a = t;
     int nbx, nby, nbz;

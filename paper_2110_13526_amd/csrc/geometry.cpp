@@ -87,6 +87,11 @@ kct_status geometry_tables(const kct_volume_desc &vol, const kct_cone_desc &cone
         double qz = ((double)iv - 0.5 * (nv - 1)) * cone.dv + cone.off_v;
         rows[iv].qz = (float)qz;
         rows[iv].inv_qz = qz != 0.0 ? (float)(1.0 / qz) : 0.0f;
+        const float zc = (float)(oz / vol.vz);
+        const bool par = rows[iv].inv_qz == 0.0f;
+        rows[iv].s_inv = par ? PAR_INV_QZ : rows[iv].inv_qz;
+        // a parallel row lies in z-cell floor(hz - zc): moved to its middle
+        rows[iv].s_off = par ? (std::floor(-zc + (float)hz) - (float)hz) + 0.5f : -zc;
     }
 
     for (int k = 0; k < nk; ++k) {

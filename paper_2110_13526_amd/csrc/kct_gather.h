@@ -50,13 +50,13 @@ struct ColStage {  // per staged detector column: in-plane ray parameters
 };
 
 // Rays parallel to a family of planes are staged as if they crossed them at a
-// slope of PAR_INV, with their coordinate on that axis moved to the middle of
-// the cell they lie in: every plane is then crossed at least PAR_INV / 2 from
-// the origin, far outside any xi-interval (finite, so the two crossings of a
-// cell never give inf - inf), and the general crossing formula gives exactly
-// the parallel-ray intervals of kct_weights.h: everything inside the ray's
-// cell, nothing elsewhere.  Staged records and columns therefore need no
-// parallel case.
+// very steep slope (PAR_INV; for rows PAR_INV_QZ * kz), with their coordinate on
+// that axis moved to the middle of the cell they lie in: every plane is then
+// crossed at least half that far from the origin, far outside any xi-interval
+// (finite, so the two crossings of a cell never give inf - inf), and the general
+// crossing formula gives exactly the parallel-ray intervals of kct_weights.h:
+// everything inside the ray's cell, nothing elsewhere.  Staged records and
+// columns therefore need no parallel case.
 constexpr float PAR_INV = 1.0e30f;
 
 // Per staged pixel.  czr is d xi / d zeta of the pixel's ray and nzc its
@@ -170,7 +170,7 @@ template <> __host__ __device__ __forceinline__ PixStage<float> load_pix<float>(
 // mb1.  Returns a + sum of w * (L e) (w^2 * le when SQ).  All NH records are
 // read before the first is used; the staging buffer holds a spare record past
 // its last, so prow + NH - 1 is always inside it.
-template <typename A, bool SQ>
+template <typename A, bool SQ, int NH>
 __host__ __device__ __forceinline__ A add_row(const PixStage<A> *prow, int nh, const float (&lo)[NH],
                                               const float (&hi)[NH], float mb, float mb1, A a)
 {
@@ -194,16 +194,13 @@ __host__ __device__ __forceinline__ A add_row(const PixStage<A> *prow, int nh, c
 }
 
 // The staged record of the pixel with column parameters cp, row parameters rp
-// and value ev; parallel rows staged as above (pzadd moves their coordinate to
-// the middle of their z-cell).  SQ: L^2 in the place of L * ev.
+// and value ev (parallel rows as above).  SQ: L^2 in the place of L * ev.
 template <typename A, bool SQ>
-__host__ __device__ __forceinline__ PixStage<A> stage_pixel(const GeoDev &g, const ColParam &cp, const RowParam &rp,
-                                                            float pzadd, A ev)
+__host__ __device__ __forceinline__ PixStage<A> stage_pixel(const ColParam &cp, const RowParam &rp, A ev)
 {
-    const bool par = rp.inv_qz == 0.0f;
     PixStage<A> ps;
-    ps.czr = par ? PAR_INV : zeta_inv_slope(rp.inv_qz, cp.kz);
-    ps.nzc = zeta_offset(zeta_centre(rp.qz, cp.tcv, g.zc) + (par ? pzadd : 0.0f), ps.czr);
+    ps.czr = zeta_inv_slope(rp.s_inv, cp.kz);
+    ps.nzc = zeta_offset(zeta_centre(rp.qz, cp.tcv, -rp.s_off), ps.czr);
     const A L = (A)ray_length_per_xi(cp.lxy2, rp.qz, cp.gp);
     ps.le = SQ ? L * L : L * ev;
     return ps;
@@ -224,11 +221,13 @@ template <typename A> __host__ __device__ __forceinline__ PixStage<A> zero_pixel
     return z;
 }
 
-// pg + r * CHC for a pointer pg into the LDS staging buffer: on the GPU one
-// shift-and-add of the 32-bit LDS address when a row of records spans a power
-// of two bytes.
+// pg + r * stride for a pointer pg into the LDS staging buffer, stride records per
+// staged row: CHC, or the run-time value (equal in every lane) where CHC is 0.  On
+// the GPU one instruction on the 32-bit LDS address: a shift-and-add when a
+// row of records spans a constant power of two bytes, else a 24-bit
+// multiply-and-add (row and row length are far below 2^23).
 template <typename A, int CHC>
-__host__ __device__ __forceinline__ const PixStage<A> *row_record(const PixStage<A> *pg, int r)
+__host__ __device__ __forceinline__ const PixStage<A> *row_record(const PixStage<A> *pg, int r, int stride)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr unsigned row_bytes = CHC * sizeof(PixStage<A>);
@@ -236,11 +235,14 @@ __host__ __device__ __forceinline__ const PixStage<A> *row_record(const PixStage
         typedef const __attribute__((address_space(3))) PixStage<A> *lds_rec;
         const unsigned base = (unsigned)(size_t)(lds_rec)pg;
         unsigned addr;
-        asm("v_lshl_add_u32 %0, %1, %3, %2" : "=v"(addr) : "v"(r), "v"(base), "i"(__builtin_ctz(row_bytes)));
+        if constexpr (CHC != 0)
+            asm("v_lshl_add_u32 %0, %1, %3, %2" : "=v"(addr) : "v"(r), "v"(base), "i"(__builtin_ctz(row_bytes)));
+        else
+            asm("v_mad_i32_i24 %0, %1, %3, %2" : "=v"(addr) : "v"(r), "v"(base), "s"(stride * (int)sizeof(PixStage<A>)));
         return (const PixStage<A> *)(lds_rec)(size_t)addr;
     }
 #endif
-    return pg + r * CHC;
+    return pg + r * (CHC != 0 ? CHC : stride);
 }
 
 // v clamped to [-1, hi] (hi >= -1 equal in every lane): one instruction on the GPU.
@@ -265,9 +267,9 @@ __host__ __device__ __forceinline__ int clamp_row(int v, int hi)
 // branch: va is clamped to [-1, nrow - 1], so row va + 1 is a staged row or the zero
 // row staged after them, and a row that is not a candidate has weight exactly
 // 0 (the weights are exact).  Further rows, up to the last staged one, follow in a
-// loop.  pg + va * CHC is the record of row va + 1 in the group's first column.
-template <typename A, bool SQ, int CHC, int TZN>
-__host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int nh, const float (&lo)[NH],
+// loop.  pg + va * stride is the record of row va + 1 in the group's first column.
+template <typename A, bool SQ, int CHC, int NH, int TZN>
+__host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int stride, int nh, const float (&lo)[NH],
                                                     const float (&hi)[NH], float mbz0, float l0, float sl,
                                                     float h0, float sh, int nrow, A (&acc)[TZN])
 {
@@ -289,11 +291,11 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int n
         const int va = clamp_row((int)floorf(vlo), nrow - 1);
         int vb = (int)floorf(vhi);
         vb = vb > nrow - 2 ? nrow - 2 : vb;
-        const PixStage<A> *prow = row_record<A, CHC>(pg, va);
-        A a = add_row<A, SQ>(prow, nh, lo, hi, mb, mb1, acc[j]);
+        const PixStage<A> *prow = row_record<A, CHC>(pg, va, stride);
+        A a = add_row<A, SQ, NH>(prow, nh, lo, hi, mb, mb1, acc[j]);
         for (int v = va; v < vb; ++v) {
-            prow += CHC;
-            a = add_row<A, SQ>(prow, nh, lo, hi, mb, mb1, a);
+            prow += CHC != 0 ? CHC : stride;
+            a = add_row<A, SQ, NH>(prow, nh, lo, hi, mb, mb1, a);
         }
         acc[j] = a;
         mb = mb1;
@@ -302,14 +304,15 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int n
 
 // One lane's share of one staged chunk of one view: add w_ij * (L_i e_i) to the
 // accumulators of its voxels (ix, iy, iz0 + j), j < TZN, for every staged ray
-// i = (column cu0 + c, row cv0 + r); s_pix[r * CHC + c] describes ray i, and
-// row nrow of s_pix holds zero records (weight 0 for any voxel).
+// i = (column cu0 + c, row cv0 + r); s_pix[r * stride + c] describes ray i (stride:
+// CHC, or the argument where CHC is 0), and row nrow of s_pix holds zero records
+// (weight 0 for any voxel).  NH columns are taken at once.
 // SQ: accumulate w_ij^2 * le instead of w_ij * le (with le = L^2 this sums the
 // squared weights, the diagonal of A^T A).
-template <typename A, bool SQ, int CHC, int TZN>
+template <typename A, bool SQ, int CHC, int NH, int TZN>
 __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const ViewParam &vp, int ix, int iy, int iz0,
                                                       const PixStage<A> *s_pix, const ColStage *s_col, int cu0,
-                                                      int ncol, int cv0, int nrow, A (&acc)[TZN])
+                                                      int ncol, int cv0, int nrow, A (&acc)[TZN], int stride = CHC)
 {
     int ixi, ieta;
     float hxi, heta;
@@ -341,7 +344,7 @@ __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const Vie
             const ColStage cs = s_col[c - cu0];
             column_interval(cs, lo_xi, ieta, heta, lo[h], hi[h]);
             if (h < nh && hi[h] > lo[h]) {
-                const float T1 = cs.tcv + lo[h] * cs.gz, T2 = cs.tcv + hi[h] * cs.gz;
+                const float T1 = __builtin_fmaf(lo[h], cs.gz, cs.tcv), T2 = __builtin_fmaf(hi[h], cs.gz, cs.tcv);
                 tmin = fminf(tmin, fminf(T1, T2));
                 tmax = fmaxf(tmax, fmaxf(T1, T2));
             }
@@ -364,8 +367,8 @@ __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const Vie
         const float sl = (fminf(b1, b2) - fminf(a1, a2)) * (1.0f / TZN);
         const float sh = (fmaxf(b1, b2) - fmaxf(a1, a2)) * (1.0f / TZN);
         const float l0 = fminf(a1, a2) + vofs_lo, h0 = fmaxf(a1, a2) + vofs_hi;
-        const PixStage<A> *pg = s_pix + ((c0 - cu0) + CHC);  // row va + 1 at pg + va * CHC
-        voxel_rows<A, SQ, CHC, TZN>(pg, nh, lo, hi, mbz0, l0, sl, h0, sh, nrow, acc);
+        const PixStage<A> *pg = s_pix + ((c0 - cu0) + (CHC != 0 ? CHC : stride));  // row va + 1 at pg + va * stride
+        voxel_rows<A, SQ, CHC, NH, TZN>(pg, stride, nh, lo, hi, mbz0, l0, sl, h0, sh, nrow, acc);
     }
 }
 

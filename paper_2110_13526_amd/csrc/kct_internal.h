@@ -49,7 +49,14 @@ struct ColParam {    // per (view, detector column)
 struct RowParam {    // per detector row
     float qz;        // z of the pixel centre [mm] (the source is at z = 0)
     float inv_qz;    // 1 / qz, 0 when qz == 0
+    // the same for the backprojector's staging, which gives rows parallel to the
+    // z-planes a finite steep slope (PAR_INV_QZ, see kct_gather.h): zeta at xi = 0 is
+    // qz * tcv + s_off and d xi / d zeta is s_inv * kz
+    float s_inv, s_off;
 };
+
+// d xi / d zeta of a parallel row is this times kz (of order 10^2 to 10^4)
+constexpr float PAR_INV_QZ = 1.0e27f;
 
 struct ViewParam {   // per view
     float sx, sy;    // source position [mm]
@@ -222,6 +229,22 @@ int64_t tt_forward_num_blocks(const GeoDev &g);
 hipError_t launch_forward_r(const GeoDev &g, const float *vol, const float *vol_z, float *out, int rows_per_lane,
                             hipStream_t st);
 
+// How a backprojection is laid out: by wavefronts (kct_wave.h: bricks of 8 x 8 x tz
+// voxels, the views in `sets` subsets) or by workgroups with bricks of
+// 16 x 16 x TZ or 16 x 16 x TZ_DEEP (backproject.hip).
+enum BwdForm { BWD_WAVES = 0, BWD_BRICKS, BWD_DEEP };
+struct BwdPlan {
+    int form, tz, sets;
+    int nbx, nby, nbz;
+    int64_t nblocks;  // bricks (and partial sums)
+};
+BwdPlan backward_plan(const GeoDev &g);               // a single backprojection's
+BwdPlan backward_plan_variant(const GeoDev &g, int variant);  // of a batched form's variant
+template <typename T>
+hipError_t launch_backward_waves(const GeoDev &g, const BwdPlan &p, const T *proj, T *out, T *out_z, int epi,
+                                 const Scalars *sc, double *partials, const int *skip, hipStream_t st,
+                                 const float *aux);
+
 // ---------------------------------------------------------------- batched CGLS
 // One instance of a batched solve as the batched kernels see it (single
 // precision storage).  The heavy steps of an iteration (backprojection,
@@ -239,8 +262,7 @@ struct BatchInst {
     GeoDev g;
     int64_t n, m;               // voxels, rays
     int fwd_r;                  // rows per lane of its forward variant (1 or 2)
-    int bwd_v;                  // its backprojection variant (BWD_VARIANTS)
-    int nbx, nby, nbz;          // backward brick grid of that variant
+    BwdPlan bwd;                // its backprojection's form and brick grid
     int64_t nf, nbk, ndir;      // tiles of its forward, backward and direction grids (partials per launch)
     const float *b;
     float *x;
@@ -249,9 +271,9 @@ struct BatchInst {
     float *d, *dz, *r, *e, *p;
 };
 
-// Backprojection variants of the batched form: brick depth and staged chunk
-// width (columns).  0: 16-deep bricks, 48-column chunks; 1: 20-deep bricks,
-// 32-column chunks (the single solve's choice for large volumes).
+// Backprojection variants of the batched form.  0: the single solve's form for the
+// instance without the deep bricks; 1: the deep bricks (the single solve's choice
+// for large volumes of fine voxels).
 enum BwdVariant { BWD_VSHALLOW = 0, BWD_VDEEP = 1, BWD_VARIANTS = 2 };
 
 enum BatchGrid { BG_FWD = 0, BG_BWD, BG_DIR, BG_STREAM, BG_COUNT };  // item tables, each count + 1 long
@@ -282,7 +304,6 @@ hipError_t batch_backward_occupancy(int &per_cu);
 hipError_t batch_dir_occupancy(int &per_cu);
 // a single backprojection (plain epilogue) with one of the batched form's variants (tuner)
 hipError_t launch_backward_variant(const GeoDev &g, int variant, const float *proj, float *out, hipStream_t st);
-int64_t backward_variant_grid(const GeoDev &g, int variant, int &nbx, int &nby, int &nbz);
 int backward_default_variant(const GeoDev &g);
 int64_t tt_backward_grid_dims(const GeoDev &g, int &nbx, int &nby, int &nbz);
 

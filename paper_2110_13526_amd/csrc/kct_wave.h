@@ -1,0 +1,239 @@
+// kct_wave.h -- the wave form of the backprojection: one wavefront takes a brick
+// of WX x WY voxel columns, TZB deep, and a subset of the views.  Per view it
+// bounds the brick's detector shadow, stages it in an LDS region of its own and
+// gathers from it (kct_gather.h), with no workgroup barrier in the view loop.
+//
+// The 16 x 16 column bricks of backproject.hip need about 4000 workgroups to fill
+// the chip and one pass through all views for each; volumes up to 192^3 have
+// 4 to 1728 of them.  Here a brick has a quarter of the columns, its depth
+// follows the shadow (so that one view's shadow is one staged chunk also where
+// a voxel spans several pixels), and the views are dealt to 4, 8 or 16 subsets.
+//
+// Bounded by VALU issue as the other form, at about 1.0 wave-instruction per
+// CU-cycle; a quarter to a third of its instructions stage the shadow.  Measured
+// (one backprojection, 16 x 16 x 16 workgroup bricks -> this form): 64^3 x 90 views,
+// 96 x 96 detector 1260 -> 98 us; 96^3 x 186, 218 x 218 4170 -> 882 us; 64^3 x 199,
+// 274 x 274 (four pixels per voxel) 22.4 -> 1.45 ms; 128^3 x 720, 154 x 120
+// 3.06 -> 1.52 ms; 192^3 x 180, 256 x 256 2.38 -> 1.95 ms.
+#pragma once
+
+#include "kct_epilogue.h"
+#include "kct_gather.h"
+#include "kct_internal.h"
+#include "kct_weights.h"
+
+namespace kct {
+
+constexpr int WX = 8, WY = 8;    // voxel columns of a brick: one per lane
+constexpr int W_GROUPS = 4;      // the view subsets are added within groups, then the groups
+constexpr int W_CAP = 448;       // staged records of a chunk, its zero row included
+constexpr int W_COLS = 48;       // most columns of a chunk
+constexpr int W_NHMAX = 3;
+
+// Detector columns held in registers at once: shallow bricks are those of wide
+// shadows, where a lane meets three and more columns.
+__host__ __device__ constexpr int wave_nh(int tzb) { return tzb <= 8 ? 3 : 2; }
+
+constexpr int W_SUMS = 8;        // voxels per lane whose partial sums pass through LDS at once
+
+// Records of one wavefront's staging region: the chunk and the spare records
+// that add_row may read.
+constexpr int W_REGION = W_CAP + W_NHMAX - 1;
+
+// LDS bytes of a workgroup of `waves` wavefronts: staging regions, columns, and
+// the wavefronts' shares of the partial sum of squares.
+__host__ __device__ constexpr size_t wave_lds_bytes(int waves)
+{
+    return (size_t)waves * (W_REGION * sizeof(PixStage<float>) + W_COLS * sizeof(ColStage) + sizeof(double));
+}
+
+// Orders one wavefront's LDS writes before its later reads, and its reads
+// before later writes (the LDS serves a wavefront in order; this keeps the
+// compiler from reordering them).
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The element of type E at byte offset off from base.
+template <typename E> __device__ __forceinline__ const E *byte_at(const void *base, unsigned off)
+{
+    return reinterpret_cast<const E *>(static_cast<const char *>(base) + off);
+}
+
+// Brick w (0 <= w < nbx * nby * nbz) of the backprojection, by a workgroup of
+// `waves` wavefronts (a multiple of W_GROUPS), each taking `subs` view subsets in
+// turn: wavefront v and turn i take views s, s + S, ... with s = v * subs + i and
+// S = waves * subs.  A voxel's S partial sums are added in order within each of
+// W_GROUPS groups of neighbouring subsets, and the groups pairwise, so the sum
+// depends on S alone.  The partial sum of squares goes to partials[w].  lds:
+// wave_lds_bytes(waves) bytes, 16-byte aligned.  MANY: subs may exceed 1, waves is
+// W_GROUPS.
+template <typename T, int EPI, int TZB, bool MANY>
+__device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, const T *__restrict__ proj,
+                                                    T *__restrict__ out, T *__restrict__ out_z,
+                                                    const Scalars *__restrict__ sc, double *__restrict__ partials,
+                                                    int nbx, int nby, int nbz, const float *__restrict__ aux,
+                                                    int waves, int subs, void *lds)
+{
+    using A = acc_t<T>;
+    constexpr bool SQ = EPI == BWD_DIAG || EPI == BWD_DIAG_INV;  // squared weights, e not read
+    constexpr int REGION = W_REGION, NCOL = wave_nh(TZB);
+    static_assert(sizeof(PixStage<A>) == sizeof(PixStage<float>) && sizeof(A) * W_SUMS * 64 <= sizeof(PixStage<A>) * REGION,
+                  "the LDS size holds for every accumulator, and the partial sums fit a staging region");
+    PixStage<A> *s_all = static_cast<PixStage<A> *>(lds);
+    ColStage *c_all = reinterpret_cast<ColStage *>(s_all + waves * REGION);
+    double *red = reinterpret_cast<double *>(c_all + waves * W_COLS);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(__builtin_amdgcn_workitem_id_x() >> 6));
+    const int lane = (int)(__builtin_amdgcn_workitem_id_x() & 63);
+    PixStage<A> *s_pix = s_all + wave * REGION;
+    ColStage *s_col = c_all + wave * W_COLS;
+
+    // XCD-aware brick assignment (see backproject.hip)
+    constexpr int XCDS = 8;
+    const int nb = nbx * nby * nbz;
+    const int b = (nb % XCDS == 0) ? (w % XCDS) * (nb / XCDS) + w / XCDS : w;
+    const int bx = b % nbx, by = (b / nbx) % nby, bz = b / (nbx * nby);
+    const int ix = bx * WX + lane % WX, iy = by * WY + lane / WX;
+    const int iz0 = bz * TZB;
+    const int nzb = g.nz - iz0 < TZB ? g.nz - iz0 : TZB;
+    const bool valid = ix < g.nx && iy < g.ny;
+    // half extents and centre of the brick's square, heights of its lowest and highest plane [mm]
+    const int cnx = g.nx - bx * WX < WX ? g.nx - bx * WX : WX, cny = g.ny - by * WY < WY ? g.ny - by * WY : WY;
+    const float ex = 0.5f * (float)cnx * g.vx, ey = 0.5f * (float)cny * g.vy;
+    const float xc = g.x0 + (float)(bx * WX) * g.vx + ex, yc = g.y0 + (float)(by * WY) * g.vy + ey;
+    const float wz0 = g.z0 + (float)iz0 * g.vz, wz1 = g.z0 + (float)(iz0 + nzb) * g.vz;
+
+    A acc[TZB], sum[MANY ? TZB : 1];
+#pragma unroll
+    for (int j = 0; j < TZB; ++j) acc[j] = 0;
+
+    const int nsets = waves * subs;
+    for (int turn = 0; turn < (MANY ? subs : 1); ++turn) {
+        for (int k = (MANY ? wave * subs + turn : wave); k < g.nviews; k += nsets) {
+            const ViewParam vp = g.views[k];
+            // 1. shadow of the brick, as voxel_columns bounds one voxel's: its
+            //    detector columns around the image of its centre, its rows from the
+            //    heights of its planes at its square's least and greatest depth
+            int u0, u1, v0, v1;
+            {
+                const float dn = __builtin_fmaf(ex, fabsf(vp.s), ey * fabsf(vp.c));  // half extent along e_u
+                const float dd = __builtin_fmaf(ex, fabsf(vp.c), ey * fabsf(vp.s));  // and in depth
+                const float dx = xc - vp.sx, dy = yc - vp.sy;
+                const float num = __builtin_fmaf(vp.c, dy, -vp.s * dx);
+                const float den = __builtin_fmaf(-vp.c, dx, -vp.s * dy);
+                const float inv = rcp_approx(den), rmax = rcp_approx(den - dd), rmin = rcp_approx(den + dd);
+                const float fc = __builtin_fmaf(num * inv, g.ku, g.fu0);
+                const float hc = __builtin_fmaf(__builtin_fmaf(dd * fabsf(num), inv, dn) * rmax, g.ku, 0.01f);
+                const float p0 = wz0 * rmin, p1 = wz0 * rmax, p2 = wz1 * rmin, p3 = wz1 * rmax;
+                const float zlo = fminf(fminf(p0, p1), fminf(p2, p3)), zhi = fmaxf(fmaxf(p0, p1), fmaxf(p2, p3));
+                const int a0 = (int)ceilf(fc - hc), a1 = (int)floorf(fc + hc);
+                const int b0 = (int)ceilf(__builtin_fmaf(zlo, g.kv, g.fv0) - 0.01f);
+                const int b1 = (int)floorf(__builtin_fmaf(zhi, g.kv, g.fv0) + 0.01f);
+                u0 = __builtin_amdgcn_readfirstlane(a0 < 0 ? 0 : a0);
+                u1 = __builtin_amdgcn_readfirstlane(a1 > g.nu - 1 ? g.nu - 1 : a1);
+                v0 = __builtin_amdgcn_readfirstlane(b0 < 0 ? 0 : b0);
+                v1 = __builtin_amdgcn_readfirstlane(b1 > g.nv - 1 ? g.nv - 1 : b1);
+            }
+            const T *pk = SQ ? proj : proj + (size_t)k * g.nv * g.nu;  // not read when SQ
+            const ColParam *ck = g.cols + (size_t)k * g.nu;
+            // chunks of at most W_CAP records with the zero row, W_COLS columns, and
+            // rows that leave room for 8 columns; typical bricks need one chunk
+            constexpr int RMAX = W_CAP / 8 - 1;
+            for (int cv0 = v0; cv0 <= v1; cv0 += RMAX) {
+                const int nrow = v1 - cv0 + 1 < RMAX ? v1 - cv0 + 1 : RMAX;
+                int cmax = W_COLS;
+                if ((nrow + 1) * cmax > W_CAP) {
+                    // W_CAP / (nrow + 1) through a reciprocal, one less where that rounds up
+                    cmax = __builtin_amdgcn_readfirstlane((int)((float)W_CAP * __builtin_amdgcn_rcpf((float)(nrow + 1)) + 0.01f));
+                    if ((nrow + 1) * cmax > W_CAP) --cmax;
+                }
+                for (int cu0 = u0; cu0 <= u1; cu0 += cmax) {
+                    const int ncol = u1 - cu0 + 1 < cmax ? u1 - cu0 + 1 : cmax;
+                    // 2. stage the chunk: lane t keeps column t % ncol and takes the rows
+                    //    t / ncol, + step, ... of it (the division through a reciprocal:
+                    //    (t + 0.5) / ncol lies at least 0.5 / ncol >= 0.01 from an integer,
+                    //    the product's rounding below 1e-4)
+                    {
+                        const float rn = __builtin_amdgcn_rcpf((float)ncol);
+                        const int step = __builtin_amdgcn_readfirstlane((int)(64.5f * rn));
+                        const int r0 = (int)(((float)lane + 0.5f) * rn), c = lane - r0 * ncol;
+                        if (r0 < step) {
+                            const ColParam cp = *byte_at<ColParam>(ck, (unsigned)(cu0 + c) * (unsigned)sizeof(ColParam));
+                            if (r0 == 0) s_col[c] = stage_column(g, vp.dom, cp);
+                            unsigned pix = ((unsigned)(cv0 + r0) * (unsigned)g.nu + (unsigned)(cu0 + c)) * (unsigned)sizeof(T);
+                            unsigned row = (unsigned)(cv0 + r0) * (unsigned)sizeof(RowParam);
+                            PixStage<A> *rec = s_pix + (r0 * ncol + c);
+                            for (int r = r0; r < nrow; r += step) {
+                                const A ev = SQ ? (A)0 : to_acc(*byte_at<T>(pk, pix));
+                                *rec = stage_pixel<A, SQ>(cp, *byte_at<RowParam>(g.rows, row), ev);
+                                pix += (unsigned)(step * g.nu) * (unsigned)sizeof(T);
+                                row += (unsigned)step * (unsigned)sizeof(RowParam);
+                                rec += step * ncol;
+                            }
+                            if (r0 == 0) s_pix[nrow * ncol + c] = zero_pixel<A>();
+                        }
+                    }
+                    wave_lds_order();
+                    // 3. gather (the lane's column indices laundered per chunk: what is
+                    //    derived from them is recomputed instead of kept through the view loop)
+                    int ixv = ix, iyv = iy;
+                    asm volatile("" : "+v"(ixv), "+v"(iyv));
+                    if (valid)
+                        gather_chunk<A, SQ, 0, NCOL>(g, vp, ixv, iyv, iz0, s_pix, s_col, cu0, ncol, cv0, nrow, acc, ncol);
+                    wave_lds_order();
+                }
+            }
+        }
+        if (MANY) {
+#pragma unroll
+            for (int j = 0; j < TZB; ++j) {
+                sum[MANY ? j : 0] = turn == 0 ? acc[j] : sum[MANY ? j : 0] + acc[j];
+                acc[j] = 0;
+            }
+        }
+    }
+
+    // every voxel's partial sums through LDS, W_SUMS voxels of each lane at a time:
+    // in order within a group, then the groups
+    A *mine = reinterpret_cast<A *>(s_pix);
+    double sq = 0.0;
+    const int per = waves / W_GROUPS;
+#pragma unroll
+    for (int j0 = 0; j0 < TZB; j0 += W_SUMS) {
+        if (j0 > 0) __syncthreads();
+#pragma unroll
+        for (int j = j0; j < j0 + W_SUMS && j < TZB; ++j)
+            mine[(j - j0) * 64 + lane] = MANY ? sum[MANY ? j : 0] : acc[j];
+        __syncthreads();
+        const int jend = nzb < j0 + W_SUMS ? nzb : j0 + W_SUMS;
+        for (int j = j0 + wave; j < jend; j += waves) {
+            const int at = (j - j0) * 64 + lane;
+            A v[W_GROUPS];
+#pragma unroll
+            for (int q = 0; q < W_GROUPS; ++q) {
+                v[q] = reinterpret_cast<const A *>(s_all + q * per * REGION)[at];
+                for (int i = 1; i < per; ++i) v[q] += reinterpret_cast<const A *>(s_all + (q * per + i) * REGION)[at];
+            }
+            if (valid) {
+                const int iz = iz0 + j;
+                const size_t vox = ((size_t)iz * g.ny + iy) * g.nx + ix;
+                sq += bwd_store<T, EPI, A>(out, out_z, sc, aux, vox, ((size_t)iy * g.nx + ix) * g.nz + iz,
+                                           (v[0] + v[1]) + (v[2] + v[3]));
+            }
+        }
+    }
+    if (bwd_has_partials<EPI>()) {
+        for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+        if (lane == 0) red[wave] = sq;
+        __syncthreads();
+        if (__builtin_amdgcn_workitem_id_x() == 0) {
+            double r = red[0];
+            for (int q = 1; q < waves; ++q) r += red[q];
+            partials[w] = r;
+        }
+    }
+}
+
+}  // namespace kct
