@@ -35,9 +35,9 @@ HBM_PEAK_GBS = 8000.0
 # Files each projector kernel is compiled from; the measured-traffic record in
 # profiles/ is valid only for the sources it was taken with.
 KERNEL_SOURCES = {
-    "forward": ("csrc/projector.hip", "csrc/kct_ray.h", "csrc/kct_weights.h", "csrc/kct_internal.h",
+    "forward": ("csrc/projector.hip", "csrc/kct_forward.h", "csrc/forward_r4.hip", "csrc/kct_ray.h", "csrc/kct_weights.h", "csrc/kct_internal.h",
                 "csrc/kct_epilogue.h", "csrc/kct_batch.h", "csrc/geometry.cpp", "build.py"),
-    "backward": ("csrc/backproject.hip", "csrc/kct_gather.h", "csrc/kct_weights.h", "csrc/kct_internal.h",
+    "backward": ("csrc/backproject.hip", "csrc/kct_wave.h", "csrc/kct_gather.h", "csrc/kct_weights.h", "csrc/kct_internal.h",
                  "csrc/kct_epilogue.h", "csrc/kct_batch.h", "csrc/geometry.cpp", "build.py"),
 }
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "projector_c3_hbm_counters.json")

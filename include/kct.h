@@ -263,8 +263,8 @@ void kct_batch_destroy(kct_batch b);
  * (projections), scalars and partial sums. */
 kct_status kct_batch_workspace_size(kct_batch b, size_t *bytes);
 
-/* Autotuner: for each instance, time its forward projection with one and with
- * two detector rows per lane, and its backprojection with each brick shape
+/* Autotuner: for each instance, time its forward projection with one to four
+ * detector rows per lane (as many as its detector can fill), and its backprojection with each brick shape
  * (0: the single solve's form for the instance without the 32-deep bricks, 1: the
  * 32-deep bricks), 3 launches each after a warm-up (HIP events), and keep the faster of
  * each for the batch's solves (a tuned instance may then differ from its own

@@ -35,7 +35,8 @@ def flags():
     ]
 
 
-PROJECTOR_SOURCES = {"projector.hip", "backproject.hip", "backproject_wave.hip", "tt.hip"}
+PROJECTOR_SOURCES = {"projector.hip", "forward_r1.hip", "forward_r2.hip", "forward_r3.hip", "forward_r4.hip",
+                     "backproject.hip", "backproject_wave.hip", "tt.hip"}
 
 
 def source_flags(src):

@@ -12,7 +12,7 @@
 // stamp each instance's set-up and completion on the device clock, so the
 // latency of every instance inside the batch is measured.
 //
-// The autotuner picks, per instance, the forward variant (1 or 2 detector rows
+// The autotuner picks, per instance, the forward variant (1 to 4 detector rows
 // per lane) and the backprojection variant (with or without the deep bricks) by
 // timing them on the instance's geometry, and can keep its choices
 // in a text file keyed by the instance's sizes.
@@ -35,7 +35,7 @@ void set_error(const std::string &msg);
 
 struct Batch {
     std::vector<const Geometry *> geoms;
-    std::vector<int> fwd_r;   // per instance, 1 or 2
+    std::vector<int> fwd_r;   // per instance, detector rows per lane (1 to 4)
     std::vector<int> bwd_v;   // per instance, a BwdVariant
     std::vector<int> order;   // grid order: instance indices, largest work first
     int device = -1;
@@ -63,7 +63,7 @@ int64_t inst_ndir(const Geometry *g)
 
 int64_t inst_partials(const Geometry *g)
 {
-    int64_t a = std::max(forward_num_blocks_r(g->dev, 1), forward_num_blocks_r(g->dev, 2));
+    int64_t a = forward_num_blocks_r(g->dev, 1);  // the most of any rows per lane
     int64_t bmax = 0;
     for (int v = 0; v < BWD_VARIANTS; ++v) bmax = std::max(bmax, backward_plan_variant(g->dev, v).nblocks);
     return std::max(std::max(a, bmax), stream_num_blocks());
@@ -182,7 +182,7 @@ kct_status kct_batch_create(const kct_geometry *geoms, int32_t count, kct_batch 
                         KCT_ERR_INVALID_ARG);
         }
         b->geoms.push_back(g);
-        b->fwd_r.push_back(2);  // two rows per lane until the tuner has timed the instance
+        b->fwd_r.push_back(forward_plan(g->dev).rows);
         b->bwd_v.push_back(backward_default_variant(g->dev));
         b->order.push_back(i);
     }
@@ -247,7 +247,7 @@ kct_status kct_batch_tune(kct_batch h, void *ws, size_t ws_bytes, const char *ca
             std::istringstream ls(line);
             std::string key;
             int r = 0, v = -1;
-            if (!(ls >> key >> r) || (r != 1 && r != 2)) continue;
+            if (!(ls >> key >> r) || r < 1 || r > 4) continue;
             if (!(ls >> v) || v < 0 || v >= BWD_VARIANTS) v = -1;
             known[key] = {r, v};
         }
@@ -283,8 +283,9 @@ kct_status kct_batch_tune(kct_batch h, void *ws, size_t ws_bytes, const char *ca
         if (e == hipSuccess) e = launch_zfast_copy<float, float>(g->dev, d, dz, stream);
         if (e == hipSuccess) e = launch_fill_zero<float>(p, inst_m(g), stream);
         float best = 0.0f;
-        int best_r = 2;
-        for (int rr = 1; rr <= 2 && e == hipSuccess; ++rr) {
+        int best_r = 1;
+        // (no more rows than the detector has: a lane's last row would be idle everywhere)
+        for (int rr = 1; rr <= 4 && 64 * (rr - 1) < g->dev.nv && e == hipSuccess; ++rr) {
             float ms = 0.0f;
             e = time_it([&] { return launch_forward_r(g->dev, d, dz, p, rr, stream); }, ms);
             if (e == hipSuccess && (rr == 1 || ms < best)) {
@@ -356,10 +357,10 @@ kct_status kct_batch_cgls_solve(kct_batch h, const float *const *bs, float *cons
         t.g = g->dev;
         t.n = inst_n(g);
         t.m = inst_m(g);
-        t.fwd_r = b->fwd_r[i];
+        t.fwd = forward_plan_rows(g->dev, b->fwd_r[i]);
         t.bwd = backward_plan_variant(g->dev, b->bwd_v[i]);
         t.nbk = t.bwd.nblocks;
-        t.nf = forward_num_blocks_r(g->dev, t.fwd_r);
+        t.nf = forward_num_blocks_r(g->dev, t.fwd.rows);
         t.ndir = inst_ndir(g);
         t.b = bs[i];
         t.x = xs[i];

@@ -183,8 +183,19 @@ hipError_t launch_forward(const GeoDev &g, const TV *vol, const TV *vol_z, TP *o
 template <typename T>
 hipError_t launch_backward(const GeoDev &g, const T *proj, T *out, T *out_z, int epi, const Scalars *sc,
                            double *partials, const int *skip, hipStream_t st, const float *aux = nullptr);
-int64_t forward_num_blocks(const GeoDev &g);                         // the default variant
-int64_t forward_num_blocks_r(const GeoDev &g, int rows_per_lane);     // rows_per_lane 1 or 2
+// How a forward projection is laid out: detector rows per lane (1 to 4), and whether
+// every ray's walk is divided among four wavefronts.
+struct FwdPlan {
+    int rows;
+    bool divided;
+};
+FwdPlan forward_plan(const GeoDev &g);
+FwdPlan forward_plan_rows(const GeoDev &g, int rows);
+int64_t forward_num_blocks(const GeoDev &g);                         // of forward_plan (or the TT projector's)
+int64_t forward_num_blocks_r(const GeoDev &g, int rows_per_lane);
+template <typename TV, typename TP, int R>
+hipError_t launch_forward_rows(const GeoDev &g, bool divided, const TV *vol, const TV *vol_z, TP *out, const TP *aux,
+                               int epi, const Scalars *sc, double *partials, const int *skip, hipStream_t st);
 int64_t backward_num_blocks(const GeoDev &g);
 
 // Vector kernels (vector_ops.hip).
@@ -225,7 +236,7 @@ template <typename T>
 hipError_t launch_backward_tt(const GeoDev &g, const T *proj, T *out, T *out_z, int epi, const Scalars *sc,
                               double *partials, const int *skip, hipStream_t st, const float *aux);
 int64_t tt_forward_num_blocks(const GeoDev &g);
-// forward with an explicit rows-per-lane variant (1 or 2), plain epilogue
+// forward with an explicit rows-per-lane variant (1 to 4), plain epilogue
 hipError_t launch_forward_r(const GeoDev &g, const float *vol, const float *vol_z, float *out, int rows_per_lane,
                             hipStream_t st);
 
@@ -261,7 +272,7 @@ hipError_t launch_backward_waves(const GeoDev &g, const BwdPlan &p, const T *pro
 struct BatchInst {
     GeoDev g;
     int64_t n, m;               // voxels, rays
-    int fwd_r;                  // rows per lane of its forward variant (1 or 2)
+    FwdPlan fwd;                // its forward's rows per lane and whether its walks are divided
     BwdPlan bwd;                // its backprojection's form and brick grid
     int64_t nf, nbk, ndir;      // tiles of its forward, backward and direction grids (partials per launch)
     const float *b;
