@@ -36,7 +36,7 @@ def flags():
 
 
 PROJECTOR_SOURCES = {"projector.hip", "forward_r1.hip", "forward_r2.hip", "forward_r3.hip", "forward_r4.hip",
-                     "backproject.hip", "backproject_wave.hip", "tt.hip"}
+                     "backproject.hip", "backproject_wave.hip", "tt.hip", "tt_forward.hip", "tt_backward.hip"}
 
 
 def source_flags(src):

@@ -356,9 +356,7 @@ hipError_t launch_backward_variant(const GeoDev &g, int variant, const float *pr
 // Workgroups (and partial sums) of a single backprojection with g.
 int64_t backward_num_blocks(const GeoDev &g)
 {
-    int nbx, nby, nbz;
-    if (g.projector == KCT_PROJECTOR_TT) return tt_backward_grid_dims(g, nbx, nby, nbz);
-    return backward_plan(g).nblocks;
+    return (g.projector == KCT_PROJECTOR_TT ? tt_backward_plan(g) : backward_plan(g)).nblocks;
 }
 
 template <typename T>

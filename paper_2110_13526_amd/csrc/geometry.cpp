@@ -1,6 +1,7 @@
 // geometry.cpp -- host-side reduction of the cone-beam geometry to the ray
 // tables of kct_internal.h.  Everything is computed in double precision and
 // rounded once to single precision.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -94,6 +95,7 @@ kct_status geometry_tables(const kct_volume_desc &vol, const kct_cone_desc &cone
         rows[iv].s_off = par ? (std::floor(-zc + (float)hz) - (float)hz) + 0.5f : -zc;
     }
 
+    double least_depth = INFINITY;  // of a volume corner, in any view
     for (int k = 0; k < nk; ++k) {
         const double t = view_angle(cone, k);
         const double c = std::cos(t), s = std::sin(t);
@@ -109,9 +111,8 @@ kct_status geometry_tables(const kct_volume_desc &vol, const kct_cone_desc &cone
                           std::to_string(k));
                 return KCT_ERR_INVALID_ARG;
             }
+            least_depth = std::min(least_depth, depth);
         }
-        (void)Z0;
-        (void)Z1;
         const int dom = (std::fabs(c) / vol.vx >= std::fabs(s) / vol.vy) ? 0 : 1;
         ViewParam &vp = views[k];
         vp.sx = (float)Sx;
@@ -179,6 +180,10 @@ kct_status geometry_tables(const kct_volume_desc &vol, const kct_cone_desc &cone
     d.cu = 0.5f * (float)(nu - 1);
     d.projector = KCT_PROJECTOR_SIDDON;
     d.sid = (float)cone.sid;
+    // The images of z-planes z and z + vz of a voxel column overlap once the image of
+    // z, which spans the depths D to D + dD of the column, reaches that of z + vz:
+    // |z| dD / D > vz, with dD at most the diagonal of the voxel's square.
+    d.tt_overlap = std::max(std::fabs(Z0), std::fabs(Z1)) * std::hypot(vol.vx, vol.vy) / least_depth > 0.99 * vol.vz;
     d.cv = 0.5f * (float)(nv - 1);
     d.ku = (float)(cone.sdd / cone.du);
     d.kv = (float)(cone.sdd / cone.dv);

@@ -92,6 +92,7 @@ struct GeoDev {
     float fu0, fv0;          // cu - off_u / du, cv - off_v / dv
     int projector;           // KCT_PROJECTOR_SIDDON or KCT_PROJECTOR_TT (host-side dispatch)
     float sid;               // source to rotation axis [mm]
+    int tt_overlap;          // TT: whether the images of neighbouring z-planes may overlap (kct_tt.h)
     const ColParam *cols;    // [nviews][nu]
     const RowParam *rows;    // [nv]
     const ViewParam *views;  // [nviews]
@@ -236,6 +237,10 @@ template <typename T>
 hipError_t launch_backward_tt(const GeoDev &g, const T *proj, T *out, T *out_z, int epi, const Scalars *sc,
                               double *partials, const int *skip, hipStream_t st, const float *aux);
 int64_t tt_forward_num_blocks(const GeoDev &g);
+// double storage (tt.hip): the plain pair only
+hipError_t launch_forward_tt_f64(const GeoDev &g, const double *vol, const double *vol_z, double *out, int epi,
+                                 const int *skip, hipStream_t st);
+hipError_t launch_backward_tt_f64(const GeoDev &g, const double *proj, double *out, int epi, const int *skip, hipStream_t st);
 // forward with an explicit rows-per-lane variant (1 to 4), plain epilogue
 hipError_t launch_forward_r(const GeoDev &g, const float *vol, const float *vol_z, float *out, int rows_per_lane,
                             hipStream_t st);
@@ -250,6 +255,7 @@ struct BwdPlan {
     int64_t nblocks;  // bricks (and partial sums)
 };
 BwdPlan backward_plan(const GeoDev &g);               // a single backprojection's
+BwdPlan tt_backward_plan(const GeoDev &g);            // the TT projector's
 BwdPlan backward_plan_variant(const GeoDev &g, int variant);  // of a batched form's variant
 template <typename T>
 hipError_t launch_backward_waves(const GeoDev &g, const BwdPlan &p, const T *proj, T *out, T *out_z, int epi,
@@ -316,6 +322,5 @@ hipError_t batch_dir_occupancy(int &per_cu);
 // a single backprojection (plain epilogue) with one of the batched form's variants (tuner)
 hipError_t launch_backward_variant(const GeoDev &g, int variant, const float *proj, float *out, hipStream_t st);
 int backward_default_variant(const GeoDev &g);
-int64_t tt_backward_grid_dims(const GeoDev &g, int &nbx, int &nby, int &nbz);
 
 }  // namespace kct

@@ -152,6 +152,66 @@ __host__ __device__ __forceinline__ float tt_amplitude(float L, float inv_a, flo
     return L * m;
 }
 
+// The same footprints by ramps, for single-precision accumulation (both kernels;
+// double storage keeps the closed forms above, whose bits it is compared in).  A
+// unit trapezoid t0 <= t1 <= t2 <= t3 is the ramp from t0 to t1 less the ramp from t2
+// to t3, a ramp rising from 0 at lo to 1 at hi and staying there.
+struct TTRamp {
+    float lo, hi, r;  // r = 1 / (2 (hi - lo)); finite for an empty ramp, where it meets a factor 0
+};
+
+__host__ __device__ __forceinline__ TTRamp tt_ramp(float lo, float hi)
+{
+    return TTRamp{lo, hi, 0.5f * tt_rcp(fmaxf(hi - lo, 1.0e-30f))};
+}
+
+// Mean of a ramp over the pixel [um, um + 1], up = um + 1: the part inside the ramp,
+// with p and q the pixel's ends clamped to it, (p - q) ((p - lo) + (q - lo)) r, and the
+// part beyond hi.  No branch, and no cancellation: every difference is one of
+// neighbouring coordinates.
+__host__ __device__ __forceinline__ float tt_ramp_mean(const TTRamp &t, float um, float up)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const float p = __builtin_amdgcn_fmed3f(up, t.lo, t.hi), q = __builtin_amdgcn_fmed3f(um, t.lo, t.hi);
+#else
+    const float p = fminf(fmaxf(up, t.lo), t.hi), q = fminf(fmaxf(um, t.lo), t.hi);
+#endif
+    const float inside = ((p - q) * t.r) * ((p - t.lo) + (q - t.lo));
+    return inside + (fmaxf(up, t.hi) - fmaxf(um, t.hi));
+}
+
+// Mean over a pixel of the trapezoid between two ramps (exactly 0 where they do not
+// meet the pixel).
+__host__ __device__ __forceinline__ float tt_trap_mean(const TTRamp &a, const TTRamp &b, float um, float up)
+{
+    return fmaxf(tt_ramp_mean(a, um, up) - tt_ramp_mean(b, um, up), 0.0f);
+}
+
+// The ramp of z-plane p (height z0 + p vz) of a column with row scales ka, kb: the
+// images of the plane at the nearest and the farthest depth.  Where the images of
+// two neighbouring planes do not overlap, layer iz's trapezoid lies between the
+// ramps of planes iz and iz + 1, so neighbouring layers share them.
+__host__ __device__ __forceinline__ TTRamp tt_plane_ramp(const GeoDev &g, float p, float ka, float kb, float off)
+{
+    const float z = __builtin_fmaf(p, g.vz, g.z0);
+    const float a = __builtin_fmaf(z, ka, off), b = __builtin_fmaf(z, kb, off);
+    return tt_ramp(fminf(a, b), fmaxf(a, b));
+}
+
+// The two ramps of a layer from those of its planes: with OVERLAP the breakpoints are
+// sorted (the inner pair may be swapped), otherwise they are the planes' ramps.
+template <bool OVERLAP>
+__host__ __device__ __forceinline__ void tt_layer_ramps(const TTRamp &p0, const TTRamp &p1, TTRamp &a, TTRamp &b)
+{
+    if (OVERLAP) {
+        a = tt_ramp(p0.lo, fminf(p0.hi, p1.lo));
+        b = tt_ramp(fmaxf(p0.hi, p1.lo), p1.hi);
+    } else {
+        a = p0;
+        b = p1;
+    }
+}
+
 // Pixels [a, b] of an axis whose extent meets the open interval (t0, t3).
 __host__ __device__ __forceinline__ void tt_pixels(float t0, float t3, int &a, int &b)
 {
@@ -303,6 +363,64 @@ __host__ __device__ __forceinline__ void tt_gather_chunk(const GeoDev &g, int iz
                     }
                 }
             }
+        }
+    }
+}
+
+// One lane's share of one staged chunk by ramps: add fl(F_u F_v) * s_le[pixel] to
+// acc[j] for the TZN voxels above layer iz0 of a column with transaxial breakpoints t
+// (sorted) and row scales ka, kb, over the staged pixels (column cu0 + c, row cv0 + r) at
+// s_le[r * stride + c].  SQ: add fl(F_u F_v)^2 * s_le instead.  Voxels beyond the volume's
+// top are taken as well (their sums are never stored).  NC columns at once.
+template <typename A, bool SQ, bool OVERLAP, int NC, int TZN>
+__host__ __device__ __forceinline__ void tt_gather_ramps(const GeoDev &g, int iz0, const float (&t)[4], float ka, float kb,
+                                                         const A *s_le, int stride, int cu0, int ncol, int cv0, int nrow,
+                                                         A (&acc)[TZN])
+{
+    int ua, ub;
+    tt_pixels(t[0], t[3], ua, ub);
+    ua = ua < cu0 ? cu0 : ua;
+    ub = ub > cu0 + ncol - 1 ? cu0 + ncol - 1 : ub;
+    const int vmax = cv0 + nrow - 1;
+    const TTRamp u0 = tt_ramp(t[0], t[1]), u1 = tt_ramp(t[2], t[3]);
+    const float roff = tt_row_offset(g);
+    for (int c0 = ua; c0 <= ub; c0 += NC) {
+        // (an empty asm keeps the planes' ramps, which do not depend on c0, from being
+        // hoisted out of this loop, where all of them would be live at once)
+        float kai = ka, kbi = kb;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(kai), "+v"(kbi));
+#endif
+        const int nc = ub - c0 + 1 < NC ? ub - c0 + 1 : NC;
+        float fu[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) fu[c] = tt_trap_mean(u0, u1, (float)(c0 + c) - 0.5f, (float)(c0 + c) + 0.5f);
+        TTRamp p0 = tt_plane_ramp(g, (float)iz0, kai, kbi, roff);
+#pragma unroll
+        for (int j = 0; j < TZN; ++j) {
+            const TTRamp p1 = tt_plane_ramp(g, (float)(iz0 + j + 1), kai, kbi, roff);
+            TTRamp a, b;
+            tt_layer_ramps<OVERLAP>(p0, p1, a, b);
+            int va, vb;
+            tt_pixels(a.lo, b.hi, va, vb);
+            va = va < cv0 ? cv0 : va;
+            vb = vb > vmax ? vmax : vb;
+            const A *lrow = s_le + (va - cv0) * stride + (c0 - cu0);
+            A sum = acc[j];
+            for (int v = va; v <= vb; ++v) {
+                const float um = (float)v - 0.5f;
+                const float fv = tt_trap_mean(a, b, um, um + 1.0f);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    if (c == 0 || c < nc) {
+                        const float w = fu[c] * fv;
+                        sum = fma_acc(SQ ? w * w : w, lrow[c], sum);
+                    }
+                }
+                lrow += stride;
+            }
+            acc[j] = sum;
+            p0 = p1;
         }
     }
 }

@@ -1,9 +1,9 @@
-// tt.hip -- the TT footprint projector pair (kct_tt.h) on gfx950, selected per
-// geometry with kct_geometry_set_projector.  Both kernels evaluate the weight
-// fl(F_u * F_v) of kct_tt.h on the same single-precision inputs, so, as for the
-// Siddon pair, the backprojector is the exact transpose of the projector up to
-// accumulation rounding; both write every output once (no atomics) and take
-// every epilogue of the solvers (kct_epilogue.h).
+// tt.hip -- the TT footprint projector pair (kct_tt.h) with double-precision
+// accumulation, selected per geometry with kct_geometry_set_projector (the single-
+// precision forms are in tt_forward.hip and tt_backward.hip).  Both kernels evaluate
+// the weight fl(F_u * F_v) by the closed forms of kct_tt.h on the same
+// single-precision inputs, so the backprojector is the exact transpose of the
+// projector up to accumulation rounding; both write every output once (no atomics).
 //
 //   forward   ray-driven: a wavefront holds 64 detector rows of one column.
 //             Walking the view's dominant axis slab by slab, the wavefront
@@ -15,9 +15,6 @@
 //             brick's detector shadow is staged in LDS as L_i e_i; each lane
 //             takes the detector columns of its voxel column's transaxial
 //             footprint and, per voxel, the rows of its axial footprint.
-#include <type_traits>
-
-#include "kct_epilogue.h"
 #include "kct_gather.h"
 #include "kct_internal.h"
 #include "kct_tt.h"
@@ -46,10 +43,8 @@ __host__ __device__ __forceinline__ TTFwdGrid tt_fwd_grid(const GeoDev &g)
     return f;
 }
 
-int64_t tt_forward_num_blocks(const GeoDev &g) { return tt_fwd_grid(g).nblocks; }
-
 // Backward grid: bricks of BX x BY x TT_TZ voxels.
-int64_t tt_backward_grid_dims(const GeoDev &g, int &nbx, int &nby, int &nbz)
+static int64_t tt_backward_grid_dims(const GeoDev &g, int &nbx, int &nby, int &nbz)
 {
     nbx = (g.nx + BX - 1) / BX;
     nby = (g.ny + BY - 1) / BY;
@@ -57,25 +52,12 @@ int64_t tt_backward_grid_dims(const GeoDev &g, int &nbx, int &nby, int &nbz)
     return (int64_t)nbx * nby * nbz;
 }
 
-__device__ __forceinline__ double tt_block_sum(double v)
-{
-    __shared__ double red[4];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    if ((__builtin_amdgcn_workitem_id_x() & 63) == 0) red[__builtin_amdgcn_workitem_id_x() >> 6] = v;
-    __syncthreads();
-    double r = 0.0;
-    if (__builtin_amdgcn_workitem_id_x() == 0) r = (red[0] + red[1]) + (red[2] + red[3]);
-    return r;
-}
-
-template <typename TV, typename TP, int EPI>
-__global__ __launch_bounds__(256) void k_forward_tt(GeoDev g, const TV *__restrict__ vol,
-                                                    const TV *__restrict__ vol_z, TP *__restrict__ out,
-                                                    const TP *__restrict__ aux, const Scalars *__restrict__ sc,
-                                                    double *__restrict__ partials, const int *__restrict__ skip)
+__global__ __launch_bounds__(256) void k_forward_tt_f64(GeoDev g, const double *__restrict__ vol,
+                                                        const double *__restrict__ vol_z, double *__restrict__ out,
+                                                        const int *__restrict__ skip)
 {
     if (skip && *skip) return;
-    using A = acc_t<TV>;
+    using A = double;
     const TTFwdGrid fg = tt_fwd_grid(g);
     const int64_t w = __builtin_amdgcn_workgroup_id_x();
     const int64_t full = fg.nblocks & ~(int64_t)63;
@@ -95,8 +77,7 @@ __global__ __launch_bounds__(256) void k_forward_tt(GeoDev g, const TV *__restri
         ok[r] = col_ok && iv[r] < g.nv;
     }
     A acc[TT_R] = {};
-    if (col_ok) tt_ray_sums<TV, TT_R>(g, g.views[k], iu, iv, ok, vol, vol_z, acc);
-    double sq = 0.0;
+    if (col_ok) tt_ray_sums<double, TT_R>(g, g.views[k], iu, iv, ok, vol, vol_z, acc);
 #pragma unroll
     for (int r = 0; r < TT_R; ++r) {
         if (ok[r]) {
@@ -105,24 +86,17 @@ __global__ __launch_bounds__(256) void k_forward_tt(GeoDev g, const TV *__restri
             const float amp = tt_amplitude(ray_length_per_xi(cp.lxy2, rp.qz, cp.gp), cp.inv_a,
                                            zeta_inv_slope(rp.inv_qz, cp.kz));
             const size_t ray = ((size_t)k * g.nv + iv[r]) * g.nu + iu;
-            sq += fwd_store<TP, EPI, A>(out, aux, sc, ray, (A)amp * acc[r]);
+            out[ray] = (A)amp * acc[r];
         }
-    }
-    if (EPI != FWD_PLAIN) {
-        const double bs = tt_block_sum(sq);
-        if (__builtin_amdgcn_workitem_id_x() == 0) partials[__builtin_amdgcn_workgroup_id_x()] = bs;
     }
 }
 
-template <typename T, int EPI>
-__global__ __launch_bounds__(256, sizeof(acc_t<T>) == 4 ? 5 : 2) void k_backward_tt(GeoDev g, const T *__restrict__ proj, T *__restrict__ out,
-                                                        T *__restrict__ out_z, const Scalars *__restrict__ sc,
-                                                        double *__restrict__ partials, const int *__restrict__ skip,
-                                                        int nbx, int nby, int nbz, const float *__restrict__ aux)
+__global__ __launch_bounds__(256, 2) void k_backward_tt_f64(GeoDev g, const double *__restrict__ proj,
+                                                            double *__restrict__ out, const int *__restrict__ skip,
+                                                            int nbx, int nby, int nbz)
 {
     if (skip && *skip) return;
-    using A = acc_t<T>;
-    constexpr bool SQ = EPI == BWD_DIAG || EPI == BWD_DIAG_INV;  // squared weights, e not read
+    using A = double;
     __shared__ A s_le[TT_CH_ROWS * TT_CH_COLS];
 
     const int nb = nbx * nby * nbz;
@@ -172,7 +146,7 @@ __global__ __launch_bounds__(256, sizeof(acc_t<T>) == 4 ? 5 : 2) void k_backward
             v0 = __builtin_amdgcn_readfirstlane(b0 < 0 ? 0 : b0);
             v1 = __builtin_amdgcn_readfirstlane(b1 > g.nv - 1 ? g.nv - 1 : b1);
         }
-        const T *pk = SQ ? proj : proj + (size_t)k * g.nv * g.nu;  // not read when SQ
+        const double *pk = proj + (size_t)k * g.nv * g.nu;
         const ColParam *ck = g.cols + (size_t)k * g.nu;
         TTTrap tu{};
         float dmin = 0.0f, dmax = 0.0f, rdmin = 0.0f, rdmax = 0.0f;
@@ -188,12 +162,12 @@ __global__ __launch_bounds__(256, sizeof(acc_t<T>) == 4 ? 5 : 2) void k_backward
                     for (int t = __builtin_amdgcn_workitem_id_x(); t < ncol * nrow; t += 256) {
                         // the projection value first: its load overlaps the parameter loads
                         // (offsets within one view fit in 32 bits: a projection has < 2^31 rays)
-                        const A ev = SQ ? (A)0 : to_acc(pk[(unsigned)((cv0 + r) * g.nu + cu0 + c)]);
+                        const A ev = pk[(unsigned)((cv0 + r) * g.nu + cu0 + c)];
                         const ColParam cp = ck[cu0 + c];
                         const RowParam rp = g.rows[cv0 + r];
                         const A amp = (A)tt_amplitude(ray_length_per_xi(cp.lxy2, rp.qz, cp.gp), cp.inv_a,
                                                       zeta_inv_slope(rp.inv_qz, cp.kz));
-                        s_le[r * TT_CH_COLS + c] = SQ ? amp * amp : amp * ev;
+                        s_le[r * TT_CH_COLS + c] = amp * ev;
                         r += dr;
                         c += dc;
                         if (c >= ncol) {
@@ -204,114 +178,35 @@ __global__ __launch_bounds__(256, sizeof(acc_t<T>) == 4 ? 5 : 2) void k_backward
                 }
                 __syncthreads();
                 if (valid)
-                    tt_gather_chunk<A, SQ>(g, iz0, nzb, tu, rdmin, rdmax, s_le, TT_CH_COLS, cu0, ncol, cv0, nrow,
+                    tt_gather_chunk<A, false>(g, iz0, nzb, tu, rdmin, rdmax, s_le, TT_CH_COLS, cu0, ncol, cv0, nrow,
                                            acc);
                 __syncthreads();
             }
         }
     }
 
-    double sq = 0.0;
     if (valid) {
 #pragma unroll
-        for (int j = 0; j < TT_TZ; ++j) {
-            if (j >= nzb) continue;
-            const int iz = iz0 + j;
-            const size_t vox = ((size_t)iz * g.ny + iy) * g.nx + ix;
-            sq += bwd_store<T, EPI, A>(out, out_z, sc, aux, vox, ((size_t)iy * g.nx + ix) * g.nz + iz, acc[j]);
-        }
-    }
-    if (bwd_has_partials<EPI>()) {
-        const double bs = tt_block_sum(sq);
-        if (__builtin_amdgcn_workitem_id_x() == 0) partials[w] = bs;
+        for (int j = 0; j < TT_TZ; ++j)
+            if (j < nzb) out[((size_t)(iz0 + j) * g.ny + iy) * g.nx + ix] = acc[j];
     }
 }
 
-template <typename TV, typename TP, int EPI>
-static void launch_ftt(const GeoDev &g, const TV *vol, const TV *vol_z, TP *out, const TP *aux, const Scalars *sc,
-                       double *partials, const int *skip, hipStream_t st)
+hipError_t launch_forward_tt_f64(const GeoDev &g, const double *vol, const double *vol_z, double *out, int epi,
+                                 const int *skip, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_forward_tt<TV, TP, EPI>), dim3((unsigned)tt_fwd_grid(g).nblocks), dim3(256), 0, st, g, vol,
-                       vol_z, out, aux, sc, partials, skip);
-}
-
-template <typename TV, typename TP>
-hipError_t launch_forward_tt(const GeoDev &g, const TV *vol, const TV *vol_z, TP *out, const TP *aux, int epi,
-                             const Scalars *sc, double *partials, const int *skip, hipStream_t st)
-{
-    if constexpr (std::is_same<TV, double>::value) {
-        if (epi != FWD_PLAIN) return hipErrorInvalidValue;
-        launch_ftt<TV, TP, FWD_PLAIN>(g, vol, vol_z, out, aux, sc, partials, skip, st);
-    } else {
-        switch (epi) {
-        case FWD_PLAIN: launch_ftt<TV, TP, FWD_PLAIN>(g, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        case FWD_NORM: launch_ftt<TV, TP, FWD_NORM>(g, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        case FWD_BMINUS: launch_ftt<TV, TP, FWD_BMINUS>(g, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        case FWD_LSQR: launch_ftt<TV, TP, FWD_LSQR>(g, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        default: return hipErrorInvalidValue;
-        }
-    }
+    if (epi != FWD_PLAIN) return hipErrorInvalidValue;  // double storage: the plain pair only
+    hipLaunchKernelGGL(k_forward_tt_f64, dim3((unsigned)tt_fwd_grid(g).nblocks), dim3(256), 0, st, g, vol, vol_z, out, skip);
     return hipGetLastError();
 }
 
-template <typename T, int EPI>
-static void launch_btt(const GeoDev &g, const T *proj, T *out, T *out_z, const Scalars *sc, double *partials,
-                       const int *skip, const float *aux, hipStream_t st)
+hipError_t launch_backward_tt_f64(const GeoDev &g, const double *proj, double *out, int epi, const int *skip, hipStream_t st)
 {
+    if (epi != BWD_PLAIN) return hipErrorInvalidValue;
     int nbx, nby, nbz;
     const int64_t nb = tt_backward_grid_dims(g, nbx, nby, nbz);
-    hipLaunchKernelGGL((k_backward_tt<T, EPI>), dim3((unsigned)nb), dim3(256), 0, st, g, proj, out, out_z, sc,
-                       partials, skip, nbx, nby, nbz, aux);
-}
-
-template <typename T>
-hipError_t launch_backward_tt(const GeoDev &g, const T *proj, T *out, T *out_z, int epi, const Scalars *sc,
-                              double *partials, const int *skip, hipStream_t st, const float *aux)
-{
-    if constexpr (std::is_same<T, double>::value) {
-        if (epi != BWD_PLAIN) return hipErrorInvalidValue;
-        launch_btt<T, BWD_PLAIN>(g, proj, out, out_z, sc, partials, skip, aux, st);
-    } else {
-        switch (epi) {
-        case BWD_PLAIN: launch_btt<T, BWD_PLAIN>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        case BWD_NORM: launch_btt<T, BWD_NORM>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        case BWD_LSQR0: launch_btt<T, BWD_LSQR0>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        case BWD_LSQR: launch_btt<T, BWD_LSQR>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        case BWD_TIK: launch_btt<T, BWD_TIK>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        case BWD_JACOBI: launch_btt<T, BWD_JACOBI>(g, proj, out, out_z, sc, partials, skip, aux, st); break;
-        default:
-            if constexpr (std::is_same<T, float>::value) {
-                if (epi == BWD_DIAG) {
-                    launch_btt<T, BWD_DIAG>(g, proj, out, out_z, sc, partials, skip, aux, st);
-                    break;
-                }
-                if (epi == BWD_DIAG_INV) {
-                    launch_btt<T, BWD_DIAG_INV>(g, proj, out, out_z, sc, partials, skip, aux, st);
-                    break;
-                }
-            }
-            return hipErrorInvalidValue;
-        }
-    }
+    hipLaunchKernelGGL(k_backward_tt_f64, dim3((unsigned)nb), dim3(256), 0, st, g, proj, out, skip, nbx, nby, nbz);
     return hipGetLastError();
 }
-
-#define KCT_TTF(TV, TP)                                                                                         \
-    template hipError_t launch_forward_tt<TV, TP>(const GeoDev &, const TV *, const TV *, TP *, const TP *, int, \
-                                                  const Scalars *, double *, const int *, hipStream_t);
-KCT_TTF(float, float)
-KCT_TTF(bf16, bf16)
-KCT_TTF(_Float16, _Float16)
-KCT_TTF(float, bf16)
-KCT_TTF(float, _Float16)
-KCT_TTF(double, double)
-
-#define KCT_TTB(T)                                                                                                \
-    template hipError_t launch_backward_tt<T>(const GeoDev &, const T *, T *, T *, int, const Scalars *, double *, \
-                                              const int *, hipStream_t, const float *);
-KCT_TTB(float)
-KCT_TTB(bf16)
-KCT_TTB(_Float16)
-KCT_TTB(double)
 
 }  // namespace kct
