@@ -23,10 +23,15 @@
 // takes 65.4 ms (74.9 ms with a test of every voxel against the brick's top, a
 // search for the first and last hit column, an integer clamp made of compares
 // and selects, and the ray parameters of a column read again for each of its pixels);
-// 256^3 x 360, 384 x 384 detector: 8.75 ms (10.5 ms).
+// 63.7 ms with the second row's test skipped where no voxel of the wavefront has one;
+// 256^3 x 360, 384 x 384 detector: 8.7 ms (10.5 ms).  EARLY (all but the 32-deep workgroup
+// bricks, whose registers it would spill): 192^3 x 180 in the wave form 1.97 -> 1.88 ms,
+// 128^3 x 720 1.48 -> 1.38, 256^3 x 90 at 0.7 pixels per voxel 0.98 -> 0.88 (both steps).
 #pragma once
 
 #pragma clang fp contract(off)
+
+#include <type_traits>
 
 #include "kct_internal.h"
 #include "kct_weights.h"
@@ -164,6 +169,42 @@ template <> __host__ __device__ __forceinline__ PixStage<float> load_pix<float>(
     return r;
 }
 
+// One staged record, read where this stands: a volatile access, which the compiler
+// does not move down to the record's first use (on the host a plain read).
+template <typename A> __host__ __device__ __forceinline__ PixStage<A> early_pix(const PixStage<A> *p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (std::is_same<A, float>::value) {
+        typedef float record __attribute__((ext_vector_type(3)));
+        typedef const volatile __attribute__((address_space(3))) record *lds_record;
+        typedef const __attribute__((address_space(3))) PixStage<A> *lds_pix;
+        const record v = *(lds_record)(lds_pix)p;
+        PixStage<A> r;
+        r.nzc = v.x;
+        r.czr = v.y;
+        r.le = v.z;
+        r.pad = 0.0f;
+        return r;
+    }
+#endif
+    return *p;
+}
+
+// The candidate of one record for one voxel with z-planes mb and mb1, over the
+// in-plane xi-interval [lo, hi], lo <= hi: a + w * (L e) (w^2 * le when SQ).
+// med3(hi, b0, b1) - med3(lo, b0, b1) is the overlap min(hi, max(b0, b1)) -
+// max(lo, min(b0, b1)) wherever that is positive (both medians then pick those
+// operands) and exactly 0 elsewhere (both medians clamp to the same end of
+// [min, max], or hi = lo): a candidate that misses adds 0 * le = 0 (le is finite)
+// and leaves the sum as it is.
+template <typename A, bool SQ>
+__host__ __device__ __forceinline__ A add_pix(const PixStage<A> &p, float lo, float hi, float mb, float mb1, A a)
+{
+    const float b0 = zeta_cross(mb, p.nzc, p.czr), b1 = zeta_cross(mb1, p.nzc, p.czr);
+    const float w = med3f(hi, b0, b1) - med3f(lo, b0, b1);
+    return fma_acc(SQ ? w * w : w, p.le, a);
+}
+
 // The candidates of one detector row for one voxel: the rays of the row in the
 // nh (<= NH) staged hit columns starting at prow, whose in-plane xi-intervals
 // are [lo[h], hi[h]] with lo[h] <= hi[h], against the voxel's z-planes mb and
@@ -179,16 +220,7 @@ __host__ __device__ __forceinline__ A add_row(const PixStage<A> *prow, int nh, c
     for (int h = 0; h < NH; ++h) p[h] = load_pix(prow + h);
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-        if (h == 0 || h < nh) {
-            const float b0 = zeta_cross(mb, p[h].nzc, p[h].czr), b1 = zeta_cross(mb1, p[h].nzc, p[h].czr);
-            // With lo <= hi, med3(hi, b0, b1) - med3(lo, b0, b1) is the overlap
-            // min(hi, max(b0, b1)) - max(lo, min(b0, b1)) wherever that is positive
-            // (both medians then pick those operands) and exactly 0 elsewhere (both
-            // medians clamp to the same end of [min, max], or hi = lo): a candidate
-            // that misses adds 0 * le = 0 (le is finite) and leaves the sum as it is.
-            const float w = med3f(hi[h], b0, b1) - med3f(lo[h], b0, b1);
-            a = fma_acc(SQ ? w * w : w, p[h].le, a);
-        }
+        if (h == 0 || h < nh) a = add_pix<A, SQ>(p[h], lo[h], hi[h], mb, mb1, a);
     }
     return a;
 }
@@ -245,6 +277,16 @@ __host__ __device__ __forceinline__ const PixStage<A> *row_record(const PixStage
     return pg + r * (CHC != 0 ? CHC : stride);
 }
 
+// Whether c holds in any lane of the wavefront: a scalar value on the GPU.
+__host__ __device__ __forceinline__ bool any_lane(bool c)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_ballot_w64(c) != 0;
+#else
+    return c;
+#endif
+}
+
 // v clamped to [-1, hi] (hi >= -1 equal in every lane): one instruction on the GPU.
 __host__ __device__ __forceinline__ int clamp_row(int v, int hi)
 {
@@ -268,7 +310,7 @@ __host__ __device__ __forceinline__ int clamp_row(int v, int hi)
 // row staged after them, and a row that is not a candidate has weight exactly
 // 0 (the weights are exact).  Further rows, up to the last staged one, follow in a
 // loop.  pg + va * stride is the record of row va + 1 in the group's first column.
-template <typename A, bool SQ, int CHC, int NH, int TZN>
+template <typename A, bool SQ, int CHC, int NH, bool EARLY, int TZN>
 __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int stride, int nh, const float (&lo)[NH],
                                                     const float (&hi)[NH], float mbz0, float l0, float sl,
                                                     float h0, float sh, int nrow, A (&acc)[TZN])
@@ -282,22 +324,56 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int s
     asm volatile("" : "+v"(mbb));
 #endif
     float mb = mbb;  // lower plane of voxel j (exact: an integer or half-integer)
+    // Whether some voxel of some lane has a second candidate row.  vhi - vlo is linear in j
+    // and negative at both ends where no voxel has (the margin is far above its rounding).
+    const float len0 = (h0 + sh) - l0, len1 = len0 + (float)(TZN - 1) * (sh - sl);
+    const bool more = any_lane(fmaxf(len0, len1) > -1.0e-3f);
+    // EARLY: the next voxel's first record is read before this voxel's arithmetic (its
+    // latency is then covered; it takes four more registers)
+    int va = clamp_row((int)floorf(l0), nrow - 1);
+    const PixStage<A> *prow = row_record<A, CHC>(pg, va, stride);
+    PixStage<A> rec{};
+    if constexpr (EARLY) rec = early_pix(prow);
 #pragma unroll
     for (int j = 0; j < TZN; ++j) {
         const float mb1 = mb + 1.0f;
         // candidate rows va + 1 .. vb + 1: floor(lo) + 1 is ceil(lo) except at an
         // integer lo, whose row lies 0.01 below the true bound and is rightly left out
-        const float vlo = __builtin_fmaf((float)j, sl, l0), vhi = __builtin_fmaf((float)(j + 1), sh, h0);
-        const int va = clamp_row((int)floorf(vlo), nrow - 1);
-        int vb = (int)floorf(vhi);
-        vb = vb > nrow - 2 ? nrow - 2 : vb;
-        const PixStage<A> *prow = row_record<A, CHC>(pg, va, stride);
-        A a = add_row<A, SQ, NH>(prow, nh, lo, hi, mb, mb1, acc[j]);
-        for (int v = va; v < vb; ++v) {
-            prow += CHC != 0 ? CHC : stride;
-            a = add_row<A, SQ, NH>(prow, nh, lo, hi, mb, mb1, a);
+        int va_next = va;
+        const PixStage<A> *prow_next = prow;
+        PixStage<A> rec_next = rec;
+        if constexpr (EARLY) {
+            if (j + 1 < TZN) {
+                va_next = clamp_row((int)floorf(__builtin_fmaf((float)(j + 1), sl, l0)), nrow - 1);
+                prow_next = row_record<A, CHC>(pg, va_next, stride);
+                rec_next = early_pix(prow_next);
+            }
+            acc[j] = add_pix<A, SQ>(rec, lo[0], hi[0], mb, mb1, acc[j]);
+#pragma unroll
+            for (int h = 1; h < NH; ++h)
+                if (h < nh) acc[j] = add_pix<A, SQ>(load_pix(prow + h), lo[h], hi[h], mb, mb1, acc[j]);
+        } else {
+            if (j > 0) {
+                va = clamp_row((int)floorf(__builtin_fmaf((float)j, sl, l0)), nrow - 1);
+                prow = row_record<A, CHC>(pg, va, stride);
+            }
+            acc[j] = add_row<A, SQ, NH>(prow, nh, lo, hi, mb, mb1, acc[j]);
         }
-        acc[j] = a;
+        if (more) {
+            int vb = (int)floorf(__builtin_fmaf((float)(j + 1), sh, h0));
+            vb = vb > nrow - 2 ? nrow - 2 : vb;
+            A a = acc[j];
+            for (int v = va; v < vb; ++v) {
+                prow += CHC != 0 ? CHC : stride;
+                a = add_row<A, SQ, NH>(prow, nh, lo, hi, mb, mb1, a);
+            }
+            acc[j] = a;
+        }
+        if constexpr (EARLY) {
+            va = va_next;
+            prow = prow_next;
+            rec = rec_next;
+        }
         mb = mb1;
     }
 }
@@ -309,7 +385,7 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int s
 // (weight 0 for any voxel).  NH columns are taken at once.
 // SQ: accumulate w_ij^2 * le instead of w_ij * le (with le = L^2 this sums the
 // squared weights, the diagonal of A^T A).
-template <typename A, bool SQ, int CHC, int NH, int TZN>
+template <typename A, bool SQ, int CHC, int NH, bool EARLY, int TZN>
 __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const ViewParam &vp, int ix, int iy, int iz0,
                                                       const PixStage<A> *s_pix, const ColStage *s_col, int cu0,
                                                       int ncol, int cv0, int nrow, A (&acc)[TZN], int stride = CHC)
@@ -368,7 +444,7 @@ __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const Vie
         const float sh = (fmaxf(b1, b2) - fmaxf(a1, a2)) * (1.0f / TZN);
         const float l0 = fminf(a1, a2) + vofs_lo, h0 = fmaxf(a1, a2) + vofs_hi;
         const PixStage<A> *pg = s_pix + ((c0 - cu0) + (CHC != 0 ? CHC : stride));  // row va + 1 at pg + va * stride
-        voxel_rows<A, SQ, CHC, NH, TZN>(pg, stride, nh, lo, hi, mbz0, l0, sl, h0, sh, nrow, acc);
+        voxel_rows<A, SQ, CHC, NH, EARLY, TZN>(pg, stride, nh, lo, hi, mbz0, l0, sl, h0, sh, nrow, acc);
     }
 }
 

@@ -12,9 +12,9 @@
 // Bounded by VALU issue as the other form, at about 1.0 wave-instruction per
 // CU-cycle; a quarter to a third of its instructions stage the shadow.  Measured
 // (one backprojection, 16 x 16 x 16 workgroup bricks -> this form): 64^3 x 90 views,
-// 96 x 96 detector 1260 -> 98 us; 96^3 x 186, 218 x 218 4170 -> 882 us; 64^3 x 199,
+// 96 x 96 detector 1260 -> 98 us; 96^3 x 186, 218 x 218 4170 -> 872 us; 64^3 x 199,
 // 274 x 274 (four pixels per voxel) 22.4 -> 1.45 ms; 128^3 x 720, 154 x 120
-// 3.06 -> 1.52 ms; 192^3 x 180, 256 x 256 2.38 -> 1.95 ms.
+// 3.06 -> 1.39 ms; 192^3 x 180, 256 x 256 2.38 -> 1.88 ms.
 #pragma once
 
 #include "kct_epilogue.h"
@@ -181,7 +181,7 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
                     int ixv = ix, iyv = iy;
                     asm volatile("" : "+v"(ixv), "+v"(iyv));
                     if (valid)
-                        gather_chunk<A, SQ, 0, NCOL>(g, vp, ixv, iyv, iz0, s_pix, s_col, cu0, ncol, cv0, nrow, acc, ncol);
+                        gather_chunk<A, SQ, 0, NCOL, true>(g, vp, ixv, iyv, iz0, s_pix, s_col, cu0, ncol, cv0, nrow, acc, ncol);
                     wave_lds_order();
                 }
             }
