@@ -20,6 +20,7 @@ whatever the storage type of b.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import dataclasses
 import math
@@ -53,6 +54,16 @@ def _dtype_code(t):
 def _stream_handle(device):
     torch = _torch()
     return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+
+
+def _on_device(device):
+    """Context with ``device`` current (nothing to do when it already is: entering
+    torch's context costs more than the call it guards)."""
+    torch = _torch()
+    return _NO_CONTEXT if torch.cuda.current_device() == device.index else torch.cuda.device(device)
+
+
+_NO_CONTEXT = contextlib.nullcontext()
 
 
 class Geometry:
@@ -207,7 +218,7 @@ def project(g: Geometry, x, out=None, workspace=None, transposed_copy: bool = Tr
         if workspace is None:
             workspace = _workspace(g.project_workspace_bytes(x.dtype), g.device)
         ws_ptr, ws_bytes = ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size()
-    with torch.cuda.device(g.device):
+    with _on_device(g.device):
         _lib.check(_lib.load().kct_project(g.handle, _dtype_code(x.dtype), ctypes.c_void_p(x.data_ptr()),
                                            ctypes.c_void_p(out.data_ptr()), ws_ptr, ws_bytes,
                                            _stream_handle(g.device)))
@@ -223,7 +234,7 @@ def backproject(g: Geometry, b, out=None):
     _check_tensor(out, g.vol_shape, "out", g.device)
     if out.dtype != b.dtype:
         raise TypeError("out must have b's dtype")
-    with torch.cuda.device(g.device):
+    with _on_device(g.device):
         _lib.check(_lib.load().kct_backproject(g.handle, _dtype_code(b.dtype), ctypes.c_void_p(b.data_ptr()),
                                                ctypes.c_void_p(out.data_ptr()), _stream_handle(g.device)))
     return out
@@ -248,7 +259,7 @@ def diag_normal(g: Geometry, out=None):
     _check_tensor(out, g.vol_shape, "out", g.device)
     if out.dtype != torch.float32:
         raise TypeError("out must be float32")
-    with torch.cuda.device(g.device):
+    with _on_device(g.device):
         _lib.check(_lib.load().kct_diag_normal(g.handle, ctypes.c_void_p(out.data_ptr()), _stream_handle(g.device)))
     return out
 
@@ -274,7 +285,7 @@ def _solve(which, g, b, K, x0, err, history, workspace, out, tikhonov=0.0, jacob
     ws_bytes = workspace.numel() * workspace.element_size()
     info = _lib.SolveInfo()
     fn = _lib.load().kct_cgls_solve if which == "cgls" else _lib.load().kct_lsqr_solve
-    with torch.cuda.device(g.device):
+    with _on_device(g.device):
         st = fn(g.handle, _dtype_code(b.dtype), ctypes.c_void_p(b.data_ptr()), ctypes.c_void_p(out.data_ptr()),
                 ctypes.byref(opts), ctypes.c_void_p(workspace.data_ptr()), ws_bytes, ctypes.byref(info),
                 _stream_handle(g.device))

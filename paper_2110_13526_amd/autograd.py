@@ -44,10 +44,17 @@ def _aligned(t):
 def _batched(fn, g, t, out_shape):
     lead = t.shape[: t.dim() - 3]
     flat = t.reshape((-1,) + tuple(t.shape[-3:]))
-    outs = [fn(g, _aligned(flat[i])) for i in range(flat.shape[0])]
-    if not outs:
-        return t.new_empty(tuple(lead) + tuple(out_shape))
-    return torch.stack(outs).reshape(tuple(lead) + tuple(out_shape))
+    if flat.shape[0] == 1:
+        return fn(g, _aligned(flat[0])).reshape(tuple(lead) + tuple(out_shape))
+    out = t.new_empty(tuple(lead) + tuple(out_shape))
+    items = out.reshape((-1,) + tuple(out_shape))
+    for i in range(flat.shape[0]):
+        # each result straight into its place where that has the C ABI's alignment
+        if items[i].data_ptr() % 16 == 0:
+            fn(g, _aligned(flat[i]), out=items[i])
+        else:
+            items[i].copy_(fn(g, _aligned(flat[i])))
+    return out
 
 
 class ProjectFn(torch.autograd.Function):
