@@ -145,8 +145,7 @@ hipError_t batch_iteration(const Batch *b, const BatchInst *T, const int64_t *of
     if ((e = launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 1, b->grid_dir, 0, st)) != hipSuccess) return e;
     if ((e = launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 2, b->grid_fwd, st)) != hipSuccess) return e;
     if ((e = launch_batch_finalize(T, c, F_ALPHA, BG_FWD, st)) != hipSuccess) return e;
-    if ((e = launch_batch_vec(T, c, BV_CGLS_X, 0, 0.0, st)) != hipSuccess) return e;
-    if ((e = launch_batch_vec(T, c, BV_CGLS_E, 0, 0.0, st)) != hipSuccess) return e;
+    if ((e = launch_batch_vec(T, c, BV_CGLS_XE, 0, 0.0, st)) != hipSuccess) return e;
     return launch_batch_finalize(T, c, F_NB, BG_STREAM, st);
 }
 
@@ -402,8 +401,7 @@ kct_status kct_batch_cgls_solve(kct_batch h, const float *const *bs, float *cons
     KCT_BTRY(launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 1, b->grid_dir, 1, st));
     KCT_BTRY(launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 2, b->grid_fwd, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_ALPHA, BG_FWD, st));
-    KCT_BTRY(launch_batch_vec(T, c, BV_CGLS_X, 0, 0.0, st));
-    KCT_BTRY(launch_batch_vec(T, c, BV_CGLS_E, 0, 0.0, st));
+    KCT_BTRY(launch_batch_vec(T, c, BV_CGLS_XE, 0, 0.0, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_NB, BG_STREAM, st));
     if (K > 1) {
         if (use_graph) {

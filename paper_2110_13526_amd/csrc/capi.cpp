@@ -246,7 +246,7 @@ kct_status project_t(const Geometry *g, const void *x, void *b, void *ws, hipStr
     const char *fn = "kct_project";
     const T *vol = (const T *)x;
     T *vz = nullptr;
-    if (ws) {
+    if (ws && !forward_in_place(g->dev)) {
         vz = (T *)ws;
         KCT_TRY((launch_zfast_copy<T, T>(g->dev, vol, vz, st)));
     }
@@ -321,13 +321,11 @@ kct_status cgls_t(const Geometry *g, const void *bv, void *xv, const kct_solve_o
     KCT_TRY(hipGetLastError());
     if (jacobi)  // M^2 = 1 / diag(A^T A), 0 where the diagonal is 0
         KCT_TRY(launch_backward<float>(G, nullptr, m2, nullptr, BWD_DIAG_INV, nullptr, nullptr, nullptr, st));
-    // NB0 = |b|
-    KCT_TRY(launch_norm2<T>(b, m, part, nullptr, st));
+    // NB0 = |b|; x = x0; p = A x; e = b - p
+    KCT_TRY(launch_norm2<T>(b, m, part, nullptr, st, o->x0_is_zero ? e : nullptr));
     KCT_TRY(launch_finalize(sc, part, ns, F_NB0, st));
-    // x = x0; p = A x; e = b - p
     if (o->x0_is_zero) {
         KCT_TRY(launch_fill_zero<float>(x, n, st));
-        KCT_TRY(launch_copy<T>(b, e, m, st));
     } else {
         // single-precision z-fastest copy of x0 in the (not yet used) d and d_z space
         float *xz0 = (float *)(w + L.v0);
@@ -337,12 +335,12 @@ kct_status cgls_t(const Geometry *g, const void *bv, void *xv, const kct_solve_o
     }
     // x += alpha d; e -= alpha p (or e = b - A x every re-th iteration); NB; i = i + 1
     auto step_end = [&](int i) -> kct_status {
-        KCT_TRY(launch_cgls_x<T>(x, d, sc, n, st));
         if (re > 0 && i % re == 0) {
+            KCT_TRY(launch_cgls_x<T>(x, d, sc, n, st));
             KCT_TRY((launch_forward<float, T>(G, x, nullptr, e, b, FWD_BMINUS, sc, part, done, st)));
             KCT_TRY(launch_finalize(sc, part, nf, F_NB, st));
         } else {
-            KCT_TRY(launch_cgls_e<T>(e, p, sc, m, part, st));
+            KCT_TRY(launch_cgls_xe<T>(x, d, n, e, p, m, sc, part, st));
             KCT_TRY(launch_finalize(sc, part, ns, F_NB, st));
         }
         return KCT_OK;
@@ -394,13 +392,11 @@ kct_status lsqr_t(const Geometry *g, const void *bv, void *xv, const kct_solve_o
     hipLaunchKernelGGL(k_init_scalars, dim3(1), dim3(64), 0, st, sc, K, o->err_tol, o->history,
                        storage_scales(g, dtype_of<T>()), 0.0, o->tikhonov);
     KCT_TRY(hipGetLastError());
-    KCT_TRY(launch_norm2<T>(b, m, part, nullptr, st));
+    // |b|; beta u = b - A x0 (u = b has the same partial sums)
+    KCT_TRY(launch_norm2<T>(b, m, part, nullptr, st, o->x0_is_zero ? u : nullptr));
     KCT_TRY(launch_finalize(sc, part, ns, F_NB0, st));
-    // beta u = b - A x0
     if (o->x0_is_zero) {
         KCT_TRY(launch_fill_zero<float>(x, n, st));
-        KCT_TRY(launch_copy<T>(b, u, m, st));
-        KCT_TRY(launch_norm2<T>(u, m, part, done, st));
         KCT_TRY(launch_finalize(sc, part, ns, F_L_BETA0, st));
     } else {
         // single-precision z-fastest copy of x0 in the (not yet used) v and v_z space

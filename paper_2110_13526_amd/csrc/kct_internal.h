@@ -192,6 +192,7 @@ struct FwdPlan {
 };
 FwdPlan forward_plan(const GeoDev &g);
 FwdPlan forward_plan_rows(const GeoDev &g, int rows);
+bool forward_in_place(const GeoDev &g);
 int64_t forward_num_blocks(const GeoDev &g);                         // of forward_plan (or the TT projector's)
 int64_t forward_num_blocks_r(const GeoDev &g, int rows_per_lane);
 template <typename TV, typename TP, int R>
@@ -204,16 +205,15 @@ int64_t stream_num_blocks();
 // dst[(iy * nx + ix) * nz + iz] = src[(iz * ny + iy) * nx + ix]
 template <typename TS, typename TD>
 hipError_t launch_zfast_copy(const GeoDev &g, const TS *src, TD *dst, hipStream_t st);
+// partial |v|^2; copy (optional): v is copied there as well
 template <typename T>
-hipError_t launch_norm2(const T *v, int64_t n, double *partials, const int *skip, hipStream_t st);
+hipError_t launch_norm2(const T *v, int64_t n, double *partials, const int *skip, hipStream_t st, T *copy = nullptr);
 hipError_t launch_finalize(Scalars *sc, const double *partials, int64_t nparts, int op, hipStream_t st,
                            const double *partials2 = nullptr, int64_t nparts2 = 0);
 template <typename T>
 hipError_t launch_fill_zero(T *v, int64_t n, hipStream_t st);
 // The solvers keep the iterate x in single precision whatever the storage type
 // of the other vectors (16-bit iterates stagnate).
-template <typename T>
-hipError_t launch_copy(const T *src, T *dst, int64_t n, hipStream_t st);
 // x += alpha d
 template <typename T>
 hipError_t launch_cgls_x(float *x, const T *d, const Scalars *sc, int64_t n, hipStream_t st);
@@ -222,9 +222,10 @@ template <typename T>
 hipError_t launch_cgls_d(const GeoDev &g, const T *r, T *d, T *dz, const Scalars *sc, int first,
                          hipStream_t st, double *dpart = nullptr);
 int64_t cgls_d_num_blocks(const GeoDev &g);
-// e -= alpha p, partial |e|^2
+// x += alpha d, e -= alpha p, partial |e|^2 (n voxels, m rays)
 template <typename T>
-hipError_t launch_cgls_e(T *e, const T *p, const Scalars *sc, int64_t n, double *partials, hipStream_t st);
+hipError_t launch_cgls_xe(float *x, const T *d, int64_t n, T *e, const T *p, int64_t m, const Scalars *sc,
+                          double *partials, hipStream_t st);
 // LSQR: w = w_vcoef v (init) or x += x_coef w; w = w_vcoef v - w_coef w
 template <typename T>
 hipError_t launch_lsqr_xw(float *x, T *w, const T *v, const Scalars *sc, int init, int64_t n, hipStream_t st);
@@ -309,7 +310,7 @@ hipError_t launch_batch_forward(const BatchInst *B, const int64_t *off, int coun
 hipError_t launch_batch_backward(const BatchInst *B, const int64_t *off, int count, BatchQueue *q, int grid,
                                  hipStream_t st);
 // op: one of the batched vector steps below
-enum BatchVecOp { BV_INIT = 0, BV_NORM_B, BV_X0_E, BV_CGLS_X, BV_CGLS_E };
+enum BatchVecOp { BV_INIT = 0, BV_NORM_B, BV_X0_E, BV_CGLS_XE };
 hipError_t launch_batch_vec(const BatchInst *B, int count, int op, int maxiter, double err, hipStream_t st);
 hipError_t launch_batch_dir(const BatchInst *B, const int64_t *off, int count, BatchQueue *q, int grid, int first,
                             hipStream_t st);

@@ -39,6 +39,16 @@ FwdPlan forward_plan_rows(const GeoDev &g, int rows)
     return FwdPlan{rows, rows <= 2 && fwd_grid(g, rows).nblocks * FWD_COLS <= 5120};
 }
 
+// Whether a plain projection reads the volume in its own layout although it has room
+// for the z-fastest copy: a divided walk of a volume of up to 32^3 voxels, which the
+// L1 and L2 hold, takes less longer than the copy's launch costs.  Measured (us, with
+// the copy / in place): 16^3 x 12 views 11.7 / 8.7; 24^3 x 60 11.3 / 8.8; 32^3 x 60 15.0 /
+// 12.3; but 32^3 x 200 (not divided) 32 / 39, 40^3 x 60 17.5 / 19.7, 48^3 x 60 22 / 32.
+bool forward_in_place(const GeoDev &g)
+{
+    return g.projector == KCT_PROJECTOR_SIDDON && (int64_t)g.nx * g.ny * g.nz <= 32768 && forward_plan(g).divided;
+}
+
 int64_t forward_num_blocks(const GeoDev &g)
 {
     return g.projector == KCT_PROJECTOR_TT ? tt_forward_num_blocks(g) : fwd_grid(g, forward_plan(g).rows).nblocks;

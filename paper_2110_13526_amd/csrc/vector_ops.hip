@@ -33,12 +33,14 @@ __device__ __forceinline__ double block_sum(double v)
 
 template <typename T>
 __global__ __launch_bounds__(TB) void k_norm2(const T *__restrict__ v, int64_t n, double *__restrict__ partials,
-                                              const int *__restrict__ skip)
+                                              const int *__restrict__ skip, T *__restrict__ copy)
 {
     if (skip && *skip) return;
     double s = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TB) {
-        double x = (double)to_f32(v[i]);
+        const T vi = v[i];
+        if (copy) copy[i] = vi;
+        const double x = (double)to_f32(vi);
         s += x * x;
     }
     double b = block_sum(s);
@@ -52,12 +54,6 @@ __global__ __launch_bounds__(TB) void k_fill_zero(T *__restrict__ v, int64_t n)
         v[i] = from_f32<T>(0.0f);
 }
 
-template <typename T>
-__global__ __launch_bounds__(TB) void k_copy(const T *__restrict__ s, T *__restrict__ d, int64_t n)
-{
-    for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TB) d[i] = s[i];
-}
-
 // x += alpha d
 template <typename T>
 __global__ __launch_bounds__(TB) void k_cgls_x(float *__restrict__ x, const T *__restrict__ d,
@@ -69,16 +65,18 @@ __global__ __launch_bounds__(TB) void k_cgls_x(float *__restrict__ x, const T *_
         x[i] = x[i] + alpha * to_f32(d[i]);
 }
 
-// e -= alpha p, partial |e|^2
+// x += alpha d; e -= alpha p, partial |e|^2
 template <typename T>
-__global__ __launch_bounds__(TB) void k_cgls_e(T *__restrict__ e, const T *__restrict__ p,
-                                               const Scalars *__restrict__ sc, int64_t n,
-                                               double *__restrict__ partials)
+__global__ __launch_bounds__(TB) void k_cgls_xe(float *__restrict__ x, const T *__restrict__ d, int64_t n,
+                                                T *__restrict__ e, const T *__restrict__ p, int64_t m,
+                                                const Scalars *__restrict__ sc, double *__restrict__ partials)
 {
     if (sc->done) return;
-    const float alpha = (float)sc->e_alpha;
+    const float xalpha = (float)sc->x_alpha, alpha = (float)sc->e_alpha;
+    const int64_t i0 = (int64_t)blockIdx.x * TB + threadIdx.x, stride = (int64_t)gridDim.x * TB;
+    for (int64_t i = i0; i < n; i += stride) x[i] = x[i] + xalpha * to_f32(d[i]);
     double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TB) {
+    for (int64_t i = i0; i < m; i += stride) {
         const T v = from_f32<T>(to_f32(e[i]) - alpha * to_f32(p[i]));
         e[i] = v;
         const double dv = (double)to_f32(v);
@@ -176,19 +174,24 @@ __global__ __launch_bounds__(TB) void k_lsqr_xw(float *__restrict__ x, T *__rest
     }
 }
 
-// Fixed-order sum of the partials followed by one scalar step.
+// Fixed-order sum of the partials (every thread gets it): strided sums in two
+// accumulators, the wavefront's by shuffles, the workgroup's in order.
 __device__ double fixed_order_sum(const double *__restrict__ partials, int64_t np, double *red)
 {
-    double s = 0.0;
-    for (int64_t i = threadIdx.x; i < np; i += TB) s += partials[i];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = TB / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
+    double s = 0.0, t = 0.0;
+    int64_t i = threadIdx.x;
+    for (; i + TB < np; i += 2 * TB) {
+        s += partials[i];
+        t += partials[i + TB];
     }
-    const double r = red[0];
+    if (i < np) s += partials[i];
+    s += t;
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    __syncthreads();  // the previous sum's readers are done with red
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
+    double r = red[0];
+    for (int q = 1; q < TB / 64; ++q) r += red[q];
     return r;
 }
 
@@ -200,7 +203,7 @@ __device__ __forceinline__ void finalize_step(Scalars *__restrict__ sc, const do
                                               int64_t np2)
 {
     if (op != F_NB0 && sc->done) return;
-    __shared__ double red[TB];
+    __shared__ double red[TB / 64];
     const double S = fixed_order_sum(partials, np, red);
     const double S2 = partials2 ? fixed_order_sum(partials2, np2, red) : 0.0;
     if (threadIdx.x != 0) return;
@@ -392,11 +395,9 @@ __global__ __launch_bounds__(TB) void kb_vec(const BatchInst *__restrict__ B, in
         return;
     }
     if (sc->done) return;
-    if (op == BV_CGLS_X) {  // x += alpha d
-        const float alpha = (float)sc->x_alpha;
-        for (int64_t k = i0; k < bi->n; k += stride) bi->x[k] = bi->x[k] + alpha * bi->d[k];
-    } else if (op == BV_CGLS_E) {  // e -= alpha p, partials of |e|^2
-        const float alpha = (float)sc->e_alpha;
+    if (op == BV_CGLS_XE) {  // x += alpha d; e -= alpha p, partials of |e|^2
+        const float xalpha = (float)sc->x_alpha, alpha = (float)sc->e_alpha;
+        for (int64_t k = i0; k < bi->n; k += stride) bi->x[k] = bi->x[k] + xalpha * bi->d[k];
         double q = 0.0;
         for (int64_t k = i0; k < bi->m; k += stride) {
             const float v = bi->e[k] - alpha * bi->p[k];
@@ -483,10 +484,10 @@ hipError_t launch_zfast_copy(const GeoDev &g, const TS *src, TD *dst, hipStream_
 }
 
 template <typename T>
-hipError_t launch_norm2(const T *v, int64_t n, double *partials, const int *skip, hipStream_t st)
+hipError_t launch_norm2(const T *v, int64_t n, double *partials, const int *skip, hipStream_t st, T *copy)
 {
     // always STREAM_BLOCKS partials so the finalize step reads a fixed count
-    hipLaunchKernelGGL(k_norm2<T>, dim3(STREAM_BLOCKS), dim3(TB), 0, st, v, n, partials, skip);
+    hipLaunchKernelGGL(k_norm2<T>, dim3(STREAM_BLOCKS), dim3(TB), 0, st, v, n, partials, skip, copy);
     return hipGetLastError();
 }
 
@@ -501,13 +502,6 @@ template <typename T>
 hipError_t launch_fill_zero(T *v, int64_t n, hipStream_t st)
 {
     hipLaunchKernelGGL(k_fill_zero<T>, sgrid(n), dim3(TB), 0, st, v, n);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_copy(const T *src, T *dst, int64_t n, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_copy<T>, sgrid(n), dim3(TB), 0, st, src, dst, n);
     return hipGetLastError();
 }
 
@@ -531,9 +525,10 @@ hipError_t launch_cgls_d(const GeoDev &g, const T *r, T *d, T *dz, const Scalars
 int64_t cgls_d_num_blocks(const GeoDev &g) { return (int64_t)((g.nx + 31) / 32) * ((g.nz + 31) / 32) * g.ny; }
 
 template <typename T>
-hipError_t launch_cgls_e(T *e, const T *p, const Scalars *sc, int64_t n, double *partials, hipStream_t st)
+hipError_t launch_cgls_xe(float *x, const T *d, int64_t n, T *e, const T *p, int64_t m, const Scalars *sc,
+                          double *partials, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_cgls_e<T>, dim3(STREAM_BLOCKS), dim3(TB), 0, st, e, p, sc, n, partials);
+    hipLaunchKernelGGL(k_cgls_xe<T>, dim3(STREAM_BLOCKS), dim3(TB), 0, st, x, d, n, e, p, m, sc, partials);
     return hipGetLastError();
 }
 
@@ -546,13 +541,13 @@ hipError_t launch_lsqr_xw(float *x, T *w, const T *v, const Scalars *sc, int ini
 }
 
 #define KCT_VINST(T)                                                                                       \
-    template hipError_t launch_norm2<T>(const T *, int64_t, double *, const int *, hipStream_t);          \
+    template hipError_t launch_norm2<T>(const T *, int64_t, double *, const int *, hipStream_t, T *);     \
     template hipError_t launch_fill_zero<T>(T *, int64_t, hipStream_t);                                   \
-    template hipError_t launch_copy<T>(const T *, T *, int64_t, hipStream_t);                             \
     template hipError_t launch_cgls_x<T>(float *, const T *, const Scalars *, int64_t, hipStream_t);      \
     template hipError_t launch_cgls_d<T>(const GeoDev &, const T *, T *, T *, const Scalars *, int,       \
                                          hipStream_t, double *);                                          \
-    template hipError_t launch_cgls_e<T>(T *, const T *, const Scalars *, int64_t, double *, hipStream_t); \
+    template hipError_t launch_cgls_xe<T>(float *, const T *, int64_t, T *, const T *, int64_t, const Scalars *, \
+                                          double *, hipStream_t);                                          \
     template hipError_t launch_lsqr_xw<T>(float *, T *, const T *, const Scalars *, int, int64_t, hipStream_t);
 KCT_VINST(float)
 KCT_VINST(bf16)
