@@ -35,17 +35,18 @@ __device__ __forceinline__ double bwd_block_sum(double v)
 
 // backward_block runs workgroup w (0 <= w < nbx * nby * nbz) of the
 // backprojection into one volume; its partial sum goes to partials[w].
-// s_pix / s_col: LDS for ch_rows(TZB) x CHC staged pixels (plus a zero row and a
-// spare record) and CHC columns.
+// s_pix / s_col / s_row: LDS for ch_rows(TZB) x CHC staged pixels (plus a zero row and a
+// spare record), CHC columns and ch_rows(TZB) + 1 rows.
 template <typename T, int EPI, int TZB, int CHC>
 __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *__restrict__ proj,
                                                T *__restrict__ out, T *__restrict__ out_z,
                                                const Scalars *__restrict__ sc, double *__restrict__ partials,
                                                int nbx, int nby, int nbz, const float *__restrict__ aux,
-                                               PixStage<acc_t<T>> *s_pix, ColStage *s_col)
+                                               PixStage<acc_t<T>, split_records<acc_t<T>>(TZB)> *s_pix, ColStage *s_col, float *s_row)
 {
     using A = acc_t<T>;
     constexpr int CHR = ch_rows(TZB);  // staged rows per chunk
+    constexpr bool SPLIT = split_records<A>(TZB);
     constexpr bool SQ = EPI == BWD_DIAG || EPI == BWD_DIAG_INV;  // squared weights, e not read
 
     // XCD-aware brick assignment
@@ -116,10 +117,10 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
                         if (r0 == 0) s_col[c] = stage_column(g, vp.dom, cp);
                         unsigned pix = ((unsigned)(cv0 + r0) * (unsigned)g.nu + (unsigned)(cu0 + c)) * (unsigned)sizeof(T);
                         unsigned row = (unsigned)(cv0 + r0) * (unsigned)sizeof(RowParam);
-                        PixStage<A> *rec = s_pix + (r0 * CHC + c);
+                        PixStage<A, SPLIT> *rec = s_pix + (r0 * CHC + c);
                         for (int r = r0; r < nrow; r += step) {
                             const A ev = SQ ? (A)0 : to_acc(*byte_at<T>(pk, pix));
-                            *rec = stage_pixel<A, SQ>(cp, *byte_at<RowParam>(g.rows, row), ev);
+                            *rec = stage_pixel<A, SQ, SPLIT>(cp, *byte_at<RowParam>(g.rows, row), ev);
                             pix += (unsigned)(step * g.nu) * (unsigned)sizeof(T);
                             row += (unsigned)step * (unsigned)sizeof(RowParam);
                             rec += step * CHC;
@@ -128,7 +129,8 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
                 }
                 // a zero row after the chunk's last: the gather reads a voxel's first
                 // candidate row without a branch, and this one has weight 0 for any voxel
-                if (tid < ncol) s_pix[nrow * CHC + tid] = zero_pixel<A>();
+                if (tid < ncol) s_pix[nrow * CHC + tid] = zero_pixel<A, SPLIT>();
+                if (SPLIT && tid <= nrow) s_row[tid] = tid < nrow ? g.rows[cv0 + tid].s_inv : 0.0f;
                 __syncthreads();
                 // 3. gather
                 // the lane's column indices laundered per chunk: the few values derived
@@ -136,7 +138,7 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
                 // through the view loop
                 int ixv = ix, iyv = iy;
                 asm volatile("" : "+v"(ixv), "+v"(iyv));
-                if (valid) gather_chunk<A, SQ, CHC, NH, (TZB < TZ_DEEP)>(g, vp, ixv, iyv, iz0, s_pix, s_col, cu0, ncol, cv0, nrow, acc);
+                if (valid) gather_chunk<A, SQ, CHC, NH, (TZB < TZ_DEEP)>(g, vp, ixv, iyv, iz0, s_pix, s_col, s_row, cu0, ncol, cv0, nrow, acc);
                 __syncthreads();
             }
         }
@@ -170,10 +172,11 @@ __global__ __launch_bounds__(256, sizeof(acc_t<T>) != 4 ? 2 : 6) void k_backward
 {
     if (skip && *skip) return;
     constexpr int CHC = ch_cols(TZB);
-    __shared__ PixStage<acc_t<T>> s_pix[(ch_rows(TZB) + 1) * CHC + NH - 1];
+    __shared__ PixStage<acc_t<T>, split_records<acc_t<T>>(TZB)> s_pix[(ch_rows(TZB) + 1) * CHC + NH - 1];
     __shared__ ColStage s_col[CHC];
+    __shared__ float s_row[ch_rows(TZB) + 1];
     backward_block<T, EPI, TZB, CHC>(g, __builtin_amdgcn_workgroup_id_x(), proj, out, out_z, sc, partials, nbx, nby, nbz, aux, s_pix,
-                                     s_col);
+                                     s_col, s_row);
 }
 
 static BwdPlan brick_plan(const GeoDev &g, int form)
@@ -198,14 +201,17 @@ static float shadow_cols(const GeoDev &g, int n)
 }
 static float shadow_rows(const GeoDev &g, int tz) { return 1.1f * (float)tz * g.vz * g.kv / g.sid + 3.0f; }
 
-// Wave form: the deepest brick whose shadow is expected to fit one chunk and that
-// leaves enough bricks, and as many view subsets as fill the chip.  Measured (us,
-// cube of n voxels, q detector pixels per voxel at the isocentre, depth 32 / 16 / 8 / 4):
-// n 128, q 0.7: 287 / 338 / 413 / -; n 192, q 1.25: - / 1405 / 1493 / 2800;
-// n 192, q 1.6: - / - / 2125 / 2480; n 192, q 2.2: - / - / 4700 / 4258; n 64, q 2: - / - / 96 / 110.
-// Subsets 4 / 8 / 16: 64^3, q 0.7 (256 bricks): - / 49 / 35; 128^3, q 1.25 (2048): 702 / 680 / 703;
-// 192^3, q 1.25 (6912): 1405 / 1566 / 1592.
-static BwdPlan wave_plan(const GeoDev &g)
+// Wave form: the deepest brick whose shadow is expected to fit one chunk (or nearly so:
+// a second chunk now and then costs less than shallower bricks) and that leaves enough
+// bricks, and as many view subsets as fill the chip.  Measured (us, cube of n voxels, q
+// detector pixels per voxel at the isocentre, depth 32 / 16 / 8 / 4):
+// n 128, q 0.7: 287 / 338 / 413 / -; n 192, q 1.25: 2179 / 1129 / 1487 / 1984;
+// n 192, q 1.6: 4288 / 1673 / 1729 / 2235; n 256, q 1.6: 24322 / 9777 / 10485 / 14020;
+// n 192, q 2.2: - / 4389 / 2929 / 3364; n 192, q 3.2: - / 12665 / 8635 / 7236; n 64, q 1.6:
+// - / 118 / 81 / 94.  4 or 8 subsets: 2048 bricks (n 128, q 1.25) 668 / 543, 4096 (n 128,
+// q 2.2) 1444 / 1373, 6912 (n 192, q 1.25) 1175 / 1129, 16384 (n 256, q 1) 5685 / 5735, 31250
+// (n 400, q 1.25) 4759 / 4876.
+static BwdPlan wave_plan(const GeoDev &g, bool single)
 {
     BwdPlan p{};
     p.form = BWD_WAVES;
@@ -216,34 +222,38 @@ static BwdPlan wave_plan(const GeoDev &g)
         const float records = cols * (shadow_rows(g, p.tz) + 1.0f);
         p.nbz = (g.nz + p.tz - 1) / p.tz;
         p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
-        // a second chunk now and then costs less than bricks of 4
-        if (records <= (p.tz == 8 ? 1.3f : 1.0f) * (float)W_CAP && p.nblocks >= (p.tz == 32 ? 1024 : 192)) break;
+        const float over = p.tz == 8 ? 1.3f : (p.tz == 16 && single ? 1.1f : 1.0f);
+        if (records <= over * (float)wave_cap(single && split_records<float>(p.tz)) && p.nblocks >= (p.tz == 32 ? 1024 : 192)) break;
     }
     p.nbz = (g.nz + p.tz - 1) / p.tz;
     p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
     // (bricks of 32: one subset per wavefront of the batched form, whose second set of
     // sums would not fit its registers)
-    p.sets = p.tz == 32 || p.nblocks > 2048 ? 4 : (p.nblocks > 512 ? 8 : 16);
+    p.sets = p.tz == 32 || p.nblocks > (single ? 8192 : 2048) ? 4 : (p.nblocks > 512 ? 8 : 16);
     return p;
 }
 
-// A single backprojection's form.  Workgroup bricks where there are enough of them
-// to fill the chip two and a half times over (six workgroups per compute unit)
-// and the shadow is expected to fit one staged chunk; wave form elsewhere.
-// Measured (us, wave form / 16-deep / 32-deep bricks; n and q as above):
-//   q 0.7:  n 192 657 / 788 / 694, n 256 1100 / 1013 / 982, n 400 2826 / 2429 / 2064
-//   q 1.25: n 192 1405 / 1672 / -, n 256 2398 / 2126 / 2700, n 400 5775 / 4821 / 6692
-//   q 1.6:  n 192 2124 / 2632 / -, n 256 3733 / 3488 / 6903, n 400 9219 / 7545 / 12683
-//   q 2.2:  n 256 7528 / 8673 / -, n 400 19068 / 19626 / 30666
-static BwdPlan plan(const GeoDev &g, bool deep_allowed)
+// A single backprojection's form (single: with single-precision accumulation).  Deep
+// workgroup bricks where there are enough of them to fill the chip and their shadow
+// is expected to fit one staged chunk; 16-deep ones where the same holds and the
+// volume is so large that the wave form's own staging of every 8 x 8 columns costs more
+// than the workgroup's barriers; wave form elsewhere.
+// Measured (us, wave form / 16-deep / 32-deep bricks; n and q as above, n 256 with 90
+// views at q 0.7 and 300 elsewhere):
+//   q 0.7:  n 192 657 / 788 / 694, n 256 1100 / 1013 / 982, n 400 2826 / 2429 / 1835
+//   q 1:    n 256 5686 / 5955 / 7188, n 400 3884 / 3898 / 3817
+//   q 1.25: n 192 1129 / 1555 / 2276, n 256 6627 / 6882 / 12587, n 400 4759 / 4602 / 6751
+//   q 1.6:  n 256 9777 / 10723 / -, n 320 3679 / 3806 / -, n 400 7145 / 6823 / 12867
+//   q 2.2:  n 256 17924 / 27169 / -, n 400 12890 / 17528 / -
+static BwdPlan plan(const GeoDev &g, bool deep_allowed, bool single = true)
 {
     const BwdPlan deep = brick_plan(g, BWD_DEEP), shallow = brick_plan(g, BWD_BRICKS);
     const float cols = shadow_cols(g, BX);
     if (deep_allowed && deep.nblocks >= 2048 && cols <= (float)ch_cols(TZ_DEEP) &&
         shadow_rows(g, TZ_DEEP) <= (float)ch_rows(TZ_DEEP))
         return deep;
-    if (shallow.nblocks >= 4096 && cols <= (float)ch_cols(TZ) && shadow_rows(g, TZ) <= (float)ch_rows(TZ)) return shallow;
-    return wave_plan(g);
+    if (shallow.nblocks >= (single ? 12288 : 4096) && cols <= (float)ch_cols(TZ) && shadow_rows(g, TZ) <= (float)ch_rows(TZ)) return shallow;
+    return wave_plan(g, single);
 }
 
 BwdPlan backward_plan(const GeoDev &g) { return plan(g, true); }
@@ -257,28 +267,34 @@ BwdPlan backward_plan_variant(const GeoDev &g, int variant)
 // partial sums) is that of kct_cgls_solve.
 int backward_default_variant(const GeoDev &g) { return backward_plan(g).form == BWD_DEEP ? BWD_VDEEP : BWD_VSHALLOW; }
 
-constexpr int BRICK_LDS_COLS = 48;  // the widest chunk of the workgroup bricks
-constexpr int BRICK_LDS_RECORDS =
-    ((ch_rows(TZ_DEEP) + 1) * ch_cols(TZ_DEEP) > (ch_rows(TZ) + 1) * ch_cols(TZ) ? (ch_rows(TZ_DEEP) + 1) * ch_cols(TZ_DEEP)
-                                                                                  : (ch_rows(TZ) + 1) * ch_cols(TZ)) +
-    NH - 1;
-constexpr size_t BATCH_LDS = wave_lds_bytes(W_GROUPS) > BRICK_LDS_RECORDS * sizeof(PixStage<float>) + BRICK_LDS_COLS * sizeof(ColStage)
-                                 ? wave_lds_bytes(W_GROUPS)
-                                 : BRICK_LDS_RECORDS * sizeof(PixStage<float>) + BRICK_LDS_COLS * sizeof(ColStage);
+// LDS of a workgroup brick in the batched form: records, columns, row factors.
+constexpr size_t brick_lds_bytes(int tz)
+{
+    const size_t rec = split_records<float>(tz) ? sizeof(PixStage<float, true>) : sizeof(PixStage<float, false>);
+    return ((ch_rows(tz) + 1) * ch_cols(tz) + NH - 1) * rec + ch_cols(tz) * sizeof(ColStage) + (ch_rows(tz) + 1) * sizeof(float);
+}
+constexpr size_t lds_max(size_t a, size_t b) { return a > b ? a : b; }
+constexpr size_t BATCH_LDS = lds_max(lds_max(wave_lds_bytes<float, true>(W_GROUPS), wave_lds_bytes<float, false>(W_GROUPS)),
+                                     lds_max(brick_lds_bytes(TZ), brick_lds_bytes(TZ_DEEP)));
+
+template <int TZB>
+__device__ __forceinline__ void batch_brick(const BatchInst *bi, const BwdPlan &p, int lw, char *lds)
+{
+    using Rec = PixStage<float, split_records<float>(TZB)>;
+    Rec *s_pix = reinterpret_cast<Rec *>(lds);
+    ColStage *s_col = reinterpret_cast<ColStage *>(s_pix + (ch_rows(TZB) + 1) * ch_cols(TZB) + NH - 1);
+    float *s_row = reinterpret_cast<float *>(s_col + ch_cols(TZB));
+    backward_block<float, BWD_NORM, TZB, ch_cols(TZB)>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
+                                                       p.nbz, nullptr, s_pix, s_col, s_row);
+}
 
 // One tile (brick) of instance bi's r = A^T e with |r|^2 partials.  Wave form: the
 // four wavefronts take the view subsets of the single solve in turns.
 __device__ __forceinline__ void batch_backward_tile(const BatchInst *bi, int lw, char *lds)
 {
     const BwdPlan p = bi->bwd;
-    PixStage<float> *s_pix = reinterpret_cast<PixStage<float> *>(lds);
-    ColStage *s_col = reinterpret_cast<ColStage *>(s_pix + BRICK_LDS_RECORDS);
-    if (p.form == BWD_DEEP)
-        backward_block<float, BWD_NORM, TZ_DEEP, ch_cols(TZ_DEEP)>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part,
-                                                                   p.nbx, p.nby, p.nbz, nullptr, s_pix, s_col);
-    else if (p.form == BWD_BRICKS)
-        backward_block<float, BWD_NORM, TZ, ch_cols(TZ)>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
-                                                         p.nbz, nullptr, s_pix, s_col);
+    if (p.form == BWD_DEEP) batch_brick<TZ_DEEP>(bi, p, lw, lds);
+    else if (p.form == BWD_BRICKS) batch_brick<TZ>(bi, p, lw, lds);
     else if (p.tz == 32)
         backward_wave_block<float, BWD_NORM, 32, false>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
                                                         p.nbz, nullptr, W_GROUPS, 1, lds);
@@ -364,7 +380,7 @@ hipError_t launch_backward(const GeoDev &g, const T *proj, T *out, T *out_z, int
                            double *partials, const int *skip, hipStream_t st, const float *aux)
 {
     if (g.projector == KCT_PROJECTOR_TT) return launch_backward_tt<T>(g, proj, out, out_z, epi, sc, partials, skip, st, aux);
-    const BwdPlan p = backward_plan(g);
+    const BwdPlan p = plan(g, true, !std::is_same<T, double>::value);
     if (p.form == BWD_WAVES) return launch_backward_waves<T>(g, p, proj, out, out_z, epi, sc, partials, skip, st, aux);
     if constexpr (std::is_same<T, double>::value) {  // double storage: plain backprojection only
         if (epi != BWD_PLAIN) return hipErrorInvalidValue;

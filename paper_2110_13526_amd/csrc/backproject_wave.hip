@@ -26,7 +26,8 @@ static void launch_waves(const GeoDev &g, const BwdPlan &p, const T *proj, T *ou
                          double *partials, const int *skip, const float *aux, hipStream_t st)
 {
     const dim3 grid((unsigned)p.nblocks), block(64u * (unsigned)p.sets);
-    const unsigned lds = (unsigned)wave_lds_bytes(p.sets);
+    using A = acc_t<T>;
+    const unsigned lds = (unsigned)(split_records<A>(p.tz) ? wave_lds_bytes<A, true>(p.sets) : wave_lds_bytes<A, false>(p.sets));
     switch (p.tz) {
     case 32:
         hipLaunchKernelGGL((k_backward_waves<T, EPI, 32>), grid, block, lds, st, g, proj, out, out_z, sc, partials, skip,

@@ -7,8 +7,8 @@
 // workgroup
 //   1. bounds the brick's shadow on the detector (the eight projected corners),
 //   2. stages, for every pixel of the shadow, the ray's z-parameters and its
-//      value multiplied by the ray length factor L in LDS (one 16-byte record
-//      per pixel), and the per-column in-plane ray parameters,
+//      value multiplied by the ray length factor L in LDS (one record per
+//      pixel), and the per-column in-plane ray parameters,
 //   3. lets each lane gather: the interval of detector columns whose
 //      rays can cross its voxel column, the in-plane xi-interval of each of those
 //      columns (shared by the TZ voxels), per voxel the candidate rows from
@@ -17,16 +17,18 @@
 // The shadow is staged in chunks of at most ch_cols(TZB) x ch_rows(TZB) pixels, so any
 // geometry works; typical bricks need one chunk.
 //
-// What bounds it: VALU issue (1.2 wave-instructions per CU-cycle at 512^3 x 720,
-// 616 x 480 detector, the most its mix of operations reaches), so its time
-// follows its instruction count per voxel and view.  At that size one launch
-// takes 65.4 ms (74.9 ms with a test of every voxel against the brick's top, a
+// What bounds it: at 512^3 x 720, 616 x 480 detector (32-deep bricks) the LDS unit is busy
+// for 0.72 of the cycles (a record's read takes it 8 cycles per wavefront) beside 0.92 VALU
+// wave-instructions per CU-cycle, of the 1.2 that its mix of operations reaches alone.
+// One launch takes 63.7 ms (74.9 ms with a test of every voxel against the brick's top, a
 // search for the first and last hit column, an integer clamp made of compares
-// and selects, and the ray parameters of a column read again for each of its pixels);
-// 63.7 ms with the second row's test skipped where no voxel of the wavefront has one;
-// 256^3 x 360, 384 x 384 detector: 8.7 ms (10.5 ms).  EARLY (all but the 32-deep workgroup
-// bricks, whose registers it would spill): 192^3 x 180 in the wave form 1.97 -> 1.88 ms,
-// 128^3 x 720 1.48 -> 1.38, 256^3 x 90 at 0.7 pixels per voxel 0.98 -> 0.88 (both steps).
+// and selects, and the ray parameters of a column read again for each of its pixels;
+// 65.4 ms before the second row's test was skipped where no voxel of the wavefront has
+// one).  The forms for wider shadows read more records per voxel; split records
+// (split_records) halve those reads: 256^3 x 360, 384 x 384 detector 10.5 -> 8.7 -> 8.2 ms.
+// EARLY (all but the 32-deep workgroup bricks, whose registers it would spill): 192^3 x 180
+// in the wave form 1.97 -> 1.88 ms, 128^3 x 720 1.48 -> 1.38, 256^3 x 90 at 0.7 pixels per
+// voxel 0.98 -> 0.88 (both steps).
 #pragma once
 
 #pragma clang fp contract(off)
@@ -40,8 +42,7 @@ namespace kct {
 
 constexpr int BX = 16, BY = 16, TZ = 16;   // brick; BX * BY = 256 lanes
 constexpr int TZ_DEEP = 32;                // deeper bricks for large volumes (more voxels share a lane's setup)
-constexpr int CH_ROWS_MAX = 36;            // staged shadow chunk: rows and columns by brick depth
-// Columns of the staged chunk: 32 for the deep bricks of large volumes (whose
+// Rows and columns of the staged chunk by brick depth.  Columns: 32 for the deep bricks of large volumes (whose
 // shadows are at most about 28 x 28 pixels at typical magnifications; the
 // smaller chunk measured faster there), 48 for the shallow bricks, whose
 // volumes tend to have coarse voxels and wide shadows.
@@ -52,6 +53,7 @@ constexpr int NH = 2;                      // detector columns held in registers
 struct ColStage {  // per staged detector column: in-plane ray parameters
     float eta_c, inv_a, tcv;  // ColParam's; columns parallel to the eta planes staged as below (PAR_INV)
     float gz;      // d T / d xi with T = (segment fraction) / vz
+    float kz;      // ColParam's: d xi / d zeta per unit of a row's factor
 };
 
 // Rays parallel to a family of planes are staged as if they crossed them at a
@@ -64,19 +66,37 @@ struct ColStage {  // per staged detector column: in-plane ray parameters
 // columns therefore need no parallel case.
 constexpr float PAR_INV = 1.0e30f;
 
-// Per staged pixel.  czr is d xi / d zeta of the pixel's ray and nzc its
-// zeta_offset (from zeta at xi = 0: zeta_centre and zeta_inv_slope of its row
-// and column); rows whose rays are parallel to the z-planes (qz == 0) staged
-// as above.
-template <typename A> struct PixStage {
+// Per staged pixel: its ray's zeta_offset nzc (from zeta at xi = 0: zeta_centre and
+// zeta_inv_slope of its row and column; rows whose rays are parallel to the z-planes
+// (qz == 0) staged as above), its d xi / d zeta czr, and L * e in the accumulator precision.
+// SPLIT: without czr, which is then the product of the row's staged factor and the
+// column's (zeta_inv_slope, the same bits).  A record of 16 bytes takes the LDS 8 cycles
+// per wavefront, one of 8 bytes 4 and a row factor 2, for one multiplication and
+// one address more.  See split_records.
+template <typename A, bool SPLIT> struct PixStage {
     float nzc, czr;
-    A le;          // L * e, in the accumulator precision
+    A le;
     float pad;
 };
-template <> struct PixStage<double> {  // the same 16 bytes with a double L * e
+template <> struct PixStage<double, false> {
     float nzc, czr;
     double le;
 };
+template <> struct PixStage<float, true> {
+    float nzc, le;
+};
+
+// Whether bricks tzb voxels deep are staged in split records.  The deepest are chosen
+// where a voxel spans less than about a pixel, and are bound by VALU issue (512^3 x 720,
+// full / split: 63.7 / 64.3 ms; 400^3 x 60 at 0.7 pixels per voxel 1.83 / 1.93; 128^3 x 720
+// 1.39 / 1.43); the others read more records per voxel and the LDS was what bound them
+// (192^3 x 180, 256 x 256 detector: 1.89 / 1.63 ms; 192^3 x 120 at 1.6 and 2.2 pixels per
+// voxel 2.12 / 1.68 and 4.13 / 3.36; 256^3 x 360 8.64 / 8.21; 64^3 x 90 96 / 85 us).
+// In double precision a record is 16 bytes either way.
+template <typename A> __host__ __device__ constexpr bool split_records(int tzb)
+{
+    return std::is_same<A, float>::value && tzb < TZ_DEEP;
+}
 
 // 1 / x to within a few ulp (bounds only).
 __host__ __device__ __forceinline__ float rcp_approx(float x)
@@ -153,41 +173,68 @@ __host__ __device__ __forceinline__ ColStage stage_column(const GeoDev &g, int d
     cs.inv_a = par ? PAR_INV : cp.inv_a;
     cs.tcv = cp.tcv;
     cs.gz = cp.gp * g.inv_vz;
+    cs.kz = cp.kz;
     return cs;
 }
 
-// One staged record, read as a whole (one 128-bit LDS read).
-template <typename A> __host__ __device__ __forceinline__ PixStage<A> load_pix(const PixStage<A> *p) { return *p; }
-template <> __host__ __device__ __forceinline__ PixStage<float> load_pix<float>(const PixStage<float> *p)
+// One staged record, read as a whole (one LDS read).
+template <typename A, bool SPLIT> __host__ __device__ __forceinline__ PixStage<A, SPLIT> load_pix(const PixStage<A, SPLIT> *p)
+{
+    return *p;
+}
+template <> __host__ __device__ __forceinline__ PixStage<float, false> load_pix<float, false>(const PixStage<float, false> *p)
 {
     const float4 v = *reinterpret_cast<const float4 *>(p);
-    PixStage<float> r;
-    r.nzc = v.x;
-    r.czr = v.y;
-    r.le = v.z;
-    r.pad = v.w;
-    return r;
+    return {v.x, v.y, v.z, v.w};
+}
+template <> __host__ __device__ __forceinline__ PixStage<float, true> load_pix<float, true>(const PixStage<float, true> *p)
+{
+    const float2 v = *reinterpret_cast<const float2 *>(p);
+    return {v.x, v.y};
 }
 
 // One staged record, read where this stands: a volatile access, which the compiler
 // does not move down to the record's first use (on the host a plain read).
-template <typename A> __host__ __device__ __forceinline__ PixStage<A> early_pix(const PixStage<A> *p)
+template <typename A, bool SPLIT> __host__ __device__ __forceinline__ PixStage<A, SPLIT> early_pix(const PixStage<A, SPLIT> *p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     if constexpr (std::is_same<A, float>::value) {
-        typedef float record __attribute__((ext_vector_type(3)));
+        typedef float record __attribute__((ext_vector_type(SPLIT ? 2 : 3)));
         typedef const volatile __attribute__((address_space(3))) record *lds_record;
-        typedef const __attribute__((address_space(3))) PixStage<A> *lds_pix;
+        typedef const __attribute__((address_space(3))) PixStage<A, SPLIT> *lds_pix;
         const record v = *(lds_record)(lds_pix)p;
-        PixStage<A> r;
+        PixStage<A, SPLIT> r{};
         r.nzc = v.x;
-        r.czr = v.y;
-        r.le = v.z;
-        r.pad = 0.0f;
+        if constexpr (SPLIT) {
+            r.le = v.y;
+        } else {
+            r.czr = v.y;
+            r.le = v.z;
+        }
         return r;
     }
 #endif
     return *p;
+}
+
+// A row's staged factor, read likewise.
+__host__ __device__ __forceinline__ float early_row(const float *p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef const volatile __attribute__((address_space(3))) float *lds_early;
+    typedef const __attribute__((address_space(3))) float *lds_float;
+    return *(lds_early)(lds_float)p;
+#else
+    return *p;
+#endif
+}
+
+// d xi / d zeta of a staged ray in a row of factor `row` and a column of factor kz.
+template <typename A, bool SPLIT>
+__host__ __device__ __forceinline__ float pix_slope(const PixStage<A, SPLIT> &p, float row, float kz)
+{
+    if constexpr (SPLIT) return zeta_inv_slope(row, kz);
+    else return p.czr;
 }
 
 // The candidate of one record for one voxel with z-planes mb and mb1, over the
@@ -197,10 +244,10 @@ template <typename A> __host__ __device__ __forceinline__ PixStage<A> early_pix(
 // operands) and exactly 0 elsewhere (both medians clamp to the same end of
 // [min, max], or hi = lo): a candidate that misses adds 0 * le = 0 (le is finite)
 // and leaves the sum as it is.
-template <typename A, bool SQ>
-__host__ __device__ __forceinline__ A add_pix(const PixStage<A> &p, float lo, float hi, float mb, float mb1, A a)
+template <typename A, bool SQ, bool SPLIT>
+__host__ __device__ __forceinline__ A add_pix(const PixStage<A, SPLIT> &p, float czr, float lo, float hi, float mb, float mb1, A a)
 {
-    const float b0 = zeta_cross(mb, p.nzc, p.czr), b1 = zeta_cross(mb1, p.nzc, p.czr);
+    const float b0 = zeta_cross(mb, p.nzc, czr), b1 = zeta_cross(mb1, p.nzc, czr);
     const float w = med3f(hi, b0, b1) - med3f(lo, b0, b1);
     return fma_acc(SQ ? w * w : w, p.le, a);
 }
@@ -211,28 +258,29 @@ __host__ __device__ __forceinline__ A add_pix(const PixStage<A> &p, float lo, fl
 // mb1.  Returns a + sum of w * (L e) (w^2 * le when SQ).  All NH records are
 // read before the first is used; the staging buffer holds a spare record past
 // its last, so prow + NH - 1 is always inside it.
-template <typename A, bool SQ, int NH>
-__host__ __device__ __forceinline__ A add_row(const PixStage<A> *prow, int nh, const float (&lo)[NH],
-                                              const float (&hi)[NH], float mb, float mb1, A a)
+template <typename A, bool SQ, int NH, bool SPLIT>
+__host__ __device__ __forceinline__ A add_row(const PixStage<A, SPLIT> *prow, float row, int nh, const float (&kz)[NH],
+                                              const float (&lo)[NH], const float (&hi)[NH], float mb, float mb1, A a)
 {
-    PixStage<A> p[NH];
+    PixStage<A, SPLIT> p[NH];
 #pragma unroll
     for (int h = 0; h < NH; ++h) p[h] = load_pix(prow + h);
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-        if (h == 0 || h < nh) a = add_pix<A, SQ>(p[h], lo[h], hi[h], mb, mb1, a);
+        if (h == 0 || h < nh) a = add_pix<A, SQ>(p[h], pix_slope(p[h], row, kz[h]), lo[h], hi[h], mb, mb1, a);
     }
     return a;
 }
 
 // The staged record of the pixel with column parameters cp, row parameters rp
 // and value ev (parallel rows as above).  SQ: L^2 in the place of L * ev.
-template <typename A, bool SQ>
-__host__ __device__ __forceinline__ PixStage<A> stage_pixel(const ColParam &cp, const RowParam &rp, A ev)
+template <typename A, bool SQ, bool SPLIT>
+__host__ __device__ __forceinline__ PixStage<A, SPLIT> stage_pixel(const ColParam &cp, const RowParam &rp, A ev)
 {
-    PixStage<A> ps;
-    ps.czr = zeta_inv_slope(rp.s_inv, cp.kz);
-    ps.nzc = zeta_offset(zeta_centre(rp.qz, cp.tcv, -rp.s_off), ps.czr);
+    PixStage<A, SPLIT> ps;
+    const float czr = zeta_inv_slope(rp.s_inv, cp.kz);
+    if constexpr (!SPLIT) ps.czr = czr;
+    ps.nzc = zeta_offset(zeta_centre(rp.qz, cp.tcv, -rp.s_off), czr);
     const A L = (A)ray_length_per_xi(cp.lxy2, rp.qz, cp.gp);
     ps.le = SQ ? L * L : L * ev;
     return ps;
@@ -240,15 +288,15 @@ __host__ __device__ __forceinline__ PixStage<A> stage_pixel(const ColParam &cp, 
 
 // A record of weight 0 for any voxel, made where it is stored (an empty asm keeps
 // the compiler from hoisting it out of the view loop and spilling it).
-template <typename A> __host__ __device__ __forceinline__ PixStage<A> zero_pixel()
+template <typename A, bool SPLIT> __host__ __device__ __forceinline__ PixStage<A, SPLIT> zero_pixel()
 {
     float zero = 0.0f;
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("" : "+v"(zero));
 #endif
-    PixStage<A> z{};
+    PixStage<A, SPLIT> z{};
     z.nzc = zero;
-    z.czr = zero;
+    if constexpr (!SPLIT) z.czr = zero;
     z.le = (A)zero;
     return z;
 }
@@ -258,23 +306,37 @@ template <typename A> __host__ __device__ __forceinline__ PixStage<A> zero_pixel
 // the GPU one instruction on the 32-bit LDS address: a shift-and-add when a
 // row of records spans a constant power of two bytes, else a 24-bit
 // multiply-and-add (row and row length are far below 2^23).
-template <typename A, int CHC>
-__host__ __device__ __forceinline__ const PixStage<A> *row_record(const PixStage<A> *pg, int r, int stride)
+template <int CHC, typename A, bool SPLIT>
+__host__ __device__ __forceinline__ const PixStage<A, SPLIT> *row_record(const PixStage<A, SPLIT> *pg, int r, int stride)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    constexpr unsigned row_bytes = CHC * sizeof(PixStage<A>);
+    constexpr unsigned row_bytes = CHC * sizeof(PixStage<A, SPLIT>);
     if constexpr ((row_bytes & (row_bytes - 1)) == 0) {
-        typedef const __attribute__((address_space(3))) PixStage<A> *lds_rec;
+        typedef const __attribute__((address_space(3))) PixStage<A, SPLIT> *lds_rec;
         const unsigned base = (unsigned)(size_t)(lds_rec)pg;
         unsigned addr;
         if constexpr (CHC != 0)
             asm("v_lshl_add_u32 %0, %1, %3, %2" : "=v"(addr) : "v"(r), "v"(base), "i"(__builtin_ctz(row_bytes)));
         else
-            asm("v_mad_i32_i24 %0, %1, %3, %2" : "=v"(addr) : "v"(r), "v"(base), "s"(stride * (int)sizeof(PixStage<A>)));
-        return (const PixStage<A> *)(lds_rec)(size_t)addr;
+            asm("v_mad_i32_i24 %0, %1, %3, %2" : "=v"(addr) : "v"(r), "v"(base), "s"(stride * (int)sizeof(PixStage<A, SPLIT>)));
+        return (const PixStage<A, SPLIT> *)(lds_rec)(size_t)addr;
     }
 #endif
     return pg + r * (CHC != 0 ? CHC : stride);
+}
+
+// rg + r for a pointer rg into the LDS: one shift-and-add of the 32-bit address on the GPU.
+__host__ __device__ __forceinline__ const float *row_factor(const float *rg, int r)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef const __attribute__((address_space(3))) float *lds_float;
+    const unsigned base = (unsigned)(size_t)(lds_float)rg;
+    unsigned addr;
+    asm("v_lshl_add_u32 %0, %1, 2, %2" : "=v"(addr) : "v"(r), "s"(base));
+    return (const float *)(lds_float)(size_t)addr;
+#else
+    return rg + r;
+#endif
 }
 
 // Whether c holds in any lane of the wavefront: a scalar value on the GPU.
@@ -310,8 +372,9 @@ __host__ __device__ __forceinline__ int clamp_row(int v, int hi)
 // row staged after them, and a row that is not a candidate has weight exactly
 // 0 (the weights are exact).  Further rows, up to the last staged one, follow in a
 // loop.  pg + va * stride is the record of row va + 1 in the group's first column.
-template <typename A, bool SQ, int CHC, int NH, bool EARLY, int TZN>
-__host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int stride, int nh, const float (&lo)[NH],
+template <typename A, bool SQ, int CHC, int NH, bool EARLY, int TZN, bool SPLIT>
+__host__ __device__ __forceinline__ void voxel_rows(const PixStage<A, SPLIT> *pg, const float *rg, int stride, int nh,
+                                                    const float (&kz)[NH], const float (&lo)[NH],
                                                     const float (&hi)[NH], float mbz0, float l0, float sl,
                                                     float h0, float sh, int nrow, A (&acc)[TZN])
 {
@@ -331,41 +394,56 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int s
     // EARLY: the next voxel's first record is read before this voxel's arithmetic (its
     // latency is then covered; it takes four more registers)
     int va = clamp_row((int)floorf(l0), nrow - 1);
-    const PixStage<A> *prow = row_record<A, CHC>(pg, va, stride);
-    PixStage<A> rec{};
-    if constexpr (EARLY) rec = early_pix(prow);
+    const PixStage<A, SPLIT> *prow = row_record<CHC>(pg, va, stride);
+    PixStage<A, SPLIT> rec{};
+    float row = 0.0f;
+    if constexpr (EARLY) {
+        if constexpr (SPLIT) row = early_row(row_factor(rg, va));
+        rec = early_pix(prow);
+    }
 #pragma unroll
     for (int j = 0; j < TZN; ++j) {
         const float mb1 = mb + 1.0f;
         // candidate rows va + 1 .. vb + 1: floor(lo) + 1 is ceil(lo) except at an
         // integer lo, whose row lies 0.01 below the true bound and is rightly left out
         int va_next = va;
-        const PixStage<A> *prow_next = prow;
-        PixStage<A> rec_next = rec;
+        const PixStage<A, SPLIT> *prow_next = prow;
+        PixStage<A, SPLIT> rec_next = rec;
+        float row_next = row;
         if constexpr (EARLY) {
             if (j + 1 < TZN) {
                 va_next = clamp_row((int)floorf(__builtin_fmaf((float)(j + 1), sl, l0)), nrow - 1);
-                prow_next = row_record<A, CHC>(pg, va_next, stride);
+                prow_next = row_record<CHC>(pg, va_next, stride);
+                if constexpr (SPLIT) row_next = early_row(row_factor(rg, va_next));
                 rec_next = early_pix(prow_next);
             }
-            acc[j] = add_pix<A, SQ>(rec, lo[0], hi[0], mb, mb1, acc[j]);
+            acc[j] = add_pix<A, SQ>(rec, pix_slope(rec, row, kz[0]), lo[0], hi[0], mb, mb1, acc[j]);
 #pragma unroll
-            for (int h = 1; h < NH; ++h)
-                if (h < nh) acc[j] = add_pix<A, SQ>(load_pix(prow + h), lo[h], hi[h], mb, mb1, acc[j]);
+            for (int h = 1; h < NH; ++h) {
+                if (h < nh) {
+                    const PixStage<A, SPLIT> p = load_pix(prow + h);
+                    acc[j] = add_pix<A, SQ>(p, pix_slope(p, row, kz[h]), lo[h], hi[h], mb, mb1, acc[j]);
+                }
+            }
         } else {
             if (j > 0) {
                 va = clamp_row((int)floorf(__builtin_fmaf((float)j, sl, l0)), nrow - 1);
-                prow = row_record<A, CHC>(pg, va, stride);
+                prow = row_record<CHC>(pg, va, stride);
             }
-            acc[j] = add_row<A, SQ, NH>(prow, nh, lo, hi, mb, mb1, acc[j]);
+            if constexpr (SPLIT) row = *row_factor(rg, va);
+            acc[j] = add_row<A, SQ, NH>(prow, row, nh, kz, lo, hi, mb, mb1, acc[j]);
         }
         if (more) {
             int vb = (int)floorf(__builtin_fmaf((float)(j + 1), sh, h0));
             vb = vb > nrow - 2 ? nrow - 2 : vb;
             A a = acc[j];
+            const float *prf = rg;
+            float further = 0.0f;
+            if constexpr (SPLIT) prf = row_factor(rg, va);
             for (int v = va; v < vb; ++v) {
                 prow += CHC != 0 ? CHC : stride;
-                a = add_row<A, SQ, NH>(prow, nh, lo, hi, mb, mb1, a);
+                if constexpr (SPLIT) further = *++prf;
+                a = add_row<A, SQ, NH>(prow, further, nh, kz, lo, hi, mb, mb1, a);
             }
             acc[j] = a;
         }
@@ -373,6 +451,7 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int s
             va = va_next;
             prow = prow_next;
             rec = rec_next;
+            row = row_next;
         }
         mb = mb1;
     }
@@ -385,9 +464,10 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A> *pg, int s
 // (weight 0 for any voxel).  NH columns are taken at once.
 // SQ: accumulate w_ij^2 * le instead of w_ij * le (with le = L^2 this sums the
 // squared weights, the diagonal of A^T A).
-template <typename A, bool SQ, int CHC, int NH, bool EARLY, int TZN>
+template <typename A, bool SQ, int CHC, int NH, bool EARLY, int TZN, bool SPLIT>
 __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const ViewParam &vp, int ix, int iy, int iz0,
-                                                      const PixStage<A> *s_pix, const ColStage *s_col, int cu0,
+                                                      const PixStage<A, SPLIT> *s_pix, const ColStage *s_col,
+                                                      const float *s_row, int cu0,
                                                       int ncol, int cv0, int nrow, A (&acc)[TZN], int stride = CHC)
 {
     int ixi, ieta;
@@ -412,12 +492,13 @@ __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const Vie
         // xi-intervals of up to NH columns, and the range of T = tcv + xi gz over
         // those that are hit (a ray of height qz is at height qz T above the source plane)
         const int nh = ub - c0 + 1 < NH ? ub - c0 + 1 : NH;
-        float lo[NH], hi[NH];
+        float lo[NH], hi[NH], kz[NH];
         float tmin = INFINITY, tmax = 0.0f;
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
             const int c = h < nh ? c0 + h : c0;
             const ColStage cs = s_col[c - cu0];
+            kz[h] = cs.kz;
             column_interval(cs, lo_xi, ieta, heta, lo[h], hi[h]);
             if (h < nh && hi[h] > lo[h]) {
                 const float T1 = __builtin_fmaf(lo[h], cs.gz, cs.tcv), T2 = __builtin_fmaf(hi[h], cs.gz, cs.tcv);
@@ -443,8 +524,8 @@ __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const Vie
         const float sl = (fminf(b1, b2) - fminf(a1, a2)) * (1.0f / TZN);
         const float sh = (fmaxf(b1, b2) - fmaxf(a1, a2)) * (1.0f / TZN);
         const float l0 = fminf(a1, a2) + vofs_lo, h0 = fmaxf(a1, a2) + vofs_hi;
-        const PixStage<A> *pg = s_pix + ((c0 - cu0) + (CHC != 0 ? CHC : stride));  // row va + 1 at pg + va * stride
-        voxel_rows<A, SQ, CHC, NH, EARLY, TZN>(pg, stride, nh, lo, hi, mbz0, l0, sl, h0, sh, nrow, acc);
+        const PixStage<A, SPLIT> *pg = s_pix + ((c0 - cu0) + (CHC != 0 ? CHC : stride));  // row va + 1 at pg + va * stride
+        voxel_rows<A, SQ, CHC, NH, EARLY>(pg, s_row + 1, stride, nh, kz, lo, hi, mbz0, l0, sl, h0, sh, nrow, acc);
     }
 }
 

@@ -9,12 +9,15 @@
 // follows the shadow (so that one view's shadow is one staged chunk also where
 // a voxel spans several pixels), and the views are dealt to 4, 8 or 16 subsets.
 //
-// Bounded by VALU issue as the other form, at about 1.0 wave-instruction per
-// CU-cycle; a quarter to a third of its instructions stage the shadow.  Measured
-// (one backprojection, 16 x 16 x 16 workgroup bricks -> this form): 64^3 x 90 views,
-// 96 x 96 detector 1260 -> 98 us; 96^3 x 186, 218 x 218 4170 -> 872 us; 64^3 x 199,
-// 274 x 274 (four pixels per voxel) 22.4 -> 1.45 ms; 128^3 x 720, 154 x 120
-// 3.06 -> 1.39 ms; 192^3 x 180, 256 x 256 2.38 -> 1.88 ms.
+// Bounded by VALU issue and, where a voxel spans more than a pixel, by the LDS reads of
+// the records; a quarter to a third of its instructions stage the shadow.  Bricks up
+// to 16 deep are staged in split records (kct_gather.h), which let a chunk hold 640 of
+// them in less LDS than 448 whole ones.  Measured (one backprojection, 16 x 16 x 16
+// workgroup bricks -> this form with whole records -> split): 64^3 x 90 views, 96 x 96
+// detector 1260 -> 96 -> 87 us; 96^3 x 186, 218 x 218 4170 -> 839 -> 640 us; 64^3 x 199,
+// 274 x 274 (four pixels per voxel) 22.4 -> 1.42 -> 1.06 ms; 192^3 x 180, 256 x 256
+// 2.38 -> 1.89 -> 1.61 ms; 256^3 x 360, 384 x 384 10.5 -> 8.6 (bricks) -> 8.2 ms; whole
+// records: 128^3 x 720, 154 x 120 3.06 -> 1.39 ms.
 #pragma once
 
 #include "kct_epilogue.h"
@@ -26,8 +29,12 @@ namespace kct {
 
 constexpr int WX = 8, WY = 8;    // voxel columns of a brick: one per lane
 constexpr int W_GROUPS = 4;      // the view subsets are added within groups, then the groups
-constexpr int W_CAP = 448;       // staged records of a chunk, its zero row included
-constexpr int W_COLS = 48;       // most columns of a chunk
+// Staged records of a chunk, its zero row included: room for the shadow of the deepest brick
+// against wavefronts per CU.  Measured (us, 576 / 640 / 720): 64^3 x 199, 274 x 274 1152 / 1098 / 1076;
+// 96^3 x 186 667 / 654 / 786; 192^3 x 180 1639 / 1646 / 1804; 192^3 x 120 at 2.2 pixels per voxel
+// 3080 / 2920 / 3126.
+constexpr int W_CAP = 640;
+constexpr int W_CAP_FULL = 448;  // the same for 16-byte records
 constexpr int W_NHMAX = 3;
 
 // Detector columns held in registers at once: shallow bricks are those of wide
@@ -36,15 +43,22 @@ __host__ __device__ constexpr int wave_nh(int tzb) { return tzb <= 8 ? 3 : 2; }
 
 constexpr int W_SUMS = 8;        // voxels per lane whose partial sums pass through LDS at once
 
+__host__ __device__ constexpr int wave_cap(bool split) { return split ? W_CAP : W_CAP_FULL; }
+// Most columns of a chunk (whole records: the deepest bricks, whose shadows are narrow; with
+// more, five workgroups of the batched form would not fit the LDS).
+__host__ __device__ constexpr int wave_cols(bool split) { return split ? 48 : 32; }
+__host__ __device__ constexpr int wave_rows(bool split) { return wave_cap(split) / 8; }  // most rows of a chunk, with its zero row
+
 // Records of one wavefront's staging region: the chunk and the spare records
 // that add_row may read.
-constexpr int W_REGION = W_CAP + W_NHMAX - 1;
+__host__ __device__ constexpr int wave_region(bool split) { return wave_cap(split) + W_NHMAX - 1; }
 
-// LDS bytes of a workgroup of `waves` wavefronts: staging regions, columns, and
-// the wavefronts' shares of the partial sum of squares.
-__host__ __device__ constexpr size_t wave_lds_bytes(int waves)
+// LDS bytes of a workgroup of `waves` wavefronts: staging regions, columns, row
+// factors, and the wavefronts' shares of the partial sum of squares.
+template <typename A, bool SPLIT> __host__ __device__ constexpr size_t wave_lds_bytes(int waves)
 {
-    return (size_t)waves * (W_REGION * sizeof(PixStage<float>) + W_COLS * sizeof(ColStage) + sizeof(double));
+    return (size_t)waves * (wave_region(SPLIT) * sizeof(PixStage<A, SPLIT>) + wave_cols(SPLIT) * sizeof(ColStage) + sizeof(double) +
+                            (SPLIT ? wave_rows(SPLIT) * sizeof(float) : 0));
 }
 
 // Orders one wavefront's LDS writes before its later reads, and its reads
@@ -79,16 +93,19 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
 {
     using A = acc_t<T>;
     constexpr bool SQ = EPI == BWD_DIAG || EPI == BWD_DIAG_INV;  // squared weights, e not read
-    constexpr int REGION = W_REGION, NCOL = wave_nh(TZB);
-    static_assert(sizeof(PixStage<A>) == sizeof(PixStage<float>) && sizeof(A) * W_SUMS * 64 <= sizeof(PixStage<A>) * REGION,
-                  "the LDS size holds for every accumulator, and the partial sums fit a staging region");
-    PixStage<A> *s_all = static_cast<PixStage<A> *>(lds);
+    constexpr bool SPLIT = split_records<A>(TZB);
+    constexpr int CAP = wave_cap(SPLIT), ROWS = wave_rows(SPLIT), REGION = wave_region(SPLIT), COLS = wave_cols(SPLIT),
+                  NCOL = wave_nh(TZB);
+    using Rec = PixStage<A, SPLIT>;
+    static_assert(sizeof(A) * W_SUMS * 64 <= sizeof(Rec) * REGION, "the partial sums fit a staging region");
+    Rec *s_all = static_cast<Rec *>(lds);
     ColStage *c_all = reinterpret_cast<ColStage *>(s_all + waves * REGION);
-    double *red = reinterpret_cast<double *>(c_all + waves * W_COLS);
+    double *red = reinterpret_cast<double *>(c_all + waves * COLS);
     const int wave = __builtin_amdgcn_readfirstlane((int)(__builtin_amdgcn_workitem_id_x() >> 6));
     const int lane = (int)(__builtin_amdgcn_workitem_id_x() & 63);
-    PixStage<A> *s_pix = s_all + wave * REGION;
-    ColStage *s_col = c_all + wave * W_COLS;
+    Rec *s_pix = s_all + wave * REGION;
+    ColStage *s_col = c_all + wave * COLS;
+    float *s_row = reinterpret_cast<float *>(red + waves) + wave * ROWS;  // used when SPLIT
 
     // XCD-aware brick assignment (see backproject.hip)
     constexpr int XCDS = 8;
@@ -138,16 +155,16 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
             }
             const T *pk = SQ ? proj : proj + (size_t)k * g.nv * g.nu;  // not read when SQ
             const ColParam *ck = g.cols + (size_t)k * g.nu;
-            // chunks of at most W_CAP records with the zero row, W_COLS columns, and
+            // chunks of at most CAP records with the zero row, COLS columns, and
             // rows that leave room for 8 columns; typical bricks need one chunk
-            constexpr int RMAX = W_CAP / 8 - 1;
+            constexpr int RMAX = ROWS - 1;
             for (int cv0 = v0; cv0 <= v1; cv0 += RMAX) {
                 const int nrow = v1 - cv0 + 1 < RMAX ? v1 - cv0 + 1 : RMAX;
-                int cmax = W_COLS;
-                if ((nrow + 1) * cmax > W_CAP) {
-                    // W_CAP / (nrow + 1) through a reciprocal, one less where that rounds up
-                    cmax = __builtin_amdgcn_readfirstlane((int)((float)W_CAP * __builtin_amdgcn_rcpf((float)(nrow + 1)) + 0.01f));
-                    if ((nrow + 1) * cmax > W_CAP) --cmax;
+                int cmax = COLS;
+                if ((nrow + 1) * cmax > CAP) {
+                    // CAP / (nrow + 1) through a reciprocal, one less where that rounds up
+                    cmax = __builtin_amdgcn_readfirstlane((int)((float)CAP * __builtin_amdgcn_rcpf((float)(nrow + 1)) + 0.01f));
+                    if ((nrow + 1) * cmax > CAP) --cmax;
                 }
                 for (int cu0 = u0; cu0 <= u1; cu0 += cmax) {
                     const int ncol = u1 - cu0 + 1 < cmax ? u1 - cu0 + 1 : cmax;
@@ -164,24 +181,26 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
                             if (r0 == 0) s_col[c] = stage_column(g, vp.dom, cp);
                             unsigned pix = ((unsigned)(cv0 + r0) * (unsigned)g.nu + (unsigned)(cu0 + c)) * (unsigned)sizeof(T);
                             unsigned row = (unsigned)(cv0 + r0) * (unsigned)sizeof(RowParam);
-                            PixStage<A> *rec = s_pix + (r0 * ncol + c);
+                            Rec *rec = s_pix + (r0 * ncol + c);
                             for (int r = r0; r < nrow; r += step) {
                                 const A ev = SQ ? (A)0 : to_acc(*byte_at<T>(pk, pix));
-                                *rec = stage_pixel<A, SQ>(cp, *byte_at<RowParam>(g.rows, row), ev);
+                                *rec = stage_pixel<A, SQ, SPLIT>(cp, *byte_at<RowParam>(g.rows, row), ev);
                                 pix += (unsigned)(step * g.nu) * (unsigned)sizeof(T);
                                 row += (unsigned)step * (unsigned)sizeof(RowParam);
                                 rec += step * ncol;
                             }
-                            if (r0 == 0) s_pix[nrow * ncol + c] = zero_pixel<A>();
+                            if (r0 == 0) s_pix[nrow * ncol + c] = zero_pixel<A, SPLIT>();
                         }
                     }
+                    if constexpr (SPLIT)
+                        for (int r = lane; r <= nrow; r += 64) s_row[r] = r < nrow ? g.rows[cv0 + r].s_inv : 0.0f;
                     wave_lds_order();
                     // 3. gather (the lane's column indices laundered per chunk: what is
                     //    derived from them is recomputed instead of kept through the view loop)
                     int ixv = ix, iyv = iy;
                     asm volatile("" : "+v"(ixv), "+v"(iyv));
                     if (valid)
-                        gather_chunk<A, SQ, 0, NCOL, true>(g, vp, ixv, iyv, iz0, s_pix, s_col, cu0, ncol, cv0, nrow, acc, ncol);
+                        gather_chunk<A, SQ, 0, NCOL, true>(g, vp, ixv, iyv, iz0, s_pix, s_col, s_row, cu0, ncol, cv0, nrow, acc, ncol);
                     wave_lds_order();
                 }
             }
