@@ -274,8 +274,11 @@ constexpr size_t brick_lds_bytes(int tz)
     return ((ch_rows(tz) + 1) * ch_cols(tz) + NH - 1) * rec + ch_cols(tz) * sizeof(ColStage) + (ch_rows(tz) + 1) * sizeof(float);
 }
 constexpr size_t lds_max(size_t a, size_t b) { return a > b ? a : b; }
-constexpr size_t BATCH_LDS = lds_max(lds_max(wave_lds_bytes<float, true>(W_GROUPS), wave_lds_bytes<float, false>(W_GROUPS)),
-                                     lds_max(brick_lds_bytes(TZ), brick_lds_bytes(TZ_DEEP)));
+constexpr size_t batch_lds_bytes(bool deep)
+{
+    return deep ? lds_max(wave_lds_bytes<float, false>(W_GROUPS), brick_lds_bytes(TZ_DEEP))
+                : lds_max(wave_lds_bytes<float, true>(W_GROUPS), brick_lds_bytes(TZ));
+}
 
 template <int TZB>
 __device__ __forceinline__ void batch_brick(const BatchInst *bi, const BwdPlan &p, int lw, char *lds)
@@ -290,14 +293,20 @@ __device__ __forceinline__ void batch_brick(const BatchInst *bi, const BwdPlan &
 
 // One tile (brick) of instance bi's r = A^T e with |r|^2 partials.  Wave form: the
 // four wavefronts take the view subsets of the single solve in turns.
+// DEEP: an instance whose bricks are 32 voxels deep, else one of the other forms.
+template <bool DEEP>
 __device__ __forceinline__ void batch_backward_tile(const BatchInst *bi, int lw, char *lds)
 {
     const BwdPlan p = bi->bwd;
-    if (p.form == BWD_DEEP) batch_brick<TZ_DEEP>(bi, p, lw, lds);
-    else if (p.form == BWD_BRICKS) batch_brick<TZ>(bi, p, lw, lds);
-    else if (p.tz == 32)
-        backward_wave_block<float, BWD_NORM, 32, false>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
-                                                        p.nbz, nullptr, W_GROUPS, 1, lds);
+    if constexpr (DEEP) {
+        if (p.form == BWD_DEEP)
+            batch_brick<TZ_DEEP>(bi, p, lw, lds);
+        else
+            backward_wave_block<float, BWD_NORM, 32, false>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx,
+                                                            p.nby, p.nbz, nullptr, W_GROUPS, 1, lds);
+        return;
+    }
+    if (p.form == BWD_BRICKS) batch_brick<TZ>(bi, p, lw, lds);
     else if (p.tz == 16)
         backward_wave_block<float, BWD_NORM, 16, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
                                                        p.nbz, nullptr, W_GROUPS, p.sets / W_GROUPS, lds);
@@ -311,15 +320,18 @@ __device__ __forceinline__ void batch_backward_tile(const BatchInst *bi, int lw,
 
 // Persistent batched r = A^T e: every workgroup takes items from the queue
 // until it is empty (see BatchInst); each item is up to BATCH_ITEM_BWD bricks
-// of one instance.
-__global__ __launch_bounds__(256, 5) void kp_backward(const BatchInst *__restrict__ B,
+// of one instance.  Two kernels, each with the instances of its forms: the 32-deep
+// bricks' sums need 96 registers and their records 31 KiB of LDS, the others' 80 and
+// 26, so the others run six workgroups per compute unit instead of five.
+template <bool DEEP>
+__global__ __launch_bounds__(256, DEEP ? 5 : 6) void kp_backward(const BatchInst *__restrict__ B,
                                                       const int64_t *__restrict__ off, int count,
                                                       BatchQueue *__restrict__ q)
 {
-    __shared__ __align__(16) char lds[BATCH_LDS];
+    __shared__ __align__(16) char lds[batch_lds_bytes(DEEP)];
     const int64_t total = off[count];
     for (;;) {
-        const int64_t item = batch_pop(q);
+        const int64_t item = batch_pop(q, total);
         if (item >= total) break;
         const int i = batch_find(off, count, item);
         const BatchInst *bi = B + i;
@@ -327,22 +339,25 @@ __global__ __launch_bounds__(256, 5) void kp_backward(const BatchInst *__restric
         const int64_t t0 = (item - off[i]) * BATCH_ITEM_BWD;
         const int64_t t1 = t0 + BATCH_ITEM_BWD < bi->nbk ? t0 + BATCH_ITEM_BWD : bi->nbk;
         for (int64_t t = t0; t < t1; ++t) {
-            batch_backward_tile(bi, (int)t, lds);
+            batch_backward_tile<DEEP>(bi, (int)t, lds);
             __syncthreads();  // the tile's block sum is read before the next tile writes it
         }
     }
     batch_exit(q);
 }
 
-hipError_t batch_backward_occupancy(int &per_cu)
+hipError_t batch_backward_occupancy(int &per_cu, int &per_cu_deep)
 {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kp_backward, 256, 0);
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kp_backward<false>, 256, 0);
+    return e != hipSuccess ? e : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_deep, kp_backward<true>, 256, 0);
 }
 
-hipError_t launch_batch_backward(const BatchInst *B, const int64_t *off, int count, BatchQueue *q, int grid,
-                                 hipStream_t st)
+// off and off_deep: the items of the instances of either kernel; q[0] and q[1] their queues.
+hipError_t launch_batch_backward(const BatchInst *B, const int64_t *off, const int64_t *off_deep, int count, BatchQueue *q,
+                                 int grid, int grid_deep, hipStream_t st)
 {
-    hipLaunchKernelGGL(kp_backward, dim3((unsigned)grid), dim3(256), 0, st, B, off, count, q);
+    hipLaunchKernelGGL(kp_backward<true>, dim3((unsigned)grid_deep), dim3(256), 0, st, B, off_deep, count, q + 1);
+    hipLaunchKernelGGL(kp_backward<false>, dim3((unsigned)grid), dim3(256), 0, st, B, off, count, q);
     return hipGetLastError();
 }
 

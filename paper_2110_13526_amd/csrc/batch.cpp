@@ -41,7 +41,7 @@ struct Batch {
     int device = -1;
     hipStream_t stream = nullptr;
     hipEvent_t ev = nullptr;
-    int grid_fwd = 0, grid_bwd = 0, grid_dir = 0;  // resident workgroups of the persistent steps
+    int grid_fwd = 0, grid_bwd = 0, grid_deep = 0, grid_dir = 0;  // resident workgroups of the persistent steps
     // the recorded iteration (valid for the workspace it was recorded with)
     hipGraphExec_t exec = nullptr;
     const void *exec_ws = nullptr;
@@ -78,7 +78,7 @@ struct BatchLayout {
     std::vector<size_t> part, d, dz, r, e, p;
 };
 
-constexpr int BATCH_QUEUES = 3;  // backprojection, direction update, forward projection
+constexpr int BATCH_QUEUES = 4;  // backprojection (two kernels), direction update, forward projection
 
 BatchLayout batch_layout(const Batch *b)
 {
@@ -140,10 +140,10 @@ hipError_t batch_iteration(const Batch *b, const BatchInst *T, const int64_t *of
                            hipStream_t st)
 {
     hipError_t e;
-    if ((e = launch_batch_backward(T, off + BG_BWD * (c + 1), c, q + 0, b->grid_bwd, st)) != hipSuccess) return e;
+    if ((e = launch_batch_backward(T, off + BG_BWD * (c + 1), off + BG_DEEP * (c + 1), c, q, b->grid_bwd, b->grid_deep, st)) != hipSuccess) return e;
     if ((e = launch_batch_finalize(T, c, F_BETA, BG_BWD, st)) != hipSuccess) return e;
-    if ((e = launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 1, b->grid_dir, 0, st)) != hipSuccess) return e;
-    if ((e = launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 2, b->grid_fwd, st)) != hipSuccess) return e;
+    if ((e = launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 2, b->grid_dir, 0, st)) != hipSuccess) return e;
+    if ((e = launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 3, b->grid_fwd, st)) != hipSuccess) return e;
     if ((e = launch_batch_finalize(T, c, F_ALPHA, BG_FWD, st)) != hipSuccess) return e;
     if ((e = launch_batch_vec(T, c, BV_CGLS_XE, 0, 0.0, st)) != hipSuccess) return e;
     return launch_batch_finalize(T, c, F_NB, BG_STREAM, st);
@@ -185,7 +185,7 @@ kct_status kct_batch_create(const kct_geometry *geoms, int32_t count, kct_batch 
         b->bwd_v.push_back(backward_default_variant(g->dev));
         b->order.push_back(i);
     }
-    if (batch_persistent_grids(b->grid_fwd, b->grid_bwd, b->grid_dir) != hipSuccess) {
+    if (batch_persistent_grids(b->grid_fwd, b->grid_bwd, b->grid_deep, b->grid_dir) != hipSuccess) {
         delete b;
         return fail(fn, "occupancy query of the persistent kernels failed", KCT_ERR_HIP);
     }
@@ -371,7 +371,10 @@ kct_status kct_batch_cgls_solve(kct_batch h, const float *const *bs, float *cons
         t.e = (float *)(w + L.e[i]);
         t.p = (float *)(w + L.p[i]);
         offs[BG_FWD * (c + 1) + j + 1] = offs[BG_FWD * (c + 1) + j] + items_of(t.nf, BATCH_ITEM_FWD);
-        offs[BG_BWD * (c + 1) + j + 1] = offs[BG_BWD * (c + 1) + j] + items_of(t.nbk, BATCH_ITEM_BWD);
+        const bool deep = t.bwd.tz == 32;  // the kernel that takes this instance's bricks
+        const int64_t nbi = items_of(t.nbk, BATCH_ITEM_BWD);
+        offs[BG_BWD * (c + 1) + j + 1] = offs[BG_BWD * (c + 1) + j] + (deep ? 0 : nbi);
+        offs[BG_DEEP * (c + 1) + j + 1] = offs[BG_DEEP * (c + 1) + j] + (deep ? nbi : 0);
         offs[BG_DIR * (c + 1) + j + 1] = offs[BG_DIR * (c + 1) + j] + items_of(t.ndir, BATCH_ITEM_DIR);
         offs[BG_STREAM * (c + 1) + j + 1] = offs[BG_STREAM * (c + 1) + j] + stream_num_blocks();
     }
@@ -396,10 +399,10 @@ kct_status kct_batch_cgls_solve(kct_batch h, const float *const *bs, float *cons
     KCT_BTRY(launch_batch_vec(T, c, BV_NORM_B, 0, 0.0, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_NB0, BG_STREAM, st));
     KCT_BTRY(launch_batch_vec(T, c, BV_X0_E, 0, 0.0, st));
-    KCT_BTRY(launch_batch_backward(T, off + BG_BWD * (c + 1), c, q + 0, b->grid_bwd, st));
+    KCT_BTRY(launch_batch_backward(T, off + BG_BWD * (c + 1), off + BG_DEEP * (c + 1), c, q, b->grid_bwd, b->grid_deep, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_NR2_INIT, BG_BWD, st));
-    KCT_BTRY(launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 1, b->grid_dir, 1, st));
-    KCT_BTRY(launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 2, b->grid_fwd, st));
+    KCT_BTRY(launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 2, b->grid_dir, 1, st));
+    KCT_BTRY(launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 3, b->grid_fwd, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_ALPHA, BG_FWD, st));
     KCT_BTRY(launch_batch_vec(T, c, BV_CGLS_XE, 0, 0.0, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_NB, BG_STREAM, st));

@@ -20,27 +20,42 @@ __device__ __forceinline__ int batch_find(const int64_t *__restrict__ off, int c
     return __builtin_amdgcn_readfirstlane(lo);
 }
 
-// The next item of a persistent step's queue, the same in every thread of the
-// workgroup.  Items are handed out in increasing order; every workgroup keeps
-// taking items until it draws one beyond the last, so the queue always drains.
-__device__ __forceinline__ int64_t batch_pop(BatchQueue *q)
+// The next of a persistent step's `total` items, the same in every thread of the
+// workgroup; total when none is left.  The items are dealt to one queue per XCD (item
+// modulo BATCH_XCDS; the resident workgroups of the step fill the XCDs in turn), so
+// that tiles which share projections or volume columns run on the XCD whose L2 holds
+// them, as they do in a separate solve's launch; a workgroup whose queue is empty draws
+// from the next one's.  Each queue hands out its items in increasing order and every
+// workgroup draws until all are empty, so the queues always drain.
+__device__ __forceinline__ int64_t batch_pop(BatchQueue *q, int64_t total)
 {
     __shared__ unsigned s_item;
     __syncthreads();  // the previous item's readers are done with s_item
-    if (__builtin_amdgcn_workitem_id_x() == 0) s_item = atomicAdd(&q->next, 1u);
+    if (__builtin_amdgcn_workitem_id_x() == 0) {
+        unsigned item = (unsigned)total;
+        for (unsigned s = 0; s < BATCH_XCDS; ++s) {
+            const unsigned c = (__builtin_amdgcn_workgroup_id_x() + s) % BATCH_XCDS;
+            const unsigned drawn = atomicAdd(&q->next[c], 1u) * BATCH_XCDS + c;
+            if (drawn < (unsigned)total) {
+                item = drawn;
+                break;
+            }
+        }
+        s_item = item;
+    }
     __syncthreads();
     return (int64_t)s_item;
 }
 
 // Leave a persistent step: the last workgroup to leave (every other one has
-// drawn its final item) resets the queue for the next launch of the step.
+// drawn its final item) resets the queues for the next launch of the step.
 __device__ __forceinline__ void batch_exit(BatchQueue *q)
 {
     if (__builtin_amdgcn_workitem_id_x() == 0) {
         __threadfence();
         const unsigned n = atomicAdd(&q->exited, 1u);
         if (n == __builtin_amdgcn_grid_size_x() / __builtin_amdgcn_workgroup_size_x() - 1) {
-            atomicExch(&q->next, 0u);
+            for (unsigned c = 0; c < BATCH_XCDS; ++c) atomicExch(&q->next[c], 0u);
             atomicExch(&q->exited, 0u);
         }
     }

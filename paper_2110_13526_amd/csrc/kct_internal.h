@@ -294,21 +294,22 @@ struct BatchInst {
 // for large volumes of fine voxels).
 enum BwdVariant { BWD_VSHALLOW = 0, BWD_VDEEP = 1, BWD_VARIANTS = 2 };
 
-enum BatchGrid { BG_FWD = 0, BG_BWD, BG_DIR, BG_STREAM, BG_COUNT };  // item tables, each count + 1 long
+enum BatchGrid { BG_FWD = 0, BG_BWD, BG_DIR, BG_STREAM, BG_DEEP, BG_COUNT };  // item tables, each count + 1 long
 // Tiles per queue item of each persistent step: items must far outnumber the
 // resident workgroups for the queue to balance the load (a brick of the
 // backprojection is a long task, a forward or direction tile a short one).
 constexpr int BATCH_ITEM_FWD = 16, BATCH_ITEM_BWD = 1, BATCH_ITEM_DIR = 8;
-// Queue state of one persistent step: the next item, and the workgroups that
-// have left (the last one resets both for the next launch).
+// Queue state of one persistent step: the items drawn from each XCD's queue, and the
+// workgroups that have left (the last one resets all for the next launch).
+constexpr unsigned BATCH_XCDS = 8;
 struct BatchQueue {
-    unsigned next, exited, pad0, pad1;
+    unsigned next[BATCH_XCDS], exited, pad[3];
 };
 
 hipError_t launch_batch_forward(const BatchInst *B, const int64_t *off, int count, BatchQueue *q, int grid,
                                 hipStream_t st);
-hipError_t launch_batch_backward(const BatchInst *B, const int64_t *off, int count, BatchQueue *q, int grid,
-                                 hipStream_t st);
+hipError_t launch_batch_backward(const BatchInst *B, const int64_t *off, const int64_t *off_deep, int count, BatchQueue *q,
+                                 int grid, int grid_deep, hipStream_t st);
 // op: one of the batched vector steps below
 enum BatchVecOp { BV_INIT = 0, BV_NORM_B, BV_X0_E, BV_CGLS_XE };
 hipError_t launch_batch_vec(const BatchInst *B, int count, int op, int maxiter, double err, hipStream_t st);
@@ -317,8 +318,8 @@ hipError_t launch_batch_dir(const BatchInst *B, const int64_t *off, int count, B
 // finalize of every instance; kind: which grid produced the partials (BatchGrid)
 hipError_t launch_batch_finalize(const BatchInst *B, int count, int op, int kind, hipStream_t st);
 // resident workgroups of the persistent kernels on the current device
-hipError_t batch_persistent_grids(int &fwd, int &bwd, int &dir);
-hipError_t batch_backward_occupancy(int &per_cu);
+hipError_t batch_persistent_grids(int &fwd, int &bwd, int &bwd_deep, int &dir);
+hipError_t batch_backward_occupancy(int &per_cu, int &per_cu_deep);
 hipError_t batch_dir_occupancy(int &per_cu);
 // a single backprojection (plain epilogue) with one of the batched form's variants (tuner)
 hipError_t launch_backward_variant(const GeoDev &g, int variant, const float *proj, float *out, hipStream_t st);

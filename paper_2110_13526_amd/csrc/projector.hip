@@ -114,14 +114,20 @@ __global__ __launch_bounds__(256, 7) void kp_forward(const BatchInst *__restrict
 {
     const int64_t total = off[count];
     for (;;) {
-        const int64_t item = batch_pop(q);
+        const int64_t item = batch_pop(q, total);
         if (item >= total) break;
         const int i = batch_find(off, count, item);
         const BatchInst *bi = B + i;
         if (bi->sc->done) continue;
-        const int64_t t0 = (item - off[i]) * BATCH_ITEM_FWD;
-        const int64_t t1 = t0 + BATCH_ITEM_FWD < bi->nf ? t0 + BATCH_ITEM_FWD : bi->nf;
-        for (int64_t t = t0; t < t1; ++t) {
+        // Eight consecutive items take the tiles of one run in turn, so that an item's tiles
+        // are all those of one XCD in the forward's own order; the last items, which do
+        // not fill such a run, take consecutive tiles.
+        constexpr int64_t RUN = (int64_t)BATCH_ITEM_FWD * BATCH_XCDS;
+        const int64_t m = item - off[i], run = m / BATCH_XCDS * RUN;
+        const bool whole = run + RUN <= bi->nf;
+        const int64_t step = whole ? BATCH_XCDS : 1, t0 = whole ? run + m % BATCH_XCDS : m * BATCH_ITEM_FWD;
+        const int64_t tend = t0 + step * BATCH_ITEM_FWD, t1 = tend < bi->nf ? tend : bi->nf;
+        for (int64_t t = t0; t < t1; t += step) {
             batch_forward_tile(bi, t);
             __syncthreads();  // the tile's block sum is read before the next tile writes it
         }
@@ -138,18 +144,19 @@ hipError_t launch_batch_forward(const BatchInst *B, const int64_t *off, int coun
 
 // Resident workgroups of the persistent batched kernels: the device's compute
 // units times the workgroups one of them holds.
-hipError_t batch_persistent_grids(int &fwd, int &bwd, int &dir)
+hipError_t batch_persistent_grids(int &fwd, int &bwd, int &bwd_deep, int &dir)
 {
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    int nf = 0, nb = 0, nd = 0;
+    int nf = 0, nb = 0, nbd = 0, nd = 0;
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nf, kp_forward, 256, 0);
-    if (e == hipSuccess) e = batch_backward_occupancy(nb);
+    if (e == hipSuccess) e = batch_backward_occupancy(nb, nbd);
     if (e == hipSuccess) e = batch_dir_occupancy(nd);
     if (e != hipSuccess) return e;
     fwd = cus * (nf > 0 ? nf : 1);
     bwd = cus * (nb > 0 ? nb : 1);
+    bwd_deep = cus * (nbd > 0 ? nbd : 1);
     dir = cus * (nd > 0 ? nd : 1);
     return hipSuccess;
 }

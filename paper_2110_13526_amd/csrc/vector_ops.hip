@@ -418,7 +418,7 @@ __global__ __launch_bounds__(TB) void kp_dir(const BatchInst *__restrict__ B, co
 {
     const int64_t total = off[count];
     for (;;) {
-        const int64_t item = batch_pop(q);
+        const int64_t item = batch_pop(q, total);
         if (item >= total) break;
         const int i = batch_find(off, count, item);
         const BatchInst *bi = B + i;
