@@ -137,8 +137,9 @@ kct_status kct_project_workspace_size(kct_geometry g, kct_dtype dtype, size_t *b
 /* Forward projection b := A x (Section 2, Eq. 1; standalone projection,
  * Section 3).  x: n_vox elements, b: n_rays elements, both of `dtype`.  `ws`
  * may be NULL (then x is read in its own layout by every view, which is
- * correct but slower); otherwise ws_bytes must be at least
- * kct_project_workspace_size.  Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE,
+ * correct but slower for all but small volumes); otherwise ws_bytes must be at
+ * least kct_project_workspace_size (volumes of up to 32^3 voxels may be read in
+ * place all the same: the same bits).  Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE,
  * HIP. */
 kct_status kct_project(kct_geometry g, kct_dtype dtype, const void *x, void *b, void *ws, size_t ws_bytes,
                        hipStream_t stream);

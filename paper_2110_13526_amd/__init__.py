@@ -202,10 +202,10 @@ def _workspace(nbytes, device):
 def project(g: Geometry, x, out=None, workspace=None, transposed_copy: bool = True):
     """b = A x (forward projection).  Returns a (n_views, nv, nu) tensor of x's dtype.
 
-    With ``transposed_copy`` (default) the library first writes a copy of x with
-    x and y swapped into ``workspace`` (allocated here if None) so that views
-    whose rays run mostly along x read neighbouring addresses; without it every
-    view reads x in place (same result bit for bit, slower)."""
+    With ``transposed_copy`` (default) the library first writes a z-fastest copy
+    of x into ``workspace`` (allocated here if None) so that neighbouring lanes
+    read neighbouring addresses (small volumes are read in place where that is
+    faster); without it every view reads x in place (same result bit for bit, slower)."""
     torch = _torch()
     _check_tensor(x, g.vol_shape, "x", g.device)
     if out is None:
