@@ -53,11 +53,11 @@ __host__ __device__ constexpr int wave_rows(bool split) { return wave_cap(split)
 // that add_row may read.
 __host__ __device__ constexpr int wave_region(bool split) { return wave_cap(split) + W_NHMAX - 1; }
 
-// LDS bytes of a workgroup of `waves` wavefronts: staging regions, columns, row
-// factors, and the wavefronts' shares of the partial sum of squares.
+// LDS bytes of a workgroup of `waves` wavefronts: staging regions, columns and row
+// factors.
 template <typename A, bool SPLIT> __host__ __device__ constexpr size_t wave_lds_bytes(int waves)
 {
-    return (size_t)waves * (wave_region(SPLIT) * sizeof(PixStage<A, SPLIT>) + wave_cols(SPLIT) * sizeof(ColStage) + sizeof(double) +
+    return (size_t)waves * (wave_region(SPLIT) * sizeof(PixStage<A, SPLIT>) + wave_cols(SPLIT) * sizeof(ColStage) +
                             (SPLIT ? wave_rows(SPLIT) * sizeof(float) : 0));
 }
 
@@ -81,8 +81,9 @@ template <typename E> __device__ __forceinline__ const E *byte_at(const void *ba
 // turn: wavefront v and turn i take views s, s + S, ... with s = v * subs + i and
 // S = waves * subs.  A voxel's S partial sums are added in order within each of
 // W_GROUPS groups of neighbouring subsets, and the groups pairwise, so the sum
-// depends on S alone.  The partial sum of squares goes to partials[w].  lds:
-// wave_lds_bytes(waves) bytes, 16-byte aligned.  MANY: subs may exceed 1, waves is
+// depends on S alone; the squares of a layer of voxels are added first, then the
+// layers in order, so the partial sum of squares, which goes to partials[w],
+// depends on S alone as well.  lds: wave_lds_bytes(waves) bytes, 16-byte aligned.  MANY: subs may exceed 1, waves is
 // W_GROUPS.
 template <typename T, int EPI, int TZB, bool MANY>
 __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, const T *__restrict__ proj,
@@ -100,12 +101,13 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
     static_assert(sizeof(A) * W_SUMS * 64 <= sizeof(Rec) * REGION, "the partial sums fit a staging region");
     Rec *s_all = static_cast<Rec *>(lds);
     ColStage *c_all = reinterpret_cast<ColStage *>(s_all + waves * REGION);
-    double *red = reinterpret_cast<double *>(c_all + waves * COLS);
+    double *layer_sq = reinterpret_cast<double *>(c_all);  // once the columns are no longer read
+    static_assert(sizeof(double) * TZB <= sizeof(ColStage) * COLS, "a layer's sum of squares each");
     const int wave = __builtin_amdgcn_readfirstlane((int)(__builtin_amdgcn_workitem_id_x() >> 6));
     const int lane = (int)(__builtin_amdgcn_workitem_id_x() & 63);
     Rec *s_pix = s_all + wave * REGION;
     ColStage *s_col = c_all + wave * COLS;
-    float *s_row = reinterpret_cast<float *>(red + waves) + wave * ROWS;  // used when SPLIT
+    float *s_row = reinterpret_cast<float *>(c_all + waves * COLS) + wave * ROWS;  // used when SPLIT
 
     // XCD-aware brick assignment (see backproject.hip)
     constexpr int XCDS = 8;
@@ -217,7 +219,6 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
     // every voxel's partial sums through LDS, W_SUMS voxels of each lane at a time:
     // in order within a group, then the groups
     A *mine = reinterpret_cast<A *>(s_pix);
-    double sq = 0.0;
     const int per = waves / W_GROUPS;
 #pragma unroll
     for (int j0 = 0; j0 < TZB; j0 += W_SUMS) {
@@ -235,21 +236,24 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
                 v[q] = reinterpret_cast<const A *>(s_all + q * per * REGION)[at];
                 for (int i = 1; i < per; ++i) v[q] += reinterpret_cast<const A *>(s_all + (q * per + i) * REGION)[at];
             }
+            double sq = 0.0;
             if (valid) {
                 const int iz = iz0 + j;
                 const size_t vox = ((size_t)iz * g.ny + iy) * g.nx + ix;
-                sq += bwd_store<T, EPI, A>(out, out_z, sc, aux, vox, ((size_t)iy * g.nx + ix) * g.nz + iz,
-                                           (v[0] + v[1]) + (v[2] + v[3]));
+                sq = bwd_store<T, EPI, A>(out, out_z, sc, aux, vox, ((size_t)iy * g.nx + ix) * g.nz + iz,
+                                          (v[0] + v[1]) + (v[2] + v[3]));
+            }
+            if (bwd_has_partials<EPI>()) {
+                for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+                if (lane == 0) layer_sq[j] = sq;
             }
         }
     }
     if (bwd_has_partials<EPI>()) {
-        for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
-        if (lane == 0) red[wave] = sq;
         __syncthreads();
         if (__builtin_amdgcn_workitem_id_x() == 0) {
-            double r = red[0];
-            for (int q = 1; q < waves; ++q) r += red[q];
+            double r = layer_sq[0];
+            for (int j = 1; j < nzb; ++j) r += layer_sq[j];
             partials[w] = r;
         }
     }

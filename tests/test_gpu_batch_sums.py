@@ -1,0 +1,35 @@
+"""A batched solve returns the separate solve's scalars to the bit, the residual norm
+NR2 of the backprojection's partial sums among them, whatever the number of wavefronts
+a brick's view subsets are dealt to."""
+import pytest
+
+import kct_inputs as ki
+from tests.gpu_util import dev, geometry, say, torch_mod
+from tests.test_gpu_forms import FORMS, _cube
+
+pytestmark = pytest.mark.gpu
+
+GEOMETRIES = {
+    "depth_4": [FORMS["4x16"], FORMS["4x16_rows_chunked"]],
+    "depth_8": [FORMS["8x16"], FORMS["8x8"]],
+    "depth_16": [FORMS["16x16"], FORMS["16x8"], _cube(49, 41, 65, 1.0, 40)],
+    "depth_32": [FORMS["32x4"]],
+}
+
+
+@pytest.mark.parametrize("depth", sorted(GEOMETRIES))
+def test_batch_scalars_equal_separate_solves(depth):
+    import paper_2110_13526_amd as kct
+    torch = torch_mod()
+    descs = GEOMETRIES[depth]
+    geoms = [geometry(g) for g in descs]
+    bs = [torch.from_numpy(ki.random_projections(g, 7)).to(dev()).to(torch.float32) for g in descs]
+    batch = kct.Batch(geoms)
+    for K in (1, 2, 5):
+        xs, infos = batch.cgls(bs, K)
+        for g, b, x, i in zip(geoms, bs, xs, infos):
+            x1, i1 = kct.cgls(g, b, K)
+            say(f"[batch sums] {depth} K {K} vol {g.vol_shape}: nr2 {i.nr2!r} {i1.nr2!r}")
+            assert torch.equal(x, x1)
+            assert (i.nr2, i.nb, i.nb0) == (i1.nr2, i1.nb, i1.nb0)
+    batch.close()
