@@ -138,7 +138,8 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
                 // through the view loop
                 int ixv = ix, iyv = iy;
                 asm volatile("" : "+v"(ixv), "+v"(iyv));
-                if (valid) gather_chunk<A, SQ, CHC, NH, (TZB < TZ_DEEP)>(g, vp, ixv, iyv, iz0, s_pix, s_col, s_row, cu0, ncol, cv0, nrow, acc);
+                if (valid)
+                    gather_chunk<A, SQ, CHC, NH, (TZB < TZ_DEEP)>(g, vp, ixv, iyv, iz0, s_pix, s_col, s_row, cu0, ncol, cv0, nrow, nzb, acc);
                 __syncthreads();
             }
         }

@@ -50,6 +50,17 @@ __host__ __device__ constexpr int ch_cols(int tzb) { return tzb == TZ_DEEP ? 32 
 __host__ __device__ constexpr int ch_rows(int tzb) { return tzb == TZ_DEEP ? 36 : 32; }
 constexpr int NH = 2;                      // detector columns held in registers at once
 
+// A brick's layers above the volume's top are left out in groups of this many (a
+// thin volume would otherwise cost what a full brick does).  One scalar branch per
+// group; a test per voxel costs a scalar condition each, which the compiler keeps in
+// spilled registers.  Measured (us, no test / groups of 8 / 4 / 2 / 1): 1024^2 x 1 at 0.7
+// pixels per voxel, 1 view 20.3 / 12.8 / 11.6 / 11.7 / 12.1; 1024^2 x 2, 60 views 890 / 424 / 351 /
+// 318 / 319; 1024^2 x 20, 8 views 134 / 113 / 102 / 104 / 109; 256^3 x 360 8165 / 8183 / 8119 /
+// 9118 / 9296; 192^3 x 180 1606 / 1618 / 1611 / 2096 / 2137; 512^3 x 720 (ms) 64.8 / 64.7 / 64.8 /
+// 65.6 / 67.7.
+constexpr int LAYER_GROUP = 4;
+__host__ __device__ constexpr bool layer_test(int j) { return j > 0 && j % LAYER_GROUP == 0; }
+
 struct ColStage {  // per staged detector column: in-plane ray parameters
     float eta_c, inv_a, tcv;  // ColParam's; columns parallel to the eta planes staged as below (PAR_INV)
     float gz;      // d T / d xi with T = (segment fraction) / vz
@@ -364,10 +375,9 @@ __host__ __device__ __forceinline__ int clamp_row(int v, int hi)
 // The voxels of one lane for one group of hit columns: voxel j has the planes
 // mbz0 + j and mbz0 + j + 1 and, counted from the first staged row, the candidate
 // rows va + 1 .. vb + 1 with va = floor(l0 + j sl) and vb = floor(h0 + (j + 1) sh).
-// All TZN voxels are taken, those of a brick that reaches past the volume's top
-// as well (their sums are never stored): a test per voxel costs a scalar condition
-// each, which the compiler kept in spilled registers (4 of about 34 instructions
-// per voxel).  The first candidate row is evaluated for every voxel, without a
+// `layers` of the TZN voxels lie in the volume (the same in every lane); those above are
+// left out from the next whole LAYER_GROUP on (sums of the others are never stored).
+// The first candidate row is evaluated for every voxel, without a
 // branch: va is clamped to [-1, nrow - 1], so row va + 1 is a staged row or the zero
 // row staged after them, and a row that is not a candidate has weight exactly
 // 0 (the weights are exact).  Further rows, up to the last staged one, follow in a
@@ -376,7 +386,7 @@ template <typename A, bool SQ, int CHC, int NH, bool EARLY, int TZN, bool SPLIT>
 __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A, SPLIT> *pg, const float *rg, int stride, int nh,
                                                     const float (&kz)[NH], const float (&lo)[NH],
                                                     const float (&hi)[NH], float mbz0, float l0, float sl,
-                                                    float h0, float sh, int nrow, A (&acc)[TZN])
+                                                    float h0, float sh, int nrow, int layers, A (&acc)[TZN])
 {
     // The per-voxel plane values do not depend on the column group; computed
     // here they stay short-lived (hoisted out of the group loop, all TZ of them
@@ -403,6 +413,7 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A, SPLIT> *pg
     }
 #pragma unroll
     for (int j = 0; j < TZN; ++j) {
+        if (layer_test(j) && j >= layers) break;
         const float mb1 = mb + 1.0f;
         // candidate rows va + 1 .. vb + 1: floor(lo) + 1 is ceil(lo) except at an
         // integer lo, whose row lies 0.01 below the true bound and is rightly left out
@@ -458,7 +469,7 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A, SPLIT> *pg
 }
 
 // One lane's share of one staged chunk of one view: add w_ij * (L_i e_i) to the
-// accumulators of its voxels (ix, iy, iz0 + j), j < TZN, for every staged ray
+// accumulators of its voxels (ix, iy, iz0 + j), j < layers <= TZN, for every staged ray
 // i = (column cu0 + c, row cv0 + r); s_pix[r * stride + c] describes ray i (stride:
 // CHC, or the argument where CHC is 0), and row nrow of s_pix holds zero records
 // (weight 0 for any voxel).  NH columns are taken at once.
@@ -468,7 +479,7 @@ template <typename A, bool SQ, int CHC, int NH, bool EARLY, int TZN, bool SPLIT>
 __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const ViewParam &vp, int ix, int iy, int iz0,
                                                       const PixStage<A, SPLIT> *s_pix, const ColStage *s_col,
                                                       const float *s_row, int cu0,
-                                                      int ncol, int cv0, int nrow, A (&acc)[TZN], int stride = CHC)
+                                                      int ncol, int cv0, int nrow, int layers, A (&acc)[TZN], int stride = CHC)
 {
     int ixi, ieta;
     float hxi, heta;
@@ -525,7 +536,7 @@ __host__ __device__ __forceinline__ void gather_chunk(const GeoDev &g, const Vie
         const float sh = (fmaxf(b1, b2) - fmaxf(a1, a2)) * (1.0f / TZN);
         const float l0 = fminf(a1, a2) + vofs_lo, h0 = fmaxf(a1, a2) + vofs_hi;
         const PixStage<A, SPLIT> *pg = s_pix + ((c0 - cu0) + (CHC != 0 ? CHC : stride));  // row va + 1 at pg + va * stride
-        voxel_rows<A, SQ, CHC, NH, EARLY>(pg, s_row + 1, stride, nh, kz, lo, hi, mbz0, l0, sl, h0, sh, nrow, acc);
+        voxel_rows<A, SQ, CHC, NH, EARLY>(pg, s_row + 1, stride, nh, kz, lo, hi, mbz0, l0, sl, h0, sh, nrow, layers, acc);
     }
 }
 

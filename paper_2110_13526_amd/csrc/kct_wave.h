@@ -202,7 +202,7 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
                     int ixv = ix, iyv = iy;
                     asm volatile("" : "+v"(ixv), "+v"(iyv));
                     if (valid)
-                        gather_chunk<A, SQ, 0, NCOL, true>(g, vp, ixv, iyv, iz0, s_pix, s_col, s_row, cu0, ncol, cv0, nrow, acc, ncol);
+                        gather_chunk<A, SQ, 0, NCOL, true>(g, vp, ixv, iyv, iz0, s_pix, s_col, s_row, cu0, ncol, cv0, nrow, nzb, acc, ncol);
                     wave_lds_order();
                 }
             }

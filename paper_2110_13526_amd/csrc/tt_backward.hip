@@ -144,7 +144,7 @@ __global__ __launch_bounds__(1024, 5) void k_backward_tt(GeoDev g, const T *__re
                 }
                 wave_lds_order();
                 if (valid)
-                    tt_gather_ramps<float, SQ, OVERLAP, TTB_NC, TZB>(g, iz0, tu.t, ka, kb, s_le, ncol, cu0, ncol, cv0, nrow, acc);
+                    tt_gather_ramps<float, SQ, OVERLAP, TTB_NC, TZB>(g, iz0, tu.t, ka, kb, s_le, ncol, cu0, ncol, cv0, nrow, nzb, acc);
                 wave_lds_order();
             }
         }
