@@ -194,13 +194,16 @@ static BwdPlan brick_plan(const GeoDev &g, int form)
 }
 
 // Expected shadow of n voxel columns a side and tz layers, in pixels at the
-// isocentre's magnification: columns over the diagonal, rows, each with a little
-// for the nearer half of the orbit and for the ends.
+// isocentre's magnification: columns over the diagonal, rows (of the layers that the
+// volume has), each with a little for the nearer half of the orbit and for the ends.
 static float shadow_cols(const GeoDev &g, int n)
 {
     return 1.05f * 1.4142f * (float)n * fmaxf(g.vx, g.vy) * g.ku / g.sid + 2.0f;
 }
-static float shadow_rows(const GeoDev &g, int tz) { return 1.1f * (float)tz * g.vz * g.kv / g.sid + 3.0f; }
+static float shadow_rows(const GeoDev &g, int tz)
+{
+    return 1.1f * (float)(tz < g.nz ? tz : g.nz) * g.vz * g.kv / g.sid + 3.0f;
+}
 
 // Wave form: the deepest brick whose shadow is expected to fit one chunk (or nearly so:
 // a second chunk now and then costs less than shallower bricks) and that leaves enough
@@ -211,7 +214,8 @@ static float shadow_rows(const GeoDev &g, int tz) { return 1.1f * (float)tz * g.
 // n 192, q 2.2: - / 4389 / 2929 / 3364; n 192, q 3.2: - / 12665 / 8635 / 7236; n 64, q 1.6:
 // - / 118 / 81 / 94.  4 or 8 subsets: 2048 bricks (n 128, q 1.25) 668 / 543, 4096 (n 128,
 // q 2.2) 1444 / 1373, 6912 (n 192, q 1.25) 1175 / 1129, 16384 (n 256, q 1) 5685 / 5735, 31250
-// (n 400, q 1.25) 4759 / 4876.
+// (n 400, q 1.25) 4759 / 4876.  No deeper than the volume: 1024^2 x 6, q 2.2, 8 views in
+// double precision, 8- / 4-deep 249 / 347.
 static BwdPlan wave_plan(const GeoDev &g, bool single)
 {
     BwdPlan p{};
@@ -220,6 +224,7 @@ static BwdPlan wave_plan(const GeoDev &g, bool single)
     p.nby = (g.ny + WY - 1) / WY;
     const float cols = shadow_cols(g, WX);
     for (p.tz = 32; p.tz > 4; p.tz /= 2) {
+        if (p.tz / 2 >= g.nz) continue;
         const float records = cols * (shadow_rows(g, p.tz) + 1.0f);
         p.nbz = (g.nz + p.tz - 1) / p.tz;
         p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
@@ -246,18 +251,21 @@ static BwdPlan wave_plan(const GeoDev &g, bool single)
 //   q 1.25: n 192 1129 / 1555 / 2276, n 256 6627 / 6882 / 12587, n 400 4759 / 4602 / 6751
 //   q 1.6:  n 256 9777 / 10723 / -, n 320 3679 / 3806 / -, n 400 7145 / 6823 / 12867
 //   q 2.2:  n 256 17924 / 27169 / -, n 400 12890 / 17528 / -
+// Double precision takes the deep bricks for volumes of 128 layers and more only: 16- /
+// 32-deep 512^2 x 40, q 0.7, 30 views 280 / 347, 1024^2 x 1, 60 views 372 / 464; n 256, 30 views
+// 373 / 352.
 static BwdPlan plan(const GeoDev &g, bool deep_allowed, bool single = true)
 {
     const BwdPlan deep = brick_plan(g, BWD_DEEP), shallow = brick_plan(g, BWD_BRICKS);
     const float cols = shadow_cols(g, BX);
-    if (deep_allowed && deep.nblocks >= 2048 && cols <= (float)ch_cols(TZ_DEEP) &&
+    if (deep_allowed && (single || g.nz >= 128) && deep.nblocks >= 2048 && cols <= (float)ch_cols(TZ_DEEP) &&
         shadow_rows(g, TZ_DEEP) <= (float)ch_rows(TZ_DEEP))
         return deep;
     if (shallow.nblocks >= (single ? 12288 : 4096) && cols <= (float)ch_cols(TZ) && shadow_rows(g, TZ) <= (float)ch_rows(TZ)) return shallow;
     return wave_plan(g, single);
 }
 
-BwdPlan backward_plan(const GeoDev &g) { return plan(g, true); }
+BwdPlan backward_plan(const GeoDev &g, bool single) { return plan(g, true, single); }
 
 BwdPlan backward_plan_variant(const GeoDev &g, int variant)
 {
@@ -396,7 +404,7 @@ hipError_t launch_backward(const GeoDev &g, const T *proj, T *out, T *out_z, int
                            double *partials, const int *skip, hipStream_t st, const float *aux)
 {
     if (g.projector == KCT_PROJECTOR_TT) return launch_backward_tt<T>(g, proj, out, out_z, epi, sc, partials, skip, st, aux);
-    const BwdPlan p = plan(g, true, !std::is_same<T, double>::value);
+    const BwdPlan p = backward_plan(g, !std::is_same<T, double>::value);
     if (p.form == BWD_WAVES) return launch_backward_waves<T>(g, p, proj, out, out_z, epi, sc, partials, skip, st, aux);
     if constexpr (std::is_same<T, double>::value) {  // double storage: plain backprojection only
         if (epi != BWD_PLAIN) return hipErrorInvalidValue;

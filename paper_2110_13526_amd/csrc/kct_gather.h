@@ -50,16 +50,20 @@ __host__ __device__ constexpr int ch_cols(int tzb) { return tzb == TZ_DEEP ? 32 
 __host__ __device__ constexpr int ch_rows(int tzb) { return tzb == TZ_DEEP ? 36 : 32; }
 constexpr int NH = 2;                      // detector columns held in registers at once
 
-// A brick's layers above the volume's top are left out in groups of this many (a
-// thin volume would otherwise cost what a full brick does).  One scalar branch per
-// group; a test per voxel costs a scalar condition each, which the compiler keeps in
-// spilled registers.  Measured (us, no test / groups of 8 / 4 / 2 / 1): 1024^2 x 1 at 0.7
-// pixels per voxel, 1 view 20.3 / 12.8 / 11.6 / 11.7 / 12.1; 1024^2 x 2, 60 views 890 / 424 / 351 /
-// 318 / 319; 1024^2 x 20, 8 views 134 / 113 / 102 / 104 / 109; 256^3 x 360 8165 / 8183 / 8119 /
-// 9118 / 9296; 192^3 x 180 1606 / 1618 / 1611 / 2096 / 2137; 512^3 x 720 (ms) 64.8 / 64.7 / 64.8 /
-// 65.6 / 67.7.
-constexpr int LAYER_GROUP = 4;
-__host__ __device__ constexpr bool layer_test(int j) { return j > 0 && j % LAYER_GROUP == 0; }
+// A brick's layers above the volume's top are left out in groups of 4 (a thin volume
+// would otherwise cost what a full brick does).  One scalar branch per group; a test
+// per voxel costs a scalar condition each, which the compiler keeps in spilled registers.
+// Measured (us, no test / groups of 8 / 4 / 2 / 1): 1024^2 x 1 at 0.7 pixels per voxel, 1 view
+// 20.3 / 12.8 / 11.6 / 11.7 / 12.1; 1024^2 x 2, 60 views 890 / 424 / 351 / 318 / 319; 1024^2 x 20,
+// 8 views 134 / 113 / 102 / 104 / 109; 256^3 x 360 8165 / 8183 / 8119 / 9118 / 9296; 192^3 x 180
+// 1606 / 1618 / 1611 / 2096 / 2137; 512^3 x 720 (ms) 64.8 / 64.7 / 64.8 / 65.6 / 67.7.
+// Double precision in bricks up to 16 deep: groups of 2, which cost full bricks nothing
+// there (groups of 4 / 2 / 1: 1024^2 x 1 at 1.25 pixels per voxel, 8 views 78.6 / 67.3 / 69.2,
+// 60 views 561 / 476 / 484; 256^3 x 20 657 / 658 / 684; 32-deep, 128^3 x 60 89.8 / 97.2 / 103).
+template <typename A> __host__ __device__ constexpr bool layer_test(int j, int tzb)
+{
+    return j > 0 && j % (sizeof(A) == 8 && tzb < TZ_DEEP ? 2 : 4) == 0;
+}
 
 struct ColStage {  // per staged detector column: in-plane ray parameters
     float eta_c, inv_a, tcv;  // ColParam's; columns parallel to the eta planes staged as below (PAR_INV)
@@ -376,7 +380,7 @@ __host__ __device__ __forceinline__ int clamp_row(int v, int hi)
 // mbz0 + j and mbz0 + j + 1 and, counted from the first staged row, the candidate
 // rows va + 1 .. vb + 1 with va = floor(l0 + j sl) and vb = floor(h0 + (j + 1) sh).
 // `layers` of the TZN voxels lie in the volume (the same in every lane); those above are
-// left out from the next whole LAYER_GROUP on (sums of the others are never stored).
+// left out from the next group on (layer_test; the others' sums are never stored).
 // The first candidate row is evaluated for every voxel, without a
 // branch: va is clamped to [-1, nrow - 1], so row va + 1 is a staged row or the zero
 // row staged after them, and a row that is not a candidate has weight exactly
@@ -413,7 +417,7 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A, SPLIT> *pg
     }
 #pragma unroll
     for (int j = 0; j < TZN; ++j) {
-        if (layer_test(j) && j >= layers) break;
+        if (layer_test<A>(j, TZN) && j >= layers) break;
         const float mb1 = mb + 1.0f;
         // candidate rows va + 1 .. vb + 1: floor(lo) + 1 is ceil(lo) except at an
         // integer lo, whose row lies 0.01 below the true bound and is rightly left out

@@ -255,7 +255,7 @@ struct BwdPlan {
     int nbx, nby, nbz;
     int64_t nblocks;  // bricks (and partial sums)
 };
-BwdPlan backward_plan(const GeoDev &g);               // a single backprojection's
+BwdPlan backward_plan(const GeoDev &g, bool single = true);  // a single backprojection's (single: in single precision)
 BwdPlan tt_backward_plan(const GeoDev &g);            // the TT projector's
 BwdPlan backward_plan_variant(const GeoDev &g, int variant);  // of a batched form's variant
 template <typename T>

@@ -18,7 +18,6 @@
 
 #pragma clang fp contract(off)
 
-#include "kct_gather.h"
 #include "kct_internal.h"
 #include "kct_weights.h"
 
@@ -368,12 +367,15 @@ __host__ __device__ __forceinline__ void tt_gather_chunk(const GeoDev &g, int iz
     }
 }
 
+// Whether layer j of tzb is tested against the volume's top: groups of 4 as in
+// kct_gather.h; every layer of the 4-deep bricks, which hold the thinnest volumes.
+__host__ __device__ constexpr bool tt_layer_test(int j, int tzb) { return j > 0 && (tzb == 4 || j % 4 == 0); }
+
 // One lane's share of one staged chunk by ramps: add fl(F_u F_v) * s_le[pixel] to
 // acc[j] for the TZN voxels above layer iz0 of a column with transaxial breakpoints t
 // (sorted) and row scales ka, kb, over the staged pixels (column cu0 + c, row cv0 + r) at
 // s_le[r * stride + c].  SQ: add fl(F_u F_v)^2 * s_le instead.  Of the layers, `layers` lie
-// in the volume; those above are left out from the next whole LAYER_GROUP on.  NC columns
-// at once.
+// in the volume; those above are left out from the next group on.  NC columns at once.
 template <typename A, bool SQ, bool OVERLAP, int NC, int TZN>
 __host__ __device__ __forceinline__ void tt_gather_ramps(const GeoDev &g, int iz0, const float (&t)[4], float ka, float kb,
                                                          const A *s_le, int stride, int cu0, int ncol, int cv0, int nrow,
@@ -400,7 +402,7 @@ __host__ __device__ __forceinline__ void tt_gather_ramps(const GeoDev &g, int iz
         TTRamp p0 = tt_plane_ramp(g, (float)iz0, kai, kbi, roff);
 #pragma unroll
         for (int j = 0; j < TZN; ++j) {
-            if (layer_test(j) && j >= layers) break;
+            if (tt_layer_test(j, TZN) && j >= layers) break;
             const TTRamp p1 = tt_plane_ramp(g, (float)(iz0 + j + 1), kai, kbi, roff);
             TTRamp a, b;
             tt_layer_ramps<OVERLAP>(p0, p1, a, b);

@@ -1,0 +1,36 @@
+// plan_query.cpp -- the kernel forms that a geometry takes, for tests of the rules that
+// choose them (not part of kct.h; host arithmetic only, no device needed).
+#include <string>
+#include <vector>
+
+#include "kct_internal.h"
+
+namespace kct {
+
+void set_error(const std::string &msg);
+kct_status geometry_tables(const kct_volume_desc &vol, const kct_cone_desc &cone, std::vector<ColParam> &cols,
+                           std::vector<RowParam> &rows, std::vector<ViewParam> &views, GeoDev &d);
+
+}  // namespace kct
+
+using namespace kct;
+
+// out: forward rows per lane, divided, read in place, forward workgroups; backward form
+// (BwdForm), brick depth, view subsets, bricks.
+extern "C" kct_status kct_test_plan(const kct_volume_desc *vol, const kct_cone_desc *cone, int32_t projector,
+                                    kct_dtype dtype, int64_t out[8])
+{
+    std::vector<ColParam> cols;
+    std::vector<RowParam> rows;
+    std::vector<ViewParam> views;
+    GeoDev g{};
+    const kct_status s = geometry_tables(*vol, *cone, cols, rows, views, g);
+    if (s != KCT_OK) return s;
+    g.projector = projector;
+    const bool tt = projector == KCT_PROJECTOR_TT;
+    const FwdPlan f = forward_plan(g);
+    const BwdPlan b = tt ? tt_backward_plan(g) : backward_plan(g, dtype != KCT_F64);
+    const int64_t v[8] = {f.rows, f.divided, forward_in_place(g), forward_num_blocks(g), b.form, b.tz, b.sets, b.nblocks};
+    for (int i = 0; i < 8; ++i) out[i] = v[i];
+    return KCT_OK;
+}

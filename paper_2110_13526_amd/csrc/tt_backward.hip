@@ -34,9 +34,10 @@ BwdPlan tt_backward_plan(const GeoDev &g)
     p.nby = (g.ny + WY - 1) / WY;
     const float cols = 1.05f * 1.4142f * (float)WX * fmaxf(g.vx, g.vy) * g.ku / g.sid + 3.0f;
     for (p.tz = 16;; p.tz /= 2) {
+        if (p.tz > 4 && p.tz / 2 >= g.nz) continue;  // (no deeper than the volume)
         p.nbz = (g.nz + p.tz - 1) / p.tz;
         p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
-        const float rows = 1.1f * (float)p.tz * g.vz * g.kv / g.sid + 3.0f;
+        const float rows = 1.1f * (float)(p.tz < g.nz ? p.tz : g.nz) * g.vz * g.kv / g.sid + 3.0f;
         if (p.tz == 4 || (cols * rows <= (float)TTB_CAP && p.nblocks >= 192)) break;
     }
     p.sets = p.nblocks > 2048 ? 4 : (p.nblocks > 512 ? 8 : 16);
