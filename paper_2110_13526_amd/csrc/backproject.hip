@@ -8,6 +8,7 @@
 // round-robin in dispatch order) owns a contiguous range of bricks: bricks that
 // neighbour each other share most of their detector shadow, so the staged
 // projection values are reused from the XCD's own L2.
+#include <cmath>
 #include <type_traits>
 
 #include "kct_batch.h"
@@ -205,6 +206,31 @@ static float shadow_rows(const GeoDev &g, int tz)
     return 1.1f * (float)(tz < g.nz ? tz : g.nz) * g.vz * g.kv / g.sid + 3.0f;
 }
 
+// View subsets of the wave form, at most `most` (a power of two): none without a view
+// but in the last octave, and for fewer than eight views the number of the least
+// ceil(views / subsets) x wavefronts, a chip of 4096 wavefronts counting as full; one and two
+// subsets cost 10 and 5 % more per view.  Measured (us, 4 / 2 / 1 subsets; n, q as
+// below): n 192, q 1.25, 1 view 78.5 / - / 25.1, 2 views - / 33.9 / 37.4, 4 views 51.0 / 53.9 / 62.1,
+// 6 views 82.1 / 76.7 / 90.2; n 256, q 2.2, 1 view 191 / - / 81, 3 views 266 / 218 / 201; n 400,
+// q 1.25, 4 views 404 / 394 / 389; 2048^2 x 4, q 0.7, 30 views 841 / 870 / 882.
+int wave_sets(int64_t bricks, int most, int views)
+{
+    int sets = most;
+    while (sets / 2 >= views) sets /= 2;
+    if (views >= 8) return sets;
+    float best = INFINITY;
+    int chosen = sets;
+    for (int s = sets; s >= 1; s /= 2) {
+        const int64_t waves = bricks * s < 4096 ? 4096 : bricks * s;
+        const float cost = (float)((views + s - 1) / s) * (float)waves * (s == 1 ? 1.1f : (s == 2 ? 1.05f : 1.0f));
+        if (cost < best) {
+            best = cost;
+            chosen = s;
+        }
+    }
+    return chosen;
+}
+
 // Wave form: the deepest brick whose shadow is expected to fit one chunk (or nearly so:
 // a second chunk now and then costs less than shallower bricks) and that leaves enough
 // bricks, and as many view subsets as fill the chip.  Measured (us, cube of n voxels, q
@@ -216,6 +242,8 @@ static float shadow_rows(const GeoDev &g, int tz)
 // q 2.2) 1444 / 1373, 6912 (n 192, q 1.25) 1175 / 1129, 16384 (n 256, q 1) 5685 / 5735, 31250
 // (n 400, q 1.25) 4759 / 4876.  No deeper than the volume: 1024^2 x 6, q 2.2, 8 views in
 // double precision, 8- / 4-deep 249 / 347.
+// For few views more bricks, as many wavefronts as eight views give (n 96, q 1.25, 1 view, 16- / 8- /
+// 4-deep 11.4 / 8.9 / 8.4).
 static BwdPlan wave_plan(const GeoDev &g, bool single)
 {
     BwdPlan p{};
@@ -223,19 +251,22 @@ static BwdPlan wave_plan(const GeoDev &g, bool single)
     p.nbx = (g.nx + WX - 1) / WX;
     p.nby = (g.ny + WY - 1) / WY;
     const float cols = shadow_cols(g, WX);
+    const int few = 1536 / (g.nviews < 8 ? g.nviews : 8);
     for (p.tz = 32; p.tz > 4; p.tz /= 2) {
         if (p.tz / 2 >= g.nz) continue;
         const float records = cols * (shadow_rows(g, p.tz) + 1.0f);
         p.nbz = (g.nz + p.tz - 1) / p.tz;
         p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
         const float over = p.tz == 8 ? 1.3f : (p.tz == 16 && single ? 1.1f : 1.0f);
-        if (records <= over * (float)wave_cap(single && split_records<float>(p.tz)) && p.nblocks >= (p.tz == 32 ? 1024 : 192)) break;
+        if (records <= over * (float)wave_cap(single && split_records<float>(p.tz)) && p.nblocks >= (p.tz == 32 && few < 1024 ? 1024 : few))
+            break;
     }
     p.nbz = (g.nz + p.tz - 1) / p.tz;
     p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
     // (bricks of 32: one subset per wavefront of the batched form, whose second set of
     // sums would not fit its registers)
-    p.sets = p.tz == 32 || p.nblocks > (single ? 8192 : 2048) ? 4 : (p.nblocks > 512 ? 8 : 16);
+    const int most = p.tz == 32 || p.nblocks > (single ? 8192 : 2048) ? 4 : (p.nblocks > 512 ? 8 : 16);
+    p.sets = wave_sets(p.nblocks, most, g.nviews);
     return p;
 }
 
@@ -251,6 +282,10 @@ static BwdPlan wave_plan(const GeoDev &g, bool single)
 //   q 1.25: n 192 1129 / 1555 / 2276, n 256 6627 / 6882 / 12587, n 400 4759 / 4602 / 6751
 //   q 1.6:  n 256 9777 / 10723 / -, n 320 3679 / 3806 / -, n 400 7145 / 6823 / 12867
 //   q 2.2:  n 256 17924 / 27169 / -, n 400 12890 / 17528 / -
+// With few views the wavefronts of a workgroup brick all work on each of them, and the
+// 16-deep bricks pay from 300 bricks per view on (wave form / 16-deep): q 1.25, n 192 (1728 bricks) 1
+// view 25.1 / 19.8, 2 views 33.9 / 31.5, 4 views 51.0 / 54.4, 6 views 76.7 / 82.9; n 256 (4096 bricks) 1
+// view 44.0 / 32.0, 6 views 160 / 143; 256^2 x 68 (1280 bricks) 4 views 36.1 / 32.7, 30 views 199 / 219.
 // Double precision takes the deep bricks for volumes of 128 layers and more only: 16- /
 // 32-deep 512^2 x 40, q 0.7, 30 views 280 / 347, 1024^2 x 1, 60 views 372 / 464; n 256, 30 views
 // 373 / 352.
@@ -261,7 +296,10 @@ static BwdPlan plan(const GeoDev &g, bool deep_allowed, bool single = true)
     if (deep_allowed && (single || g.nz >= 128) && deep.nblocks >= 2048 && cols <= (float)ch_cols(TZ_DEEP) &&
         shadow_rows(g, TZ_DEEP) <= (float)ch_rows(TZ_DEEP))
         return deep;
-    if (shallow.nblocks >= (single ? 12288 : 4096) && cols <= (float)ch_cols(TZ) && shadow_rows(g, TZ) <= (float)ch_rows(TZ)) return shallow;
+    const int enough = single ? 12288 : 4096, per_view = 300;
+    if (shallow.nblocks >= (g.nviews < enough / per_view ? per_view * g.nviews : enough) && cols <= (float)ch_cols(TZ) &&
+        shadow_rows(g, TZ) <= (float)ch_rows(TZ))
+        return shallow;
     return wave_plan(g, single);
 }
 
@@ -312,19 +350,19 @@ __device__ __forceinline__ void batch_backward_tile(const BatchInst *bi, int lw,
             batch_brick<TZ_DEEP>(bi, p, lw, lds);
         else
             backward_wave_block<float, BWD_NORM, 32, false>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx,
-                                                            p.nby, p.nbz, nullptr, W_GROUPS, 1, lds);
+                                                            p.nby, p.nbz, nullptr, W_GROUPS, p.sets, lds);
         return;
     }
     if (p.form == BWD_BRICKS) batch_brick<TZ>(bi, p, lw, lds);
     else if (p.tz == 16)
         backward_wave_block<float, BWD_NORM, 16, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
-                                                       p.nbz, nullptr, W_GROUPS, p.sets / W_GROUPS, lds);
+                                                       p.nbz, nullptr, W_GROUPS, p.sets, lds);
     else if (p.tz == 8)
         backward_wave_block<float, BWD_NORM, 8, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
-                                                      p.nbz, nullptr, W_GROUPS, p.sets / W_GROUPS, lds);
+                                                      p.nbz, nullptr, W_GROUPS, p.sets, lds);
     else
         backward_wave_block<float, BWD_NORM, 4, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
-                                                      p.nbz, nullptr, W_GROUPS, p.sets / W_GROUPS, lds);
+                                                      p.nbz, nullptr, W_GROUPS, p.sets, lds);
 }
 
 // Persistent batched r = A^T e: every workgroup takes items from the queue

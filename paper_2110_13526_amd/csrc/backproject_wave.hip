@@ -17,8 +17,9 @@ __global__ __launch_bounds__(1024, sizeof(acc_t<T>) != 4 ? 2 : 5) void k_backwar
 {
     extern __shared__ __align__(16) char lds[];
     if (skip && *skip) return;
+    const int waves = (int)(__builtin_amdgcn_workgroup_size_x() >> 6);
     backward_wave_block<T, EPI, TZB, false>(g, __builtin_amdgcn_workgroup_id_x(), proj, out, out_z, sc, partials, nbx, nby,
-                                            nbz, aux, (int)(__builtin_amdgcn_workgroup_size_x() >> 6), 1, lds);
+                                            nbz, aux, waves, waves, lds);
 }
 
 template <typename T, int EPI>

@@ -256,6 +256,7 @@ struct BwdPlan {
     int64_t nblocks;  // bricks (and partial sums)
 };
 BwdPlan backward_plan(const GeoDev &g, bool single = true);  // a single backprojection's (single: in single precision)
+int wave_sets(int64_t bricks, int most, int views);   // view subsets of the wave form
 BwdPlan tt_backward_plan(const GeoDev &g);            // the TT projector's
 BwdPlan backward_plan_variant(const GeoDev &g, int variant);  // of a batched form's variant
 template <typename T>

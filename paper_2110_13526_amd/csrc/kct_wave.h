@@ -7,7 +7,7 @@
 // the chip and one pass through all views for each; volumes up to 192^3 have
 // 4 to 1728 of them.  Here a brick has a quarter of the columns, its depth
 // follows the shadow (so that one view's shadow is one staged chunk also where
-// a voxel spans several pixels), and the views are dealt to 4, 8 or 16 subsets.
+// a voxel spans several pixels), and the views are dealt to up to 16 subsets.
 //
 // Bounded by VALU issue and, where a voxel spans more than a pixel, by the LDS reads of
 // the records; a quarter to a third of its instructions stage the shadow.  Bricks up
@@ -76,21 +76,23 @@ template <typename E> __device__ __forceinline__ const E *byte_at(const void *ba
     return reinterpret_cast<const E *>(static_cast<const char *>(base) + off);
 }
 
-// Brick w (0 <= w < nbx * nby * nbz) of the backprojection, by a workgroup of
-// `waves` wavefronts (a multiple of W_GROUPS), each taking `subs` view subsets in
-// turn: wavefront v and turn i take views s, s + S, ... with s = v * subs + i and
-// S = waves * subs.  A voxel's S partial sums are added in order within each of
-// W_GROUPS groups of neighbouring subsets, and the groups pairwise, so the sum
-// depends on S alone; the squares of a layer of voxels are added first, then the
-// layers in order, so the partial sum of squares, which goes to partials[w],
-// depends on S alone as well.  lds: wave_lds_bytes(waves) bytes, 16-byte aligned.  MANY: subs may exceed 1, waves is
+// Brick w (0 <= w < nbx * nby * nbz) of the backprojection, by a workgroup of `waves`
+// wavefronts, the views dealt to `sets` subsets (1, 2 or a multiple of W_GROUPS): views
+// s, s + sets, ... are subset s.  With subs = sets / waves (at least 1), wavefront v takes
+// the subsets v * subs, v * subs + 1, ... in turn, so `waves` is sets or a divisor of it
+// (or above it, those beyond without a view).  A voxel's partial sums are added in
+// order within each of W_GROUPS groups of neighbouring subsets (one subset each where
+// there are fewer), and the groups pairwise, so the sum depends on `sets` alone; the
+// squares of a layer of voxels are added first, then the layers in order, so the
+// partial sum of squares, which goes to partials[w], depends on `sets` alone as
+// well.  lds: wave_lds_bytes(waves) bytes, 16-byte aligned.  MANY: subs may exceed 1, waves is
 // W_GROUPS.
 template <typename T, int EPI, int TZB, bool MANY>
 __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, const T *__restrict__ proj,
                                                     T *__restrict__ out, T *__restrict__ out_z,
                                                     const Scalars *__restrict__ sc, double *__restrict__ partials,
                                                     int nbx, int nby, int nbz, const float *__restrict__ aux,
-                                                    int waves, int subs, void *lds)
+                                                    int waves, int sets, void *lds)
 {
     using A = acc_t<T>;
     constexpr bool SQ = EPI == BWD_DIAG || EPI == BWD_DIAG_INV;  // squared weights, e not read
@@ -128,9 +130,9 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
 #pragma unroll
     for (int j = 0; j < TZB; ++j) acc[j] = 0;
 
-    const int nsets = waves * subs;
-    for (int turn = 0; turn < (MANY ? subs : 1); ++turn) {
-        for (int k = (MANY ? wave * subs + turn : wave); k < g.nviews; k += nsets) {
+    const int subs = MANY && sets > waves ? sets / waves : 1;
+    for (int turn = 0; turn < subs; ++turn) {
+        for (int k = wave < sets ? wave * subs + turn : g.nviews; k < g.nviews; k += sets) {
             const ViewParam vp = g.views[k];
             // 1. shadow of the brick, as voxel_columns bounds one voxel's: its
             //    detector columns around the image of its centre, its rows from the
@@ -219,7 +221,7 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
     // every voxel's partial sums through LDS, W_SUMS voxels of each lane at a time:
     // in order within a group, then the groups
     A *mine = reinterpret_cast<A *>(s_pix);
-    const int per = waves / W_GROUPS;
+    const int per = waves > W_GROUPS ? waves / W_GROUPS : 1;
 #pragma unroll
     for (int j0 = 0; j0 < TZB; j0 += W_SUMS) {
         if (j0 > 0) __syncthreads();
@@ -233,6 +235,8 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
             A v[W_GROUPS];
 #pragma unroll
             for (int q = 0; q < W_GROUPS; ++q) {
+                v[q] = 0;
+                if (q * per >= waves) continue;
                 v[q] = reinterpret_cast<const A *>(s_all + q * per * REGION)[at];
                 for (int i = 1; i < per; ++i) v[q] += reinterpret_cast<const A *>(s_all + (q * per + i) * REGION)[at];
             }

@@ -33,14 +33,15 @@ BwdPlan tt_backward_plan(const GeoDev &g)
     p.nbx = (g.nx + WX - 1) / WX;
     p.nby = (g.ny + WY - 1) / WY;
     const float cols = 1.05f * 1.4142f * (float)WX * fmaxf(g.vx, g.vy) * g.ku / g.sid + 3.0f;
+    const int few = 1536 / (g.nviews < 8 ? g.nviews : 8);
     for (p.tz = 16;; p.tz /= 2) {
         if (p.tz > 4 && p.tz / 2 >= g.nz) continue;  // (no deeper than the volume)
         p.nbz = (g.nz + p.tz - 1) / p.tz;
         p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
         const float rows = 1.1f * (float)(p.tz < g.nz ? p.tz : g.nz) * g.vz * g.kv / g.sid + 3.0f;
-        if (p.tz == 4 || (cols * rows <= (float)TTB_CAP && p.nblocks >= 192)) break;
+        if (p.tz == 4 || (cols * rows <= (float)TTB_CAP && p.nblocks >= few)) break;
     }
-    p.sets = p.nblocks > 2048 ? 4 : (p.nblocks > 512 ? 8 : 16);
+    p.sets = wave_sets(p.nblocks, p.nblocks > 2048 ? 4 : (p.nblocks > 512 ? 8 : 16), g.nviews);
     return p;
 }
 
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(1024, 5) void k_backward_tt(GeoDev g, const T *__re
 
     // every voxel's partial sums through LDS, in order within a group of subsets, then the groups
     double sq = 0.0;
-    const int per = waves / W_GROUPS;
+    const int per = waves > W_GROUPS ? waves / W_GROUPS : 1;
 #pragma unroll
     for (int j0 = 0; j0 < TZB; j0 += W_SUMS) {
         if (j0 > 0) __syncthreads();
@@ -166,6 +167,8 @@ __global__ __launch_bounds__(1024, 5) void k_backward_tt(GeoDev g, const T *__re
             float v[W_GROUPS];
 #pragma unroll
             for (int q = 0; q < W_GROUPS; ++q) {
+                v[q] = 0.0f;
+                if (q * per >= waves) continue;
                 v[q] = s_all[q * per * TTB_CAP + at];
                 for (int i = 1; i < per; ++i) v[q] += s_all[(q * per + i) * TTB_CAP + at];
             }

@@ -1,10 +1,11 @@
 """A batched solve returns the separate solve's scalars to the bit, the residual norm
 NR2 of the backprojection's partial sums among them, whatever the number of wavefronts
-a brick's view subsets are dealt to."""
+a brick's view subsets are dealt to, and in the workgroup bricks."""
 import pytest
 
 import kct_inputs as ki
 from tests.gpu_util import dev, geometry, say, torch_mod
+from tests.plan_util import BWD_BRICKS, BWD_DEEP, plan_of
 from tests.test_gpu_forms import FORMS, _cube
 
 pytestmark = pytest.mark.gpu
@@ -14,6 +15,10 @@ GEOMETRIES = {
     "depth_8": [FORMS["8x16"], FORMS["8x8"]],
     "depth_16": [FORMS["16x16"], FORMS["16x8"], _cube(49, 41, 65, 1.0, 40)],
     "depth_32": [FORMS["32x4"]],
+    "few_views": [_cube(49, 41, 51, 1.7, 1), _cube(49, 41, 51, 1.2, 2), _cube(49, 41, 65, 1.0, 3), _cube(33, 29, 21, 3.0, 5),
+                  _cube(125, 123, 121, 0.7, 2)],
+    "bricks": [_cube(131, 129, 115, 1.25, 1), _cube(161, 159, 163, 1.25, 2)],
+    "deep_bricks": [_cube(256, 256, 256, 0.7, 1)],
 }
 
 
@@ -24,6 +29,9 @@ def test_batch_scalars_equal_separate_solves(depth):
     descs = GEOMETRIES[depth]
     geoms = [geometry(g) for g in descs]
     bs = [torch.from_numpy(ki.random_projections(g, 7)).to(dev()).to(torch.float32) for g in descs]
+    for g in descs:
+        if "bricks" in depth:
+            assert plan_of(g)["form"] == {"bricks": BWD_BRICKS, "deep_bricks": BWD_DEEP}[depth]
     batch = kct.Batch(geoms)
     for K in (1, 2, 5):
         xs, infos = batch.cgls(bs, K)

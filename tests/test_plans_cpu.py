@@ -1,29 +1,17 @@
 """The rules that choose a kernel form, evaluated on the host (no GPU calls)."""
-import ctypes
-import math
-
 import pytest
 
-F32, F64 = 0, 3
-SIDDON, TT = 0, 1
-BWD_WAVES, BWD_BRICKS, BWD_DEEP = 0, 1, 2
+import kct_inputs as ki
+from tests.plan_util import BWD_BRICKS, BWD_DEEP, BWD_WAVES, plan_of
 
 
-def plan(n, q, views, dtype="f32", projector="siddon", detector=None):
+def plan(n, q, views, dtype="f32", projector="siddon"):
     """The forms of nx x ny x nz voxels of 120 / max mm with q detector pixels per voxel at the isocentre."""
-    from paper_2110_13526_amd import _lib
-    L = _lib.load()
     nx, ny, nz = n
     v = 120.0 / max(n)
-    nu, nv = detector or (int(1.45 * max(nx, ny) * q) + 3, int(1.1 * nz * q) + 3)
-    vol = _lib.VolumeDesc(nx, ny, nz, v, v, v, 0.0, 0.0, 0.0)
-    cone = _lib.ConeDesc(views, 0.3, 2.0 * math.pi, None, 500.0, 1000.0, nu, nv, 2.0 * v / q, 2.0 * v / q, 0.0, 0.0)
-    out = (ctypes.c_int64 * 8)()
-    code = {"f32": _lib.KCT_F32, "f64": _lib.KCT_F64}[dtype]
-    proj = {"siddon": _lib.PROJECTOR_SIDDON, "tt": _lib.PROJECTOR_TT}[projector]
-    assert L.kct_test_plan(ctypes.byref(vol), ctypes.byref(cone), proj, code, out) == 0
-    keys = ("rows", "divided", "in_place", "fwd_blocks", "form", "tz", "sets", "blocks")
-    return dict(zip(keys, out))
+    g = ki.ConeGeometry(nx, ny, nz, v, v, v, n_views=views, nu=int(1.45 * max(nx, ny) * q) + 3, nv=int(1.1 * nz * q) + 3,
+                        du=2.0 * v / q, dv=2.0 * v / q, angle0=0.3)
+    return plan_of(g, dtype, projector)
 
 
 @pytest.mark.parametrize("projector, dtype", [("siddon", "f32"), ("siddon", "f64"), ("tt", "f32")])
@@ -41,3 +29,22 @@ def test_double_precision_has_no_deep_bricks_for_thin_volumes():
     for layers in (1, 8, 20, 40):
         assert plan((1024, 1024, layers), 0.7, 12, "f64")["form"] != BWD_DEEP
     assert plan((512, 512, 256), 0.7, 12, "f64")["form"] == BWD_DEEP
+
+
+@pytest.mark.parametrize("projector, dtype", [("siddon", "f32"), ("siddon", "f64"), ("tt", "f32")])
+@pytest.mark.parametrize("views", [1, 2, 3, 4, 5, 7, 9, 15, 16, 100])
+def test_no_wavefront_waits_for_views_that_do_not_exist(views, projector, dtype):
+    """Half as many view subsets would not do, and a single view has one."""
+    for n in (12, 48, 96, 192, 256, 400):
+        for q in (0.7, 1.25, 2.2, 6.0):
+            p = plan((n, n, n), q, views, dtype, projector)
+            if p["form"] == BWD_WAVES:
+                assert p["sets"] == 1 or p["sets"] // 2 < views
+                assert p["sets"] in (1, 2, 4, 8, 16)
+
+
+def test_few_views_take_workgroup_bricks():
+    assert plan((256, 256, 256), 1.25, 1)["form"] == BWD_BRICKS
+    assert plan((192, 192, 192), 1.25, 2)["form"] == BWD_BRICKS
+    assert plan((192, 192, 192), 1.25, 180)["form"] == BWD_WAVES
+    assert plan((96, 96, 96), 1.25, 1)["form"] == BWD_WAVES
