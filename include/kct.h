@@ -101,7 +101,7 @@ typedef struct kct_geometry_s *kct_geometry;
  * Errors: KCT_ERR_INVALID_ARG for non-positive sizes or pitches, SDD <= SID, a
  * volume that is not strictly between source and detector, a volume of 2^31
  * voxels or more (or a side above 2^20), projection data of 2^31 rays or more,
- * or a detector of 2^28 pixels or more; KCT_ERR_HIP if the upload fails.
+ * or a detector of 2^28 pixels or 2^27 columns or more; KCT_ERR_HIP if the upload fails.
  * Synchronous. */
 kct_status kct_geometry_create(const kct_volume_desc *vol, const kct_cone_desc *cone, kct_geometry *out);
 

@@ -27,6 +27,9 @@ std::string validate_geometry(const kct_volume_desc &v, const kct_cone_desc &c)
     if ((int64_t)c.n_views * c.nu * c.nv >= (int64_t)1 << 31) return "projection data has 2^31 rays or more";
     // the backprojector addresses one view's projection values by 32-bit byte offsets
     if ((int64_t)c.nu * c.nv >= (int64_t)1 << 28) return "detector has 2^28 pixels or more";
+    // and one view's column parameters; (a projection onto as many columns is beyond the
+    // largest launch, and its column coordinates are beyond single precision)
+    if (c.nu >= 1 << 27) return "detector has 2^27 columns or more";
     if (!finite_pos(c.du) || !finite_pos(c.dv)) return "pixel pitch must be positive";
     if (!finite_pos(c.sid) || !finite_pos(c.sdd)) return "SID and SDD must be positive";
     if (!(c.sdd > c.sid)) return "SDD must exceed SID";

@@ -81,16 +81,18 @@ __host__ __device__ __forceinline__ FwdGrid fwd_grid(const GeoDev &g, int rows_p
 // pairs of one or four groups 1 to 3 % slower, one run per XCD 11 to 20 %.
 constexpr unsigned FWD_PAIR = 2, FWD_VIEWS = 128, FWD_RUN = 128;
 
-// The column group, view and band of workgroup w.
-__device__ __forceinline__ void fwd_tile(const FwdGrid &f, unsigned w, int &cg, int &k, int &band)
+// The column group, view and band of workgroup w.  All products are at most f.nblocks,
+// which a projection of less than 2^31 rays keeps below 2^31.
+__host__ __device__ __forceinline__ void fwd_tile(const FwdGrid &f, unsigned w, int &cg, int &k, int &band)
 {
     const unsigned n = (unsigned)f.nblocks, ncg = (unsigned)f.ncg, nviews = (unsigned)f.nviews;
     const unsigned full = n / (FWD_XCDS * FWD_RUN) * (FWD_XCDS * FWD_RUN);  // the rest keeps its order
     unsigned i = w < full ? (w / (FWD_XCDS * FWD_RUN) * FWD_XCDS + w % FWD_XCDS) * FWD_RUN + w / FWD_XCDS % FWD_RUN : w;
     band = (int)(i / (ncg * nviews));
     i -= (unsigned)band * (ncg * nviews);
-    const unsigned vb = i / (ncg * FWD_VIEWS);
-    i -= vb * (ncg * FWD_VIEWS);
+    const unsigned block = ncg * (nviews < FWD_VIEWS ? nviews : FWD_VIEWS);
+    const unsigned vb = i / block;
+    i -= vb * block;
     const unsigned nv = nviews - vb * FWD_VIEWS < FWD_VIEWS ? nviews - vb * FWD_VIEWS : FWD_VIEWS;
     const unsigned pair = i / (FWD_PAIR * nv);
     i -= pair * (FWD_PAIR * nv);

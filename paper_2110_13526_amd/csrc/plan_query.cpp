@@ -3,6 +3,7 @@
 #include <string>
 #include <vector>
 
+#include "kct_forward.h"
 #include "kct_internal.h"
 
 namespace kct {
@@ -33,4 +34,19 @@ extern "C" kct_status kct_test_plan(const kct_volume_desc *vol, const kct_cone_d
     const int64_t v[8] = {f.rows, f.divided, forward_in_place(g), forward_num_blocks(g), b.form, b.tz, b.sets, b.nblocks};
     for (int i = 0; i < 8; ++i) out[i] = v[i];
     return KCT_OK;
+}
+
+// out: column group, view and row band of workgroup w of a forward projection with
+// `rows` detector rows per lane.
+extern "C" void kct_test_forward_tile(int32_t nu, int32_t nv, int32_t views, int32_t rows, int64_t w, int64_t out[3])
+{
+    GeoDev g{};
+    g.nu = nu;
+    g.nv = nv;
+    g.nviews = views;
+    int cg, k, band;
+    fwd_tile(fwd_grid(g, rows), (unsigned)w, cg, k, band);
+    out[0] = cg;
+    out[1] = k;
+    out[2] = band;
 }
