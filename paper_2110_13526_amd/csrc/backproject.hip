@@ -112,8 +112,9 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
                     const int r0 = (int)(((float)tid + 0.5f) * rn), c = (int)tid - r0 * ncol;
                     if (r0 < step) {
                         // all addressed as a uniform base plus a 32-bit byte offset (one
-                        // view's projection values span < 2^31 bytes: a detector has
-                        // < 2^28 pixels)
+                        // view's projection values span < 2^31 bytes, the row parameters
+                        // and one view's column parameters < 2^32: a detector has < 2^28
+                        // pixels and < 2^27 columns)
                         const ColParam cp = *byte_at<ColParam>(ck, (unsigned)(cu0 + c) * (unsigned)sizeof(ColParam));
                         if (r0 == 0) s_col[c] = stage_column(g, vp.dom, cp);
                         unsigned pix = ((unsigned)(cv0 + r0) * (unsigned)g.nu + (unsigned)(cu0 + c)) * (unsigned)sizeof(T);
@@ -256,6 +257,7 @@ static BwdPlan wave_plan(const GeoDev &g, bool single)
         if (p.tz / 2 >= g.nz) continue;
         const float records = cols * (shadow_rows(g, p.tz) + 1.0f);
         p.nbz = (g.nz + p.tz - 1) / p.tz;
+        if (p.tz == 32 && 4 * g.nz < 3 * 32 * p.nbz) continue;  // all 32 layers are taken (layer_test)
         p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
         const float over = p.tz == 8 ? 1.3f : (p.tz == 16 && single ? 1.1f : 1.0f);
         if (records <= over * (float)wave_cap(single && split_records<float>(p.tz)) && p.nblocks >= (p.tz == 32 && few < 1024 ? 1024 : few))
@@ -349,7 +351,7 @@ __device__ __forceinline__ void batch_backward_tile(const BatchInst *bi, int lw,
         if (p.form == BWD_DEEP)
             batch_brick<TZ_DEEP>(bi, p, lw, lds);
         else
-            backward_wave_block<float, BWD_NORM, 32, false>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx,
+            backward_wave_block<float, BWD_NORM, 32, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx,
                                                             p.nby, p.nbz, nullptr, W_GROUPS, p.sets, lds);
         return;
     }

@@ -60,9 +60,12 @@ constexpr int NH = 2;                      // detector columns held in registers
 // Double precision in bricks up to 16 deep: groups of 2, which cost full bricks nothing
 // there (groups of 4 / 2 / 1: 1024^2 x 1 at 1.25 pixels per voxel, 8 views 78.6 / 67.3 / 69.2,
 // 60 views 561 / 476 / 484; 256^3 x 20 657 / 658 / 684; 32-deep, 128^3 x 60 89.8 / 97.2 / 103).
-template <typename A> __host__ __device__ constexpr bool layer_test(int j, int tzb)
+// Bricks of 32 layers by wavefronts: no test (128^3 x 720, groups of 4 / 16 / no test 1368 / 1371 /
+// 1349); volumes that would fill less than three quarters of them take shallower ones.
+template <typename A> __host__ __device__ constexpr bool layer_test(int j, int tzb, bool waves)
 {
-    return j > 0 && j % (sizeof(A) == 8 && tzb < TZ_DEEP ? 2 : 4) == 0;
+    if (j == 0 || (tzb == TZ_DEEP && waves)) return false;
+    return j % (sizeof(A) == 8 && tzb < TZ_DEEP ? 2 : 4) == 0;
 }
 
 struct ColStage {  // per staged detector column: in-plane ray parameters
@@ -417,7 +420,7 @@ __host__ __device__ __forceinline__ void voxel_rows(const PixStage<A, SPLIT> *pg
     }
 #pragma unroll
     for (int j = 0; j < TZN; ++j) {
-        if (layer_test<A>(j, TZN) && j >= layers) break;
+        if (layer_test<A>(j, TZN, CHC == 0) && j >= layers) break;
         const float mb1 = mb + 1.0f;
         // candidate rows va + 1 .. vb + 1: floor(lo) + 1 is ceil(lo) except at an
         // integer lo, whose row lies 0.01 below the true bound and is rightly left out

@@ -85,9 +85,9 @@ template <typename E> __device__ __forceinline__ const E *byte_at(const void *ba
 // there are fewer), and the groups pairwise, so the sum depends on `sets` alone; the
 // squares of a layer of voxels are added first, then the layers in order, so the
 // partial sum of squares, which goes to partials[w], depends on `sets` alone as
-// well.  lds: wave_lds_bytes(waves) bytes, 16-byte aligned.  MANY: subs may exceed 1, waves is
-// W_GROUPS.
-template <typename T, int EPI, int TZB, bool MANY>
+// well.  lds: wave_lds_bytes(waves) bytes, 16-byte aligned.  BATCH: waves is
+// W_GROUPS; else it is sets.
+template <typename T, int EPI, int TZB, bool BATCH>
 __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, const T *__restrict__ proj,
                                                     T *__restrict__ out, T *__restrict__ out_z,
                                                     const Scalars *__restrict__ sc, double *__restrict__ partials,
@@ -126,13 +126,14 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
     const float xc = g.x0 + (float)(bx * WX) * g.vx + ex, yc = g.y0 + (float)(by * WY) * g.vy + ey;
     const float wz0 = g.z0 + (float)iz0 * g.vz, wz1 = g.z0 + (float)(iz0 + nzb) * g.vz;
 
+    constexpr bool MANY = BATCH && TZB < TZ_DEEP;  // a wavefront may take several subsets
     A acc[TZB], sum[MANY ? TZB : 1];
 #pragma unroll
     for (int j = 0; j < TZB; ++j) acc[j] = 0;
 
     const int subs = MANY && sets > waves ? sets / waves : 1;
     for (int turn = 0; turn < subs; ++turn) {
-        for (int k = wave < sets ? wave * subs + turn : g.nviews; k < g.nviews; k += sets) {
+        for (int k = !BATCH ? wave : (wave < sets ? wave * subs + turn : g.nviews); k < g.nviews; k += BATCH ? sets : waves) {
             const ViewParam vp = g.views[k];
             // 1. shadow of the brick, as voxel_columns bounds one voxel's: its
             //    detector columns around the image of its centre, its rows from the
