@@ -232,6 +232,19 @@ int wave_sets(int64_t bricks, int most, int views)
     return chosen;
 }
 
+// Bricks and view subsets that one launch can hold (a grid has less than 2^32
+// threads): fewer subsets, then deeper bricks, for the flattest of the largest volumes.
+void wave_fit_launch(const GeoDev &g, BwdPlan &p)
+{
+    for (;;) {
+        p.nbz = (g.nz + p.tz - 1) / p.tz;
+        p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
+        if (p.nblocks * 64 * p.sets < (int64_t)1 << 32) return;
+        if (p.sets > 1) p.sets /= 2;
+        else p.tz *= 2;
+    }
+}
+
 // Wave form: the deepest brick whose shadow is expected to fit one chunk (or nearly so:
 // a second chunk now and then costs less than shallower bricks) and that leaves enough
 // bricks, and as many view subsets as fill the chip.  Measured (us, cube of n voxels, q
@@ -269,6 +282,7 @@ static BwdPlan wave_plan(const GeoDev &g, bool single)
     // sums would not fit its registers)
     const int most = p.tz == 32 || p.nblocks > (single ? 8192 : 2048) ? 4 : (p.nblocks > 512 ? 8 : 16);
     p.sets = wave_sets(p.nblocks, most, g.nviews);
+    wave_fit_launch(g, p);
     return p;
 }
 

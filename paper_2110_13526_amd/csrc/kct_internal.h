@@ -257,6 +257,7 @@ struct BwdPlan {
 };
 BwdPlan backward_plan(const GeoDev &g, bool single = true);  // a single backprojection's (single: in single precision)
 int wave_sets(int64_t bricks, int most, int views);   // view subsets of the wave form
+void wave_fit_launch(const GeoDev &g, BwdPlan &p);
 BwdPlan tt_backward_plan(const GeoDev &g);            // the TT projector's
 BwdPlan backward_plan_variant(const GeoDev &g, int variant);  // of a batched form's variant
 template <typename T>

@@ -42,6 +42,7 @@ BwdPlan tt_backward_plan(const GeoDev &g)
         if (p.tz == 4 || (cols * rows <= (float)TTB_CAP && p.nblocks >= few)) break;
     }
     p.sets = wave_sets(p.nblocks, p.nblocks > 2048 ? 4 : (p.nblocks > 512 ? 8 : 16), g.nviews);
+    wave_fit_launch(g, p);
     return p;
 }
 

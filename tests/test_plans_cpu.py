@@ -88,3 +88,21 @@ def test_detectors_beyond_the_column_offsets_are_refused():
     cone = _lib.ConeDesc(1, 0.0, 6.28, None, 500.0, 1000.0, 2**27, 1, 1e-6, 1.0, 0.0, 0.0)
     assert _lib.load().kct_test_plan(ctypes.byref(vol), ctypes.byref(cone), 0, _lib.KCT_F32, out) == 1
     assert b"2^27 columns" in _lib.load().kct_last_error()
+
+
+def thin(nx, ny, nz, q, views=8):
+    """A volume of at most 116 mm on a truncated 512 x 512 detector, q pixels per voxel."""
+    v = 116.0 / max(nx, ny, nz)
+    return ki.ConeGeometry(nx, ny, nz, v, v, v, n_views=views, nu=512, nv=512, du=2.0 * v / q, dv=2.0 * v / q, angle0=0.3)
+
+
+@pytest.mark.parametrize("projector, dtype", [("siddon", "f32"), ("siddon", "f64"), ("tt", "f32")])
+@pytest.mark.parametrize("n", [(1, 46340, 46340), (46340, 46340, 1), (1, 2**20, 2047), (2**20, 1, 2047), (2**20, 2047, 1),
+                               (1, 2047, 2**20), (1290, 1290, 1290), (3, 26000, 26000), (1, 23170, 23170)])
+def test_bricks_fit_one_launch(n, projector, dtype):
+    """A grid has less than 2^32 threads."""
+    for q in (0.7, 2.5, 3.2, 9.0):
+        for views in (1, 2, 8):
+            p = plan_of(thin(*n, q, views), dtype, projector)
+            assert p["blocks"] * (64 * p["sets"] if p["form"] == BWD_WAVES else 256) < 2**32
+            assert p["tz"] <= (16 if projector == "tt" else 32)
