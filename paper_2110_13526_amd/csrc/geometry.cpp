@@ -87,18 +87,8 @@ kct_status geometry_tables(const kct_volume_desc &vol, const kct_cone_desc &cone
     const double ox = vol.cx + (hx - 0.5 * vol.nx) * vol.vx, oy = vol.cy + (hy - 0.5 * vol.ny) * vol.vy;
     const double oz = vol.cz + (hz - 0.5 * vol.nz) * vol.vz;
 
-    for (int iv = 0; iv < nv; ++iv) {
-        double qz = ((double)iv - 0.5 * (nv - 1)) * cone.dv + cone.off_v;
-        rows[iv].qz = (float)qz;
-        rows[iv].inv_qz = qz != 0.0 ? (float)(1.0 / qz) : 0.0f;
-        const float zc = (float)(oz / vol.vz);
-        const bool par = rows[iv].inv_qz == 0.0f;
-        rows[iv].s_inv = par ? PAR_INV_QZ : rows[iv].inv_qz;
-        // a parallel row lies in z-cell floor(hz - zc): moved to its middle
-        rows[iv].s_off = par ? (std::floor(-zc + (float)hz) - (float)hz) + 0.5f : -zc;
-    }
-
     double least_depth = INFINITY;  // of a volume corner, in any view
+    float most_kz = 0.0f;           // of any column
     for (int k = 0; k < nk; ++k) {
         const double t = view_angle(cone, k);
         const double c = std::cos(t), s = std::sin(t);
@@ -150,10 +140,25 @@ kct_status geometry_tables(const kct_volume_desc &vol, const kct_cone_desc &cone
             if (cp.inv_a == 0.0f) cp.a = 0.0f;
             cp.tcv = (float)(t_c / vol.vz);
             cp.kz = (float)(vol.vz / gp);
+            most_kz = std::max(most_kz, std::fabs(cp.kz));
             cp.gp = (float)gp;
             cp.lxy2 = (float)(vxi * vxi * (1.0 + slope * slope));
             cp.pad = 0.0f;
         }
+    }
+
+    // Rows parallel to the z-planes get the slope PAR_INV in the steepest column and
+    // at least its share of kz elsewhere, whatever the unit of length.
+    const float zc = (float)(oz / vol.vz);
+    const float par_inv = (float)std::min((double)PAR_INV / (double)most_kz, 1.0e38);
+    for (int iv = 0; iv < nv; ++iv) {
+        const double qz = ((double)iv - 0.5 * (nv - 1)) * cone.dv + cone.off_v;
+        rows[iv].qz = (float)qz;
+        rows[iv].inv_qz = qz != 0.0 ? (float)(1.0 / qz) : 0.0f;
+        const bool par = rows[iv].inv_qz == 0.0f;
+        rows[iv].s_inv = par ? par_inv : rows[iv].inv_qz;
+        // a parallel row lies in z-cell floor(hz - zc): moved to its middle
+        rows[iv].s_off = par ? (std::floor(-zc + (float)hz) - (float)hz) + 0.5f : -zc;
     }
 
     d.nx = vol.nx;

@@ -75,14 +75,13 @@ struct ColStage {  // per staged detector column: in-plane ray parameters
 };
 
 // Rays parallel to a family of planes are staged as if they crossed them at a
-// very steep slope (PAR_INV; for rows PAR_INV_QZ * kz), with their coordinate on
+// very steep slope (PAR_INV, in kct_internal.h), with their coordinate on
 // that axis moved to the middle of the cell they lie in: every plane is then
 // crossed at least half that far from the origin, far outside any xi-interval
 // (finite, so the two crossings of a cell never give inf - inf), and the general
 // crossing formula gives exactly the parallel-ray intervals of kct_weights.h:
 // everything inside the ray's cell, nothing elsewhere.  Staged records and
 // columns therefore need no parallel case.
-constexpr float PAR_INV = 1.0e30f;
 
 // Per staged pixel: its ray's zeta_offset nzc (from zeta at xi = 0: zeta_centre and
 // zeta_inv_slope of its row and column; rows whose rays are parallel to the z-planes

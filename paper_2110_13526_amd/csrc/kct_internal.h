@@ -50,13 +50,14 @@ struct RowParam {    // per detector row
     float qz;        // z of the pixel centre [mm] (the source is at z = 0)
     float inv_qz;    // 1 / qz, 0 when qz == 0
     // the same for the backprojector's staging, which gives rows parallel to the
-    // z-planes a finite steep slope (PAR_INV_QZ, see kct_gather.h): zeta at xi = 0 is
+    // z-planes a finite steep slope (PAR_INV, see kct_gather.h): zeta at xi = 0 is
     // qz * tcv + s_off and d xi / d zeta is s_inv * kz
     float s_inv, s_off;
 };
 
-// d xi / d zeta of a parallel row is this times kz (of order 10^2 to 10^4)
-constexpr float PAR_INV_QZ = 1.0e27f;
+// d xi per crossed plane that stands for a ray parallel to the planes (kct_gather.h):
+// for a row, s_inv times the largest kz of the geometry
+constexpr float PAR_INV = 1.0e30f;
 
 struct ViewParam {   // per view
     float sx, sy;    // source position [mm]
