@@ -219,6 +219,14 @@ __host__ __device__ __forceinline__ void tt_pixels(float t0, float t3, int &a, i
     b = (int)floorf(t3 + 0.5f);
 }
 
+// The same without the pixels that (t0, t3) only touches, whose mean is 0 (and 0 times
+// a value that is not finite would be added).
+__host__ __device__ __forceinline__ void tt_met_pixels(float t0, float t3, int &a, int &b)
+{
+    a = (int)floorf(t0 + 0.5f);
+    b = (int)ceilf(t3 - 0.5f);
+}
+
 // In-plane line through the source and the detector point at column coordinate
 // uc, in the view's dominant frame of voxel indices (kct_internal.h): eta = e0 + e1 xi.
 __host__ __device__ __forceinline__ void tt_edge_line(const GeoDev &g, const ViewParam &vp, float uc, float &e0, float &e1)
@@ -382,7 +390,7 @@ __host__ __device__ __forceinline__ void tt_gather_ramps(const GeoDev &g, int iz
                                                          int layers, A (&acc)[TZN])
 {
     int ua, ub;
-    tt_pixels(t[0], t[3], ua, ub);
+    tt_met_pixels(t[0], t[3], ua, ub);
     ua = ua < cu0 ? cu0 : ua;
     ub = ub > cu0 + ncol - 1 ? cu0 + ncol - 1 : ub;
     const int vmax = cv0 + nrow - 1;
@@ -407,7 +415,7 @@ __host__ __device__ __forceinline__ void tt_gather_ramps(const GeoDev &g, int iz
             TTRamp a, b;
             tt_layer_ramps<OVERLAP>(p0, p1, a, b);
             int va, vb;
-            tt_pixels(a.lo, b.hi, va, vb);
+            tt_met_pixels(a.lo, b.hi, va, vb);
             va = va < cv0 ? cv0 : va;
             vb = vb > vmax ? vmax : vb;
             const A *lrow = s_le + (va - cv0) * stride + (c0 - cu0);
