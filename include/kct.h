@@ -271,8 +271,8 @@ kct_status kct_batch_workspace_size(kct_batch b, size_t *bytes);
  * each for the batch's solves (a tuned instance may then differ from its own
  * kct_cgls_solve by the rounding of regrouped partial sums).  cache_path
  * (host, optional): a text file of "<sizes> <rows per lane> <brick shape>"
- * lines; instances whose sizes are listed are not timed, new choices are
- * appended.  ws is scratch (kct_batch_workspace_size bytes, contents
+ * lines (sizes: the counts and the voxel's extent in pixels at the isocentre);
+ * instances whose sizes are listed are not timed, new choices are appended.  ws is scratch (kct_batch_workspace_size bytes, contents
  * overwritten).  Synchronous.  Errors: INVALID_ARG, WORKSPACE, HIP. */
 kct_status kct_batch_tune(kct_batch b, void *ws, size_t ws_bytes, const char *cache_path, hipStream_t stream);
 

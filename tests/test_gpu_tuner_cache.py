@@ -1,0 +1,39 @@
+"""The batched form's tuner keeps its choices by what they depend on: voxels of another
+width in pixels are another choice, and choices of an older file format are not taken."""
+import pytest
+
+from tests.gpu_util import geometry
+from tests.test_gpu_forms import _cube
+
+pytestmark = pytest.mark.gpu
+
+
+def _lines(path):
+    return [ln.split() for ln in open(path).read().splitlines() if ln.strip()]
+
+
+def test_equal_counts_of_another_magnification(tmp_path):
+    import paper_2110_13526_amd as kct
+    a = _cube(48, 48, 48, 1.0, 9)
+    b = type(a)(**{**{f: getattr(a, f) for f in kct.Geometry.FIELDS}, "du": a.du / 2, "dv": a.dv / 2})
+    assert a.proj_shape == b.proj_shape
+    cache = str(tmp_path / "tune.txt")
+    batch = kct.Batch([geometry(a), geometry(b), geometry(a)])
+    batch.tune(cache=cache)
+    batch.close()
+    assert len({ln[0] for ln in _lines(cache)}) == len(_lines(cache)) == 2
+
+
+def test_older_lines_are_not_taken(tmp_path):
+    import paper_2110_13526_amd as kct
+    g = _cube(48, 48, 48, 1.0, 9)
+    cache = str(tmp_path / "tune.txt")
+    old = f"{g.nx}x{g.ny}x{g.nz}/{g.n_views}x{g.nv}x{g.nu} 1 1\n"
+    open(cache, "w").write(old)
+    for _ in range(2):  # the second reads what the first appended
+        batch = kct.Batch([geometry(g)])
+        batch.tune(cache=cache)
+        batch.close()
+        lines = _lines(cache)
+        assert open(cache).read().startswith(old) and len(lines) == 2
+        assert lines[1][0] != lines[0][0] and lines[1][1] in "1234" and lines[1][2] in "01"
