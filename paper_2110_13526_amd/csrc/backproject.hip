@@ -415,12 +415,14 @@ hipError_t batch_backward_occupancy(int &per_cu, int &per_cu_deep)
     return e != hipSuccess ? e : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_deep, kp_backward<true>, 256, 0);
 }
 
-// off and off_deep: the items of the instances of either kernel; q[0] and q[1] their queues.
+// off and off_deep: the items of the instances of either kernel; q[0] and q[1] their queues.  A
+// kernel without instances (grid 0) is not launched.
 hipError_t launch_batch_backward(const BatchInst *B, const int64_t *off, const int64_t *off_deep, int count, BatchQueue *q,
                                  int grid, int grid_deep, hipStream_t st)
 {
-    hipLaunchKernelGGL(kp_backward<true>, dim3((unsigned)grid_deep), dim3(256), 0, st, B, off_deep, count, q + 1);
-    hipLaunchKernelGGL(kp_backward<false>, dim3((unsigned)grid), dim3(256), 0, st, B, off, count, q);
+    if (grid_deep > 0)
+        hipLaunchKernelGGL(kp_backward<true>, dim3((unsigned)grid_deep), dim3(256), 0, st, B, off_deep, count, q + 1);
+    if (grid > 0) hipLaunchKernelGGL(kp_backward<false>, dim3((unsigned)grid), dim3(256), 0, st, B, off, count, q);
     return hipGetLastError();
 }
 

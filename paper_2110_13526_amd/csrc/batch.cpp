@@ -42,9 +42,11 @@ struct Batch {
     hipStream_t stream = nullptr;
     hipEvent_t ev = nullptr;
     int grid_fwd = 0, grid_bwd = 0, grid_deep = 0, grid_dir = 0;  // resident workgroups of the persistent steps
-    // the recorded iteration (valid for the workspace it was recorded with)
+    // the recorded iteration (valid for the workspace it was recorded with and the
+    // backprojection kernels that its instances take, a bit each)
     hipGraphExec_t exec = nullptr;
     const void *exec_ws = nullptr;
+    int exec_bwd = 0;
     // device-clock stamps of the last solve, per instance (set-up, completion)
     std::vector<unsigned long long> t_start, t_done;
 };
@@ -141,13 +143,22 @@ kct_status check_batch(kct_batch h, const char *fn, Batch *&b)
     return KCT_OK;
 }
 
+// r = A^T e of every instance; bwd: the kernels that have instances (1: kp_backward<false>,
+// 2: kp_backward<true>).
+hipError_t batch_backward(const Batch *b, const BatchInst *T, const int64_t *off, BatchQueue *q, int c, int bwd,
+                          hipStream_t st)
+{
+    return launch_batch_backward(T, off + BG_BWD * (c + 1), off + BG_DEEP * (c + 1), c, q, (bwd & 1) ? b->grid_bwd : 0,
+                                 (bwd & 2) ? b->grid_deep : 0, st);
+}
+
 // One batched iteration after the init block: r = A^T e, beta, d = r + beta d,
 // p = A d, alpha, x += alpha d, e -= alpha p, NB.
-hipError_t batch_iteration(const Batch *b, const BatchInst *T, const int64_t *off, BatchQueue *q, int c,
+hipError_t batch_iteration(const Batch *b, const BatchInst *T, const int64_t *off, BatchQueue *q, int c, int bwd,
                            hipStream_t st)
 {
     hipError_t e;
-    if ((e = launch_batch_backward(T, off + BG_BWD * (c + 1), off + BG_DEEP * (c + 1), c, q, b->grid_bwd, b->grid_deep, st)) != hipSuccess) return e;
+    if ((e = batch_backward(b, T, off, q, c, bwd, st)) != hipSuccess) return e;
     if ((e = launch_batch_finalize(T, c, F_BETA, BG_BWD, st)) != hipSuccess) return e;
     if ((e = launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 2, b->grid_dir, 0, st)) != hipSuccess) return e;
     if ((e = launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 3, b->grid_fwd, st)) != hipSuccess) return e;
@@ -407,7 +418,8 @@ kct_status kct_batch_cgls_solve(kct_batch h, const float *const *bs, float *cons
     KCT_BTRY(launch_batch_vec(T, c, BV_NORM_B, 0, 0.0, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_NB0, BG_STREAM, st));
     KCT_BTRY(launch_batch_vec(T, c, BV_X0_E, 0, 0.0, st));
-    KCT_BTRY(launch_batch_backward(T, off + BG_BWD * (c + 1), off + BG_DEEP * (c + 1), c, q, b->grid_bwd, b->grid_deep, st));
+    const int bwd = (offs[BG_BWD * (c + 1) + c] > 0 ? 1 : 0) | (offs[BG_DEEP * (c + 1) + c] > 0 ? 2 : 0);
+    KCT_BTRY(batch_backward(b, T, off, q, c, bwd, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_NR2_INIT, BG_BWD, st));
     KCT_BTRY(launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 2, b->grid_dir, 1, st));
     KCT_BTRY(launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 3, b->grid_fwd, st));
@@ -417,12 +429,13 @@ kct_status kct_batch_cgls_solve(kct_batch h, const float *const *bs, float *cons
     if (K > 1) {
         if (use_graph) {
             // the iteration's launches depend only on the workspace (tables, queues,
-            // instance blocks) and the count: recorded once per workspace
-            if (!b->exec || b->exec_ws != ws) {
+            // instance blocks), the count and the backprojection kernels: recorded once per
+            // workspace, and anew where a tuning changed the last
+            if (!b->exec || b->exec_ws != ws || b->exec_bwd != bwd) {
                 drop_graph(b);
                 hipGraph_t graph = nullptr;
                 KCT_BTRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-                const hipError_t ce = batch_iteration(b, T, off, q, c, st);
+                const hipError_t ce = batch_iteration(b, T, off, q, c, bwd, st);
                 const hipError_t ee = hipStreamEndCapture(st, &graph);
                 hipError_t ie = ce != hipSuccess ? ce : ee;
                 if (ie == hipSuccess) ie = hipGraphInstantiate(&b->exec, graph, nullptr, nullptr, 0);
@@ -432,13 +445,14 @@ kct_status kct_batch_cgls_solve(kct_batch h, const float *const *bs, float *cons
                     return fail(fn, std::string("graph capture failed: ") + hipGetErrorString(ie), KCT_ERR_HIP);
                 }
                 b->exec_ws = ws;
+                b->exec_bwd = bwd;
             }
             hipError_t ie = hipSuccess;
             for (int it = 1; it < K && ie == hipSuccess; ++it) ie = hipGraphLaunch(b->exec, st);
             if (ie == hipSuccess) ie = hipStreamSynchronize(st);
             if (ie != hipSuccess) return fail(fn, std::string("graph replay failed: ") + hipGetErrorString(ie), KCT_ERR_HIP);
         } else {
-            for (int it = 1; it < K; ++it) KCT_BTRY(batch_iteration(b, T, off, q, c, st));
+            for (int it = 1; it < K; ++it) KCT_BTRY(batch_iteration(b, T, off, q, c, bwd, st));
         }
     }
     // results
