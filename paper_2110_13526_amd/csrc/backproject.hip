@@ -393,8 +393,9 @@ __global__ __launch_bounds__(256, DEEP ? 5 : 6) void kp_backward(const BatchInst
 {
     __shared__ __align__(16) char lds[batch_lds_bytes(DEEP)];
     const int64_t total = off[count];
+    unsigned passed = 0;
     for (;;) {
-        const int64_t item = batch_pop(q, total);
+        const int64_t item = batch_pop(q, total, passed);
         if (item >= total) break;
         const int i = batch_find(off, count, item);
         const BatchInst *bi = B + i;

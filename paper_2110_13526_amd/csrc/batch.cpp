@@ -33,6 +33,13 @@ namespace kct {
 
 void set_error(const std::string &msg);
 
+// Workgroups of an iteration's persistent launches: no more than the device holds at
+// once, nor than there are items (0: a kernel that no instance takes).
+struct BatchGrids {
+    int fwd = 0, bwd = 0, deep = 0, dir = 0;
+    bool operator==(const BatchGrids &o) const { return fwd == o.fwd && bwd == o.bwd && deep == o.deep && dir == o.dir; }
+};
+
 struct Batch {
     std::vector<const Geometry *> geoms;
     std::vector<int> fwd_r;   // per instance, detector rows per lane (1 to 4)
@@ -41,12 +48,11 @@ struct Batch {
     int device = -1;
     hipStream_t stream = nullptr;
     hipEvent_t ev = nullptr;
-    int grid_fwd = 0, grid_bwd = 0, grid_deep = 0, grid_dir = 0;  // resident workgroups of the persistent steps
-    // the recorded iteration (valid for the workspace it was recorded with and the
-    // backprojection kernels that its instances take, a bit each)
+    BatchGrids resident;  // workgroups of each persistent kernel that the device holds at once
+    // the recorded iteration (valid for the workspace and the launches it was recorded with)
     hipGraphExec_t exec = nullptr;
     const void *exec_ws = nullptr;
-    int exec_bwd = 0;
+    BatchGrids exec_grids;
     // device-clock stamps of the last solve, per instance (set-up, completion)
     std::vector<unsigned long long> t_start, t_done;
 };
@@ -143,25 +149,20 @@ kct_status check_batch(kct_batch h, const char *fn, Batch *&b)
     return KCT_OK;
 }
 
-// r = A^T e of every instance; bwd: the kernels that have instances (1: kp_backward<false>,
-// 2: kp_backward<true>).
-hipError_t batch_backward(const Batch *b, const BatchInst *T, const int64_t *off, BatchQueue *q, int c, int bwd,
-                          hipStream_t st)
+hipError_t batch_backward(const BatchInst *T, const int64_t *off, BatchQueue *q, int c, const BatchGrids &n, hipStream_t st)
 {
-    return launch_batch_backward(T, off + BG_BWD * (c + 1), off + BG_DEEP * (c + 1), c, q, (bwd & 1) ? b->grid_bwd : 0,
-                                 (bwd & 2) ? b->grid_deep : 0, st);
+    return launch_batch_backward(T, off + BG_BWD * (c + 1), off + BG_DEEP * (c + 1), c, q, n.bwd, n.deep, st);
 }
 
 // One batched iteration after the init block: r = A^T e, beta, d = r + beta d,
 // p = A d, alpha, x += alpha d, e -= alpha p, NB.
-hipError_t batch_iteration(const Batch *b, const BatchInst *T, const int64_t *off, BatchQueue *q, int c, int bwd,
-                           hipStream_t st)
+hipError_t batch_iteration(const BatchInst *T, const int64_t *off, BatchQueue *q, int c, const BatchGrids &n, hipStream_t st)
 {
     hipError_t e;
-    if ((e = batch_backward(b, T, off, q, c, bwd, st)) != hipSuccess) return e;
+    if ((e = batch_backward(T, off, q, c, n, st)) != hipSuccess) return e;
     if ((e = launch_batch_finalize(T, c, F_BETA, BG_BWD, st)) != hipSuccess) return e;
-    if ((e = launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 2, b->grid_dir, 0, st)) != hipSuccess) return e;
-    if ((e = launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 3, b->grid_fwd, st)) != hipSuccess) return e;
+    if ((e = launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 2, n.dir, 0, st)) != hipSuccess) return e;
+    if ((e = launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 3, n.fwd, st)) != hipSuccess) return e;
     if ((e = launch_batch_finalize(T, c, F_ALPHA, BG_FWD, st)) != hipSuccess) return e;
     if ((e = launch_batch_vec(T, c, BV_CGLS_XE, 0, 0.0, st)) != hipSuccess) return e;
     return launch_batch_finalize(T, c, F_NB, BG_STREAM, st);
@@ -203,7 +204,7 @@ kct_status kct_batch_create(const kct_geometry *geoms, int32_t count, kct_batch 
         b->bwd_v.push_back(backward_default_variant(g->dev));
         b->order.push_back(i);
     }
-    if (batch_persistent_grids(b->grid_fwd, b->grid_bwd, b->grid_deep, b->grid_dir) != hipSuccess) {
+    if (batch_persistent_grids(b->resident.fwd, b->resident.bwd, b->resident.deep, b->resident.dir) != hipSuccess) {
         delete b;
         return fail(fn, "occupancy query of the persistent kernels failed", KCT_ERR_HIP);
     }
@@ -418,24 +419,29 @@ kct_status kct_batch_cgls_solve(kct_batch h, const float *const *bs, float *cons
     KCT_BTRY(launch_batch_vec(T, c, BV_NORM_B, 0, 0.0, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_NB0, BG_STREAM, st));
     KCT_BTRY(launch_batch_vec(T, c, BV_X0_E, 0, 0.0, st));
-    const int bwd = (offs[BG_BWD * (c + 1) + c] > 0 ? 1 : 0) | (offs[BG_DEEP * (c + 1) + c] > 0 ? 2 : 0);
-    KCT_BTRY(batch_backward(b, T, off, q, c, bwd, st));
+    auto grid = [&](int resident, int kind) { return (int)std::min<int64_t>(resident, offs[kind * (c + 1) + c]); };
+    BatchGrids n;
+    n.fwd = grid(b->resident.fwd, BG_FWD);
+    n.bwd = grid(b->resident.bwd, BG_BWD);
+    n.deep = grid(b->resident.deep, BG_DEEP);
+    n.dir = grid(b->resident.dir, BG_DIR);
+    KCT_BTRY(batch_backward(T, off, q, c, n, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_NR2_INIT, BG_BWD, st));
-    KCT_BTRY(launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 2, b->grid_dir, 1, st));
-    KCT_BTRY(launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 3, b->grid_fwd, st));
+    KCT_BTRY(launch_batch_dir(T, off + BG_DIR * (c + 1), c, q + 2, n.dir, 1, st));
+    KCT_BTRY(launch_batch_forward(T, off + BG_FWD * (c + 1), c, q + 3, n.fwd, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_ALPHA, BG_FWD, st));
     KCT_BTRY(launch_batch_vec(T, c, BV_CGLS_XE, 0, 0.0, st));
     KCT_BTRY(launch_batch_finalize(T, c, F_NB, BG_STREAM, st));
     if (K > 1) {
         if (use_graph) {
             // the iteration's launches depend only on the workspace (tables, queues,
-            // instance blocks), the count and the backprojection kernels: recorded once per
-            // workspace, and anew where a tuning changed the last
-            if (!b->exec || b->exec_ws != ws || b->exec_bwd != bwd) {
+            // instance blocks), the count and the grids: recorded once per workspace, and
+            // anew where a tuning changed the grids
+            if (!b->exec || b->exec_ws != ws || !(b->exec_grids == n)) {
                 drop_graph(b);
                 hipGraph_t graph = nullptr;
                 KCT_BTRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-                const hipError_t ce = batch_iteration(b, T, off, q, c, bwd, st);
+                const hipError_t ce = batch_iteration(T, off, q, c, n, st);
                 const hipError_t ee = hipStreamEndCapture(st, &graph);
                 hipError_t ie = ce != hipSuccess ? ce : ee;
                 if (ie == hipSuccess) ie = hipGraphInstantiate(&b->exec, graph, nullptr, nullptr, 0);
@@ -445,14 +451,14 @@ kct_status kct_batch_cgls_solve(kct_batch h, const float *const *bs, float *cons
                     return fail(fn, std::string("graph capture failed: ") + hipGetErrorString(ie), KCT_ERR_HIP);
                 }
                 b->exec_ws = ws;
-                b->exec_bwd = bwd;
+                b->exec_grids = n;
             }
             hipError_t ie = hipSuccess;
             for (int it = 1; it < K && ie == hipSuccess; ++it) ie = hipGraphLaunch(b->exec, st);
             if (ie == hipSuccess) ie = hipStreamSynchronize(st);
             if (ie != hipSuccess) return fail(fn, std::string("graph replay failed: ") + hipGetErrorString(ie), KCT_ERR_HIP);
         } else {
-            for (int it = 1; it < K; ++it) KCT_BTRY(batch_iteration(b, T, off, q, c, bwd, st));
+            for (int it = 1; it < K; ++it) KCT_BTRY(batch_iteration(T, off, q, c, n, st));
         }
     }
     // results

@@ -304,9 +304,13 @@ enum BatchGrid { BG_FWD = 0, BG_BWD, BG_DIR, BG_STREAM, BG_DEEP, BG_COUNT };  //
 constexpr int BATCH_ITEM_FWD = 16, BATCH_ITEM_BWD = 1, BATCH_ITEM_DIR = 8;
 // Queue state of one persistent step: the items drawn from each XCD's queue, and the
 // workgroups that have left (the last one resets all for the next launch).
+// Each counter has a cache line of its own.
 constexpr unsigned BATCH_XCDS = 8;
 struct BatchQueue {
-    unsigned next[BATCH_XCDS], exited, pad[3];
+    struct Counter {
+        unsigned n, pad[31];
+    } next[BATCH_XCDS];
+    unsigned exited, pad[31];
 };
 
 hipError_t launch_batch_forward(const BatchInst *B, const int64_t *off, int count, BatchQueue *q, int grid,

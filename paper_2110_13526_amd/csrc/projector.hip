@@ -113,8 +113,9 @@ __global__ __launch_bounds__(256, 7) void kp_forward(const BatchInst *__restrict
                                                   int count, BatchQueue *__restrict__ q)
 {
     const int64_t total = off[count];
+    unsigned passed = 0;
     for (;;) {
-        const int64_t item = batch_pop(q, total);
+        const int64_t item = batch_pop(q, total, passed);
         if (item >= total) break;
         const int i = batch_find(off, count, item);
         const BatchInst *bi = B + i;

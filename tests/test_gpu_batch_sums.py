@@ -41,3 +41,25 @@ def test_batch_scalars_equal_separate_solves(depth):
             assert torch.equal(x, x1)
             assert (i.nr2, i.nb, i.nb0) == (i1.nr2, i1.nb, i1.nb0)
     batch.close()
+
+
+def test_small_batch_does_not_wait_for_its_queues():
+    """Two 24^3 instances, 12 views: an iteration takes 0.26 ms; a draw from each of eight
+    empty queues by every workgroup that the device holds made it 0.84 (bound: half way)."""
+    import time
+    import paper_2110_13526_amd as kct
+    torch = torch_mod()
+    descs = [_cube(24, 24, 24, 1.0, 12), _cube(24, 24, 24, 1.0, 12)]
+    geoms = [geometry(g) for g in descs]
+    bs = [torch.from_numpy(ki.random_projections(g, 7)).to(dev()).to(torch.float32) for g in descs]
+    batch = kct.Batch(geoms)
+    batch.cgls(bs, 4)
+    best = float("inf")
+    for _ in range(8):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        batch.cgls(bs, 50)
+        best = min(best, (time.perf_counter() - t) / 50)
+    say(f"[batch sums] two 24^3 instances: {1e3 * best:.3f} ms per iteration")
+    assert best < 0.55e-3
+    batch.close()
