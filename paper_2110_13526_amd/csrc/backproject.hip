@@ -35,15 +35,14 @@ __device__ __forceinline__ double bwd_block_sum(double v)
 }
 
 // backward_block runs workgroup w (0 <= w < nbx * nby * nbz) of the
-// backprojection into one volume; its partial sum goes to partials[w].
+// backprojection into one volume; its partial sum goes to the partials' [w].  late(): the
+// BwdOut, after the view loop (see there).
 // s_pix / s_col / s_row: LDS for ch_rows(TZB) x CHC staged pixels (plus a zero row and a
 // spare record), CHC columns and ch_rows(TZB) + 1 rows.
-template <typename T, int EPI, int TZB, int CHC>
-__device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *__restrict__ proj,
-                                               T *__restrict__ out, T *__restrict__ out_z,
-                                               const Scalars *__restrict__ sc, double *__restrict__ partials,
-                                               int nbx, int nby, int nbz, const float *__restrict__ aux,
-                                               PixStage<acc_t<T>, split_records<acc_t<T>>(TZB)> *s_pix, ColStage *s_col, float *s_row)
+template <typename T, int EPI, int TZB, int CHC, typename Late>
+__device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *__restrict__ proj, int nbx, int nby, int nbz,
+                                               PixStage<acc_t<T>, split_records<acc_t<T>>(TZB)> *s_pix, ColStage *s_col,
+                                               float *s_row, Late late)
 {
     using A = acc_t<T>;
     constexpr int CHR = ch_rows(TZB);  // staged rows per chunk
@@ -147,6 +146,7 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
         }
     }
 
+    const BwdOut<T> o = late();
     double sq = 0.0;
     if (valid) {
 #pragma unroll
@@ -154,32 +154,27 @@ __device__ __forceinline__ void backward_block(const GeoDev &g, int w, const T *
             if (j >= nzb) continue;
             const int iz = iz0 + j;
             const size_t vox = ((size_t)iz * g.ny + iy) * g.nx + ix;
-            sq += bwd_store<T, EPI, A>(out, out_z, sc, aux, vox, ((size_t)iy * g.nx + ix) * g.nz + iz, acc[j]);
+            sq += bwd_store<T, EPI, A>(o.out, o.out_z, o.sc, o.aux, vox, ((size_t)iy * g.nx + ix) * g.nz + iz, acc[j]);
         }
     }
     if (bwd_has_partials<EPI>()) {
         const double bs = bwd_block_sum(sq);
-        if (__builtin_amdgcn_workitem_id_x() == 0) partials[w] = bs;
+        if (__builtin_amdgcn_workitem_id_x() == 0) o.partials[w] = bs;
     }
 }
 
 template <typename T, int EPI, int TZB>
-__global__ __launch_bounds__(256, sizeof(acc_t<T>) != 4 ? 2 : 6) void k_backward(GeoDev g, const T *__restrict__ proj,
-                                                                                T *__restrict__ out,
-                                                                                T *__restrict__ out_z,
-                                                                                const Scalars *__restrict__ sc,
-                                                                                double *__restrict__ partials,
+__global__ __launch_bounds__(256, sizeof(acc_t<T>) != 4 ? 2 : 6) void k_backward(BwdOut<T>, GeoDev g, const T *__restrict__ proj,
                                                                                 const int *__restrict__ skip, int nbx,
-                                                                                int nby, int nbz,
-                                                                                const float *__restrict__ aux)
+                                                                                int nby, int nbz)
 {
     if (skip && *skip) return;
     constexpr int CHC = ch_cols(TZB);
     __shared__ PixStage<acc_t<T>, split_records<acc_t<T>>(TZB)> s_pix[(ch_rows(TZB) + 1) * CHC + NH - 1];
     __shared__ ColStage s_col[CHC];
     __shared__ float s_row[ch_rows(TZB) + 1];
-    backward_block<T, EPI, TZB, CHC>(g, __builtin_amdgcn_workgroup_id_x(), proj, out, out_z, sc, partials, nbx, nby, nbz, aux, s_pix,
-                                     s_col, s_row);
+    backward_block<T, EPI, TZB, CHC>(g, __builtin_amdgcn_workgroup_id_x(), proj, nbx, nby, nbz, s_pix, s_col, s_row,
+                                     [] { return late_out<T>(); });
 }
 
 static BwdPlan brick_plan(const GeoDev &g, int form)
@@ -343,6 +338,13 @@ constexpr size_t batch_lds_bytes(bool deep)
                 : lds_max(wave_lds_bytes<float, true>(W_GROUPS), brick_lds_bytes(TZ));
 }
 
+// Instance bi's BwdOut (read at once: reading it late keeps bi alive and cost the batched
+// kernels more, 8 uneven instances 44.0 -> 49.7 ms).
+__device__ __forceinline__ auto batch_out(const BatchInst *bi)
+{
+    return [o = BwdOut<float>{bi->r, nullptr, bi->sc, bi->part, nullptr}] { return o; };
+}
+
 template <int TZB>
 __device__ __forceinline__ void batch_brick(const BatchInst *bi, const BwdPlan &p, int lw, char *lds)
 {
@@ -350,8 +352,8 @@ __device__ __forceinline__ void batch_brick(const BatchInst *bi, const BwdPlan &
     Rec *s_pix = reinterpret_cast<Rec *>(lds);
     ColStage *s_col = reinterpret_cast<ColStage *>(s_pix + (ch_rows(TZB) + 1) * ch_cols(TZB) + NH - 1);
     float *s_row = reinterpret_cast<float *>(s_col + ch_cols(TZB));
-    backward_block<float, BWD_NORM, TZB, ch_cols(TZB)>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
-                                                       p.nbz, nullptr, s_pix, s_col, s_row);
+    backward_block<float, BWD_NORM, TZB, ch_cols(TZB)>(bi->g, lw, bi->e, p.nbx, p.nby, p.nbz, s_pix, s_col, s_row,
+                                                       batch_out(bi));
 }
 
 // One tile (brick) of instance bi's r = A^T e with |r|^2 partials.  Wave form: the
@@ -361,24 +363,21 @@ template <bool DEEP>
 __device__ __forceinline__ void batch_backward_tile(const BatchInst *bi, int lw, char *lds)
 {
     const BwdPlan p = bi->bwd;
+    const auto out = batch_out(bi);
     if constexpr (DEEP) {
         if (p.form == BWD_DEEP)
             batch_brick<TZ_DEEP>(bi, p, lw, lds);
         else
-            backward_wave_block<float, BWD_NORM, 32, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx,
-                                                            p.nby, p.nbz, nullptr, W_GROUPS, p.sets, lds);
+            backward_wave_block<float, BWD_NORM, 32, true>(bi->g, lw, bi->e, p.nbx, p.nby, p.nbz, W_GROUPS, p.sets, lds, out);
         return;
     }
     if (p.form == BWD_BRICKS) batch_brick<TZ>(bi, p, lw, lds);
     else if (p.tz == 16)
-        backward_wave_block<float, BWD_NORM, 16, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
-                                                       p.nbz, nullptr, W_GROUPS, p.sets, lds);
+        backward_wave_block<float, BWD_NORM, 16, true>(bi->g, lw, bi->e, p.nbx, p.nby, p.nbz, W_GROUPS, p.sets, lds, out);
     else if (p.tz == 8)
-        backward_wave_block<float, BWD_NORM, 8, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
-                                                      p.nbz, nullptr, W_GROUPS, p.sets, lds);
+        backward_wave_block<float, BWD_NORM, 8, true>(bi->g, lw, bi->e, p.nbx, p.nby, p.nbz, W_GROUPS, p.sets, lds, out);
     else
-        backward_wave_block<float, BWD_NORM, 4, true>(bi->g, lw, bi->e, bi->r, nullptr, bi->sc, bi->part, p.nbx, p.nby,
-                                                      p.nbz, nullptr, W_GROUPS, p.sets, lds);
+        backward_wave_block<float, BWD_NORM, 4, true>(bi->g, lw, bi->e, p.nbx, p.nby, p.nbz, W_GROUPS, p.sets, lds, out);
 }
 
 // Persistent batched r = A^T e: every workgroup takes items from the queue
@@ -432,12 +431,11 @@ static void launch_bricks(const GeoDev &g, const BwdPlan &p, const T *proj, T *o
                           double *partials, const int *skip, const float *aux, hipStream_t st)
 {
     const dim3 grid((unsigned)p.nblocks);
+    const BwdOut<T> o{out, out_z, sc, partials, aux};
     if (p.form == BWD_DEEP)
-        hipLaunchKernelGGL((k_backward<T, EPI, TZ_DEEP>), grid, dim3(256), 0, st, g, proj, out, out_z, sc, partials,
-                           skip, p.nbx, p.nby, p.nbz, aux);
+        hipLaunchKernelGGL((k_backward<T, EPI, TZ_DEEP>), grid, dim3(256), 0, st, o, g, proj, skip, p.nbx, p.nby, p.nbz);
     else
-        hipLaunchKernelGGL((k_backward<T, EPI, TZ>), grid, dim3(256), 0, st, g, proj, out, out_z, sc, partials, skip,
-                           p.nbx, p.nby, p.nbz, aux);
+        hipLaunchKernelGGL((k_backward<T, EPI, TZ>), grid, dim3(256), 0, st, o, g, proj, skip, p.nbx, p.nby, p.nbz);
 }
 
 // A single plain backprojection with batched-form variant v (the tuner times these).

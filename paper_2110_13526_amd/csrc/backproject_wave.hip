@@ -8,18 +8,17 @@
 
 namespace kct {
 
-// 5 waves per SIMD: what the LDS of the staging regions leaves room for.
+// Waves per SIMD that the LDS of the staging regions leaves room for: 6 with split
+// records, 5 with whole ones.
 template <typename T, int EPI, int TZB>
-__global__ __launch_bounds__(1024, sizeof(acc_t<T>) != 4 ? 2 : 5) void k_backward_waves(
-    GeoDev g, const T *__restrict__ proj, T *__restrict__ out, T *__restrict__ out_z, const Scalars *__restrict__ sc,
-    double *__restrict__ partials, const int *__restrict__ skip, int nbx, int nby, int nbz,
-    const float *__restrict__ aux)
+__global__ __launch_bounds__(1024, sizeof(acc_t<T>) != 4 ? 2 : (TZB < TZ_DEEP ? 6 : 5)) void k_backward_waves(
+    BwdOut<T>, GeoDev g, const T *__restrict__ proj, const int *__restrict__ skip, int nbx, int nby, int nbz)
 {
     extern __shared__ __align__(16) char lds[];
     if (skip && *skip) return;
     const int waves = (int)(__builtin_amdgcn_workgroup_size_x() >> 6);
-    backward_wave_block<T, EPI, TZB, false>(g, __builtin_amdgcn_workgroup_id_x(), proj, out, out_z, sc, partials, nbx, nby,
-                                            nbz, aux, waves, waves, lds);
+    backward_wave_block<T, EPI, TZB, false>(g, __builtin_amdgcn_workgroup_id_x(), proj, nbx, nby, nbz, waves, waves, lds,
+                                            [] { return late_out<T>(); });
 }
 
 template <typename T, int EPI>
@@ -28,23 +27,24 @@ static void launch_waves(const GeoDev &g, const BwdPlan &p, const T *proj, T *ou
 {
     const dim3 grid((unsigned)p.nblocks), block(64u * (unsigned)p.sets);
     using A = acc_t<T>;
+    const BwdOut<T> o{out, out_z, sc, partials, aux};
     const unsigned lds = (unsigned)(split_records<A>(p.tz) ? wave_lds_bytes<A, true>(p.sets) : wave_lds_bytes<A, false>(p.sets));
     switch (p.tz) {
     case 32:
-        hipLaunchKernelGGL((k_backward_waves<T, EPI, 32>), grid, block, lds, st, g, proj, out, out_z, sc, partials, skip,
-                           p.nbx, p.nby, p.nbz, aux);
+        hipLaunchKernelGGL((k_backward_waves<T, EPI, 32>), grid, block, lds, st, o, g, proj, skip, p.nbx, p.nby,
+                           p.nbz);
         break;
     case 16:
-        hipLaunchKernelGGL((k_backward_waves<T, EPI, 16>), grid, block, lds, st, g, proj, out, out_z, sc, partials, skip,
-                           p.nbx, p.nby, p.nbz, aux);
+        hipLaunchKernelGGL((k_backward_waves<T, EPI, 16>), grid, block, lds, st, o, g, proj, skip, p.nbx, p.nby,
+                           p.nbz);
         break;
     case 8:
-        hipLaunchKernelGGL((k_backward_waves<T, EPI, 8>), grid, block, lds, st, g, proj, out, out_z, sc, partials, skip,
-                           p.nbx, p.nby, p.nbz, aux);
+        hipLaunchKernelGGL((k_backward_waves<T, EPI, 8>), grid, block, lds, st, o, g, proj, skip, p.nbx, p.nby,
+                           p.nbz);
         break;
     default:
-        hipLaunchKernelGGL((k_backward_waves<T, EPI, 4>), grid, block, lds, st, g, proj, out, out_z, sc, partials, skip,
-                           p.nbx, p.nby, p.nbz, aux);
+        hipLaunchKernelGGL((k_backward_waves<T, EPI, 4>), grid, block, lds, st, o, g, proj, skip, p.nbx, p.nby,
+                           p.nbz);
     }
 }
 

@@ -76,6 +76,27 @@ template <typename E> __device__ __forceinline__ const E *byte_at(const void *ba
     return reinterpret_cast<const E *>(static_cast<const char *>(base) + off);
 }
 
+// Where a backprojection's sums go, needed after the view loop only.  A kernel takes it
+// as its first argument and reads it from the argument segment after the loop
+// (late_out): kept through the loop, the five pointers take ten of the scalar registers
+// that the loop is short of, and what is then spilled to vector registers costs a
+// wavefront per SIMD (16-deep wave form of the solvers, 256^3 x 360 9.2 ms against 8.1).
+template <typename T> struct BwdOut {
+    T *out, *out_z;
+    const Scalars *sc;
+    double *partials;
+    const float *aux;
+};
+
+// The running kernel's first argument, read where this stands.
+template <typename T> __device__ __forceinline__ BwdOut<T> late_out()
+{
+    typedef const __attribute__((address_space(4))) BwdOut<T> *segment;
+    segment a = (segment)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return BwdOut<T>{a->out, a->out_z, a->sc, a->partials, a->aux};
+}
+
 // Brick w (0 <= w < nbx * nby * nbz) of the backprojection, by a workgroup of `waves`
 // wavefronts, the views dealt to `sets` subsets (1, 2 or a multiple of W_GROUPS): views
 // s, s + sets, ... are subset s.  With subs = sets / waves (at least 1), wavefront v takes
@@ -84,15 +105,12 @@ template <typename E> __device__ __forceinline__ const E *byte_at(const void *ba
 // order within each of W_GROUPS groups of neighbouring subsets (one subset each where
 // there are fewer), and the groups pairwise, so the sum depends on `sets` alone; the
 // squares of a layer of voxels are added first, then the layers in order, so the
-// partial sum of squares, which goes to partials[w], depends on `sets` alone as
+// partial sum of squares, which goes to the partials' [w], depends on `sets` alone as
 // well.  lds: wave_lds_bytes(waves) bytes, 16-byte aligned.  BATCH: waves is
-// W_GROUPS; else it is sets.
-template <typename T, int EPI, int TZB, bool BATCH>
-__device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, const T *__restrict__ proj,
-                                                    T *__restrict__ out, T *__restrict__ out_z,
-                                                    const Scalars *__restrict__ sc, double *__restrict__ partials,
-                                                    int nbx, int nby, int nbz, const float *__restrict__ aux,
-                                                    int waves, int sets, void *lds)
+// W_GROUPS; else it is sets.  late(): the BwdOut, after the view loop.
+template <typename T, int EPI, int TZB, bool BATCH, typename Late>
+__device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, const T *__restrict__ proj, int nbx, int nby,
+                                                    int nbz, int waves, int sets, void *lds, Late late)
 {
     using A = acc_t<T>;
     constexpr bool SQ = EPI == BWD_DIAG || EPI == BWD_DIAG_INV;  // squared weights, e not read
@@ -221,6 +239,7 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
 
     // every voxel's partial sums through LDS, W_SUMS voxels of each lane at a time:
     // in order within a group, then the groups
+    const BwdOut<T> o = late();
     A *mine = reinterpret_cast<A *>(s_pix);
     const int per = waves > W_GROUPS ? waves / W_GROUPS : 1;
 #pragma unroll
@@ -245,7 +264,7 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
             if (valid) {
                 const int iz = iz0 + j;
                 const size_t vox = ((size_t)iz * g.ny + iy) * g.nx + ix;
-                sq = bwd_store<T, EPI, A>(out, out_z, sc, aux, vox, ((size_t)iy * g.nx + ix) * g.nz + iz,
+                sq = bwd_store<T, EPI, A>(o.out, o.out_z, o.sc, o.aux, vox, ((size_t)iy * g.nx + ix) * g.nz + iz,
                                           (v[0] + v[1]) + (v[2] + v[3]));
             }
             if (bwd_has_partials<EPI>()) {
@@ -259,7 +278,7 @@ __device__ __forceinline__ void backward_wave_block(const GeoDev &g, int w, cons
         if (__builtin_amdgcn_workitem_id_x() == 0) {
             double r = layer_sq[0];
             for (int j = 1; j < nzb; ++j) r += layer_sq[j];
-            partials[w] = r;
+            o.partials[w] = r;
         }
     }
 }
