@@ -243,52 +243,52 @@ __global__ __launch_bounds__(256 * FWD_PARTS) void k_forward_divided(
 }
 
 // The launch of a forward projection with R rows per lane; divided (R <= 2): see FwdPlan.
-template <typename TV, typename TP, int EPI, int R>
-static void launch_forward_epi(const GeoDev &g, bool divided, const TV *vol, const TV *vol_z, TP *out, const TP *aux,
-                               const Scalars *sc, double *partials, const int *skip, hipStream_t st)
+template <typename TV, typename TP, int EPI, int R, bool ZFAST>
+static hipError_t launch_forward_epi(const GeoDev &g, bool divided, const TV *vol, const TV *vol_z, TP *out, const TP *aux,
+                                     const Scalars *sc, double *partials, const int *skip, hipStream_t st)
 {
     const dim3 grid((unsigned)fwd_grid(g, R).nblocks);
     if constexpr (R <= 2) {
         if (divided) {
-            if (vol_z)
-                hipLaunchKernelGGL((k_forward_divided<TV, TP, EPI, R, true>), grid, dim3(256 * FWD_PARTS), 0, st, g, vol,
-                                   vol_z, out, aux, sc, partials, skip);
-            else
-                hipLaunchKernelGGL((k_forward_divided<TV, TP, EPI, R, false>), grid, dim3(256 * FWD_PARTS), 0, st, g, vol,
-                                   vol_z, out, aux, sc, partials, skip);
-            return;
+            hipLaunchKernelGGL((k_forward_divided<TV, TP, EPI, R, ZFAST>), grid, dim3(256 * FWD_PARTS), 0, st, g, vol, vol_z,
+                               out, aux, sc, partials, skip);
+            return hipGetLastError();
         }
     }
-    if (vol_z)
-        hipLaunchKernelGGL((k_forward<TV, TP, EPI, R, true>), grid, dim3(256), 0, st, g, vol, vol_z, out, aux, sc, partials,
-                           skip);
-    else
-        hipLaunchKernelGGL((k_forward<TV, TP, EPI, R, false>), grid, dim3(256), 0, st, g, vol, vol_z, out, aux, sc, partials,
-                           skip);
+    hipLaunchKernelGGL((k_forward<TV, TP, EPI, R, ZFAST>), grid, dim3(256), 0, st, g, vol, vol_z, out, aux, sc, partials,
+                       skip);
+    return hipGetLastError();
 }
 
 template <typename TV, typename TP, int R>
 hipError_t launch_forward_rows(const GeoDev &g, bool divided, const TV *vol, const TV *vol_z, TP *out, const TP *aux,
                                int epi, const Scalars *sc, double *partials, const int *skip, hipStream_t st)
 {
-    if constexpr (std::is_same<TV, double>::value) {  // double storage: plain projection only
-        if (epi != FWD_PLAIN) return hipErrorInvalidValue;
-        launch_forward_epi<TV, TP, FWD_PLAIN, R>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st);
-    } else {
-        switch (epi) {
-        case FWD_PLAIN: launch_forward_epi<TV, TP, FWD_PLAIN, R>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        case FWD_NORM: launch_forward_epi<TV, TP, FWD_NORM, R>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        case FWD_BMINUS: launch_forward_epi<TV, TP, FWD_BMINUS, R>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        case FWD_LSQR: launch_forward_epi<TV, TP, FWD_LSQR, R>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        default: return hipErrorInvalidValue;
+    if constexpr (std::is_same<TV, TP>::value) {
+        if (epi == FWD_PLAIN)
+            return vol_z ? launch_forward_epi<TV, TP, FWD_PLAIN, R, true>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st)
+                         : launch_forward_epi<TV, TP, FWD_PLAIN, R, false>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st);
+        if constexpr (!std::is_same<TV, double>::value) {
+            if (epi == FWD_NORM && vol_z)
+                return launch_forward_epi<TV, TP, FWD_NORM, R, true>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st);
+            if (epi == FWD_LSQR && vol_z)
+                return launch_forward_epi<TV, TP, FWD_LSQR, R, true>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st);
         }
     }
-    return hipGetLastError();
+    if constexpr (std::is_same<TV, float>::value) {
+        if (epi == FWD_BMINUS)
+            return vol_z ? launch_forward_epi<TV, TP, FWD_BMINUS, R, true>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st)
+                         : launch_forward_epi<TV, TP, FWD_BMINUS, R, false>(g, divided, vol, vol_z, out, aux, sc, partials, skip, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 // every storage combination of launch_forward_rows with R rows per lane
 #define KCT_FORWARD_ROWS(R)                                                                                             \
     KCT_FORWARD_INST(float, float, R)                                                                                  \
+// The forms that are called: plain projections and b - A x with and without the z-fastest
+// copy, the solvers' directions, which have it, in the storage of the projections, and b - A x
+// of the single-precision iterate (double storage: plain projections only).
     KCT_FORWARD_INST(bf16, bf16, R)                                                                                    \
     KCT_FORWARD_INST(_Float16, _Float16, R)                                                                            \
     KCT_FORWARD_INST(float, bf16, R)                                                                                   \

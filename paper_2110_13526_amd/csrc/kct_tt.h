@@ -323,9 +323,8 @@ __host__ __device__ __forceinline__ void tt_ray_sums(const GeoDev &g, const View
 // One lane's share of one staged chunk: add fl(F_u F_v) * s_le[pixel] to acc[j]
 // for the voxels (ix, iy, iz0 + j), j < nzb, of a column with transaxial
 // breakpoints tu and depth reciprocals rdmin, rdmax, over the staged pixels
-// (column cu0 + c, row cv0 + r) at s_le[r * stride + c].  SQ: add
-// fl(F_u F_v)^2 * s_le instead (with s_le = L^2 this sums the squared weights).
-template <typename A, bool SQ, int NC = 4, int TZN = 16>
+// (column cu0 + c, row cv0 + r) at s_le[r * stride + c].
+template <typename A, int NC = 4, int TZN = 16>
 __host__ __device__ __forceinline__ void tt_gather_chunk(const GeoDev &g, int iz0, int nzb, const TTTrap &tu,
                                                          float rdmin, float rdmax, const A *s_le, int stride, int cu0,
                                                          int ncol, int cv0, int nrow, A (&acc)[TZN])
@@ -366,7 +365,7 @@ __host__ __device__ __forceinline__ void tt_gather_chunk(const GeoDev &g, int iz
                     for (int c = 0; c < NC; ++c) {
                         if (c0 + c <= ub) {
                             const float wgt = fu[c] * fv;
-                            if (wgt > 0.0f) acc[j] = fma_acc(SQ ? wgt * wgt : wgt, lrow[c], acc[j]);
+                            if (wgt > 0.0f) acc[j] = fma_acc(wgt, lrow[c], acc[j]);
                         }
                     }
                 }

@@ -178,8 +178,7 @@ __global__ __launch_bounds__(256, 2) void k_backward_tt_f64(GeoDev g, const doub
                 }
                 __syncthreads();
                 if (valid)
-                    tt_gather_chunk<A, false>(g, iz0, nzb, tu, rdmin, rdmax, s_le, TT_CH_COLS, cu0, ncol, cv0, nrow,
-                                           acc);
+                    tt_gather_chunk<A>(g, iz0, nzb, tu, rdmin, rdmax, s_le, TT_CH_COLS, cu0, ncol, cv0, nrow, acc);
                 __syncthreads();
             }
         }

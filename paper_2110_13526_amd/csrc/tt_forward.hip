@@ -240,31 +240,27 @@ __global__ __launch_bounds__(256, 5) void k_forward_tt(GeoDev g, const TV *__res
     }
 }
 
-template <typename TV, typename TP, int EPI>
-static void launch_ftt(const GeoDev &g, const TV *vol, const TV *vol_z, TP *out, const TP *aux, const Scalars *sc,
-                       double *partials, const int *skip, hipStream_t st)
+template <typename TV, typename TP, int EPI, bool ZFAST>
+static hipError_t launch_ftt(const GeoDev &g, const TV *vol, const TV *vol_z, TP *out, const TP *aux, const Scalars *sc,
+                             double *partials, const int *skip, hipStream_t st)
 {
     const TTFGrid f = ttf_grid(g);
     const dim3 grid((unsigned)f.nblocks), block(64 * TTF_WAVES);
-#define KCT_TTF_LAUNCH(R, OVERLAP, ZFAST)                                                                             \
+#define KCT_TTF_LAUNCH(R, OVERLAP)                                                                                     \
     hipLaunchKernelGGL((k_forward_tt<TV, TP, EPI, R, OVERLAP, ZFAST>), grid, block, 0, st, g, vol, vol_z, out, aux, sc, \
                        partials, skip)
-#define KCT_TTF_ROWS(OVERLAP, ZFAST)                      \
-    do {                                                  \
-        if (f.rows == 1) KCT_TTF_LAUNCH(1, OVERLAP, ZFAST); \
-        else KCT_TTF_LAUNCH(2, OVERLAP, ZFAST);             \
-    } while (0)
-    if (vol_z) {
-        if (g.tt_overlap) KCT_TTF_ROWS(true, true);
-        else KCT_TTF_ROWS(false, true);
+    if (g.tt_overlap) {
+        if (f.rows == 1) KCT_TTF_LAUNCH(1, true);
+        else KCT_TTF_LAUNCH(2, true);
     } else {
-        if (g.tt_overlap) KCT_TTF_ROWS(true, false);
-        else KCT_TTF_ROWS(false, false);
+        if (f.rows == 1) KCT_TTF_LAUNCH(1, false);
+        else KCT_TTF_LAUNCH(2, false);
     }
-#undef KCT_TTF_ROWS
 #undef KCT_TTF_LAUNCH
+    return hipGetLastError();
 }
 
+// The forms that are called: as for the Siddon pair (launch_forward_rows).
 template <typename TV, typename TP>
 hipError_t launch_forward_tt(const GeoDev &g, const TV *vol, const TV *vol_z, TP *out, const TP *aux, int epi,
                              const Scalars *sc, double *partials, const int *skip, hipStream_t st)
@@ -272,15 +268,20 @@ hipError_t launch_forward_tt(const GeoDev &g, const TV *vol, const TV *vol_z, TP
     if constexpr (std::is_same<TV, double>::value) {
         return launch_forward_tt_f64(g, vol, vol_z, out, epi, skip, st);
     } else {
-        switch (epi) {
-        case FWD_PLAIN: launch_ftt<TV, TP, FWD_PLAIN>(g, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        case FWD_NORM: launch_ftt<TV, TP, FWD_NORM>(g, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        case FWD_BMINUS: launch_ftt<TV, TP, FWD_BMINUS>(g, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        case FWD_LSQR: launch_ftt<TV, TP, FWD_LSQR>(g, vol, vol_z, out, aux, sc, partials, skip, st); break;
-        default: return hipErrorInvalidValue;
+        if constexpr (std::is_same<TV, TP>::value) {
+            if (epi == FWD_PLAIN)
+                return vol_z ? launch_ftt<TV, TP, FWD_PLAIN, true>(g, vol, vol_z, out, aux, sc, partials, skip, st)
+                             : launch_ftt<TV, TP, FWD_PLAIN, false>(g, vol, vol_z, out, aux, sc, partials, skip, st);
+            if (epi == FWD_NORM && vol_z) return launch_ftt<TV, TP, FWD_NORM, true>(g, vol, vol_z, out, aux, sc, partials, skip, st);
+            if (epi == FWD_LSQR && vol_z) return launch_ftt<TV, TP, FWD_LSQR, true>(g, vol, vol_z, out, aux, sc, partials, skip, st);
         }
+        if constexpr (std::is_same<TV, float>::value) {
+            if (epi == FWD_BMINUS)
+                return vol_z ? launch_ftt<TV, TP, FWD_BMINUS, true>(g, vol, vol_z, out, aux, sc, partials, skip, st)
+                             : launch_ftt<TV, TP, FWD_BMINUS, false>(g, vol, vol_z, out, aux, sc, partials, skip, st);
+        }
+        return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 #define KCT_TTF(TV, TP)                                                                                         \
