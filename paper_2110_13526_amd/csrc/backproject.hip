@@ -265,7 +265,7 @@ static BwdPlan wave_plan(const GeoDev &g, bool single)
         if (p.tz / 2 >= g.nz) continue;
         const float records = cols * (shadow_rows(g, p.tz) + 1.0f);
         p.nbz = (g.nz + p.tz - 1) / p.tz;
-        if (p.tz == 32 && 4 * g.nz < 3 * 32 * p.nbz) continue;  // all 32 layers are taken (layer_test)
+        if (p.tz == 32 && 7 * g.nz < 5 * 32 * p.nbz) continue;  // all 32 layers are taken (layer_test)
         p.nblocks = (int64_t)p.nbx * p.nby * p.nbz;
         const float over = p.tz == 8 ? 1.3f : (p.tz == 16 && single ? 1.1f : 1.0f);
         if (records <= over * (float)wave_cap(single && split_records<float>(p.tz)) && p.nblocks >= (p.tz == 32 && few < 1024 ? 1024 : few))
@@ -293,10 +293,12 @@ static BwdPlan wave_plan(const GeoDev &g, bool single)
 //   q 1.25: n 192 1129 / 1555 / 2276, n 256 6627 / 6882 / 12587, n 400 4759 / 4602 / 6751
 //   q 1.6:  n 256 9777 / 10723 / -, n 320 3679 / 3806 / -, n 400 7145 / 6823 / 12867
 //   q 2.2:  n 256 17924 / 27169 / -, n 400 12890 / 17528 / -
-// With few views the wavefronts of a workgroup brick all work on each of them, and the
-// 16-deep bricks pay from 300 bricks per view on (wave form / 16-deep): q 1.25, n 192 (1728 bricks) 1
-// view 25.1 / 19.8, 2 views 33.9 / 31.5, 4 views 51.0 / 54.4, 6 views 76.7 / 82.9; n 256 (4096 bricks) 1
-// view 44.0 / 32.0, 6 views 160 / 143; 256^2 x 68 (1280 bricks) 4 views 36.1 / 32.7, 30 views 199 / 219.
+// With fewer than eight views the wavefronts of a workgroup brick all work on each of
+// them, and the 16-deep bricks pay from 300 bricks per view on (wave form / 16-deep): q 1.25,
+// n 192 (1728 bricks) 1 view 25.1 / 19.8, 2 views 33.9 / 31.5, 4 views 51.7 / 55.2, 6 views 76.7 / 82.1;
+// n 256 (4096 bricks) 1 view 44.0 / 32.0, 6 views 160 / 143, 8 views 196 / 184, 20 views 454 / 456;
+// 256^2 x 68 (1280 bricks) 4 views 36.1 / 32.7, 30 views 199 / 219; 311 x 305 x 228 with voxels 1.4 as
+// high (6000 bricks) 2 views 100 / 91, 4 views 169 / 169, 8 views 288 / 324, 20 views 664 / 793.
 // Double precision takes the deep bricks for volumes of 128 layers and more only: 16- /
 // 32-deep 512^2 x 40, q 0.7, 30 views 280 / 347, 1024^2 x 1, 60 views 372 / 464; n 256, 30 views
 // 373 / 352.
@@ -308,7 +310,7 @@ static BwdPlan plan(const GeoDev &g, bool deep_allowed, bool single = true)
         shadow_rows(g, TZ_DEEP) <= (float)ch_rows(TZ_DEEP))
         return deep;
     const int enough = single ? 12288 : 4096, per_view = 300;
-    if (shallow.nblocks >= (g.nviews < enough / per_view ? per_view * g.nviews : enough) && cols <= (float)ch_cols(TZ) &&
+    if (shallow.nblocks >= (g.nviews < 8 ? per_view * g.nviews : enough) && cols <= (float)ch_cols(TZ) &&
         shadow_rows(g, TZ) <= (float)ch_rows(TZ))
         return shallow;
     return wave_plan(g, single);

@@ -61,7 +61,8 @@ constexpr int NH = 2;                      // detector columns held in registers
 // there (groups of 4 / 2 / 1: 1024^2 x 1 at 1.25 pixels per voxel, 8 views 78.6 / 67.3 / 69.2,
 // 60 views 561 / 476 / 484; 256^3 x 20 657 / 658 / 684; 32-deep, 128^3 x 60 89.8 / 97.2 / 103).
 // Bricks of 32 layers by wavefronts: no test (128^3 x 720, groups of 4 / 16 / no test 1368 / 1371 /
-// 1349); volumes that would fill less than three quarters of them take shallower ones.
+// 1349); volumes that would fill less than five sevenths of them take shallower ones
+// (16- / 32-deep: 256^2 x 68, 30 views 113 / 119; double precision, 115 x 261 x 71, 37 views 80 / 71).
 template <typename A> __host__ __device__ constexpr bool layer_test(int j, int tzb, bool waves)
 {
     if (j == 0 || (tzb == TZ_DEEP && waves)) return false;

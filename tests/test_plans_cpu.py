@@ -48,6 +48,15 @@ def test_few_views_take_workgroup_bricks():
     assert plan((192, 192, 192), 1.25, 2)["form"] == BWD_BRICKS
     assert plan((192, 192, 192), 1.25, 180)["form"] == BWD_WAVES
     assert plan((96, 96, 96), 1.25, 1)["form"] == BWD_WAVES
+    assert plan((256, 256, 256), 1.25, 7)["form"] == BWD_BRICKS
+    assert plan((256, 256, 256), 1.25, 8)["form"] == BWD_WAVES
+
+
+@pytest.mark.parametrize("layers, tz", [(64, 32), (68, 16), (69, 32), (96, 32)])
+def test_deepest_wave_bricks_are_mostly_filled(layers, tz):
+    """They take all 32 layers: at least five sevenths of the last layers exist."""
+    p = plan((256, 256, layers), 0.7, 60)
+    assert (p["form"], p["tz"]) == (BWD_WAVES, tz)
 
 
 def forward_tiles(nu, nv, views, rows, ws):
