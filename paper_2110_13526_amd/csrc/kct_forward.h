@@ -101,6 +101,25 @@ __host__ __device__ __forceinline__ void fwd_tile(const FwdGrid &f, unsigned w, 
     k = (int)(vb * FWD_VIEWS + (np == 2 ? i / 2 : i));
 }
 
+// The same for a volume read in its own layout in up to FWD_VIEWS_IN_PLACE views: the
+// lanes of a wavefront (rows) share no cache line there but neighbouring columns do.
+// Column group fastest, then view, then band; within 64 consecutive workgroups each XCD
+// gets 8 neighbouring groups.  Measured (us, this order / the one above): 224 x 371 x 274,
+// 13 views, FP64 4519 / 5128; 129 x 214 x 89, 9 views 259 / 371; 390 x 540 x 443, 4 views
+// 4033 / 4595; 191 x 157 x 209, 61 views, bfloat16 1101 / 1299; with more views it loses:
+// 214 x 91 x 142, 78 views 672 / 569; 262 x 143 x 400,
+// 264 views 21490 / 15270.
+constexpr int FWD_VIEWS_IN_PLACE = 64;
+__host__ __device__ __forceinline__ void fwd_tile_in_place(const FwdGrid &f, unsigned w, int &cg, int &k, int &band)
+{
+    const unsigned full = (unsigned)f.nblocks & ~63u;
+    const unsigned i = w < full ? (w & ~63u) + w % FWD_XCDS * 8 + w / FWD_XCDS % 8 : w;
+    cg = (int)(i % (unsigned)f.ncg);
+    const unsigned rest = i / (unsigned)f.ncg;
+    k = (int)(rest % (unsigned)f.nviews);
+    band = (int)(rest / (unsigned)f.nviews);
+}
+
 // forward_block runs workgroup w (0 <= w < fwd_grid(g, R).nblocks) of the
 // projection of one volume; R rows per lane.  Its partial sum goes to
 // partials[w].  A ray is walked whole (FWD_WHOLE, workgroups of 4 wavefronts, one
@@ -118,7 +137,10 @@ __device__ __forceinline__ void forward_block(const GeoDev &g, int64_t w, const 
     constexpr int FWD_ROWS = 64 * R;
     const FwdGrid fg = fwd_grid(g, R);
     int cg, k, band;
-    fwd_tile(fg, (unsigned)w, cg, k, band);
+    if (!ZFAST && WALK == FWD_WHOLE && g.nviews <= FWD_VIEWS_IN_PLACE)
+        fwd_tile_in_place(fg, (unsigned)w, cg, k, band);
+    else
+        fwd_tile(fg, (unsigned)w, cg, k, band);
     // the wavefront's column, made provably uniform so that the in-plane walk
     // (a function of the column) runs on scalar registers and branches
     const int wave = __builtin_amdgcn_readfirstlane((int)(__builtin_amdgcn_workitem_id_x() >> 6));
@@ -260,6 +282,9 @@ static hipError_t launch_forward_epi(const GeoDev &g, bool divided, const TV *vo
     return hipGetLastError();
 }
 
+// The forms that are called: plain projections and b - A x with and without the z-fastest
+// copy, the solvers' directions, which have it, in the storage of the projections, and b - A x
+// of the single-precision iterate (double storage: plain projections only).
 template <typename TV, typename TP, int R>
 hipError_t launch_forward_rows(const GeoDev &g, bool divided, const TV *vol, const TV *vol_z, TP *out, const TP *aux,
                                int epi, const Scalars *sc, double *partials, const int *skip, hipStream_t st)
@@ -286,9 +311,6 @@ hipError_t launch_forward_rows(const GeoDev &g, bool divided, const TV *vol, con
 // every storage combination of launch_forward_rows with R rows per lane
 #define KCT_FORWARD_ROWS(R)                                                                                             \
     KCT_FORWARD_INST(float, float, R)                                                                                  \
-// The forms that are called: plain projections and b - A x with and without the z-fastest
-// copy, the solvers' directions, which have it, in the storage of the projections, and b - A x
-// of the single-precision iterate (double storage: plain projections only).
     KCT_FORWARD_INST(bf16, bf16, R)                                                                                    \
     KCT_FORWARD_INST(_Float16, _Float16, R)                                                                            \
     KCT_FORWARD_INST(float, bf16, R)                                                                                   \

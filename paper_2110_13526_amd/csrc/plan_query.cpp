@@ -37,15 +37,17 @@ extern "C" kct_status kct_test_plan(const kct_volume_desc *vol, const kct_cone_d
 }
 
 // out: column group, view and row band of workgroup w of a forward projection with
-// `rows` detector rows per lane.
-extern "C" void kct_test_forward_tile(int32_t nu, int32_t nv, int32_t views, int32_t rows, int64_t w, int64_t out[3])
+// `rows` detector rows per lane; in_place: of one that reads the volume in its own layout.
+extern "C" void kct_test_forward_tile(int32_t nu, int32_t nv, int32_t views, int32_t rows, int32_t in_place, int64_t w,
+                                      int64_t out[3])
 {
     GeoDev g{};
     g.nu = nu;
     g.nv = nv;
     g.nviews = views;
     int cg, k, band;
-    fwd_tile(fwd_grid(g, rows), (unsigned)w, cg, k, band);
+    if (in_place) fwd_tile_in_place(fwd_grid(g, rows), (unsigned)w, cg, k, band);
+    else fwd_tile(fwd_grid(g, rows), (unsigned)w, cg, k, band);
     out[0] = cg;
     out[1] = k;
     out[2] = band;

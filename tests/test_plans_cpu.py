@@ -59,31 +59,33 @@ def test_deepest_wave_bricks_are_mostly_filled(layers, tz):
     assert (p["form"], p["tz"]) == (BWD_WAVES, tz)
 
 
-def forward_tiles(nu, nv, views, rows, ws):
+def forward_tiles(nu, nv, views, rows, ws, in_place=0):
     import ctypes
     from paper_2110_13526_amd import _lib
     fn = _lib.load().kct_test_forward_tile
     out = (ctypes.c_int64 * 3)()
     for w in ws:
-        fn(nu, nv, views, rows, ctypes.c_int64(w), out)
+        fn(nu, nv, views, rows, in_place, ctypes.c_int64(w), out)
         yield tuple(out)
 
 
+@pytest.mark.parametrize("in_place", [0, 1])
 @pytest.mark.parametrize("nu, nv, views, rows", [(1, 1, 1, 1), (37, 65, 23, 1), (616, 480, 7, 4), (131, 129, 300, 2), (9, 200, 129, 3)])
-def test_forward_tiles_cover_the_projection_once(nu, nv, views, rows):
+def test_forward_tiles_cover_the_projection_once(nu, nv, views, rows, in_place):
     groups, bands = (nu + 3) // 4, (nv + 64 * rows - 1) // (64 * rows)
-    tiles = set(forward_tiles(nu, nv, views, rows, range(groups * bands * views)))
+    tiles = set(forward_tiles(nu, nv, views, rows, range(groups * bands * views), in_place))
     assert len(tiles) == groups * bands * views
     assert all(0 <= c < groups and 0 <= k < views and 0 <= b < bands for c, k, b in tiles)
 
 
+@pytest.mark.parametrize("in_place", [0, 1])
 @pytest.mark.parametrize("nu, views", [(2**28 - 1, 1), (2**28 - 1, 7), (2**27, 15), (2**27 - 1, 2), (2**24, 127), (2**23 - 3, 250)])
-def test_forward_tiles_of_the_widest_detectors(nu, views):
+def test_forward_tiles_of_the_widest_detectors(nu, views, in_place):
     """Detectors of one row whose column groups times a block of views pass 2^32."""
     groups = (nu + 3) // 4
     n = groups * views
     ws = [w for w in (0, 1, 2, groups - 1, groups, n // 2, n // 3, n - 2, n - 1) if w < n]
-    tiles = list(forward_tiles(nu, 1, views, 1, ws))
+    tiles = list(forward_tiles(nu, 1, views, 1, ws, in_place))
     assert len(set(tiles)) == len(set(ws))
     assert all(0 <= c < groups and 0 <= k < views and b == 0 for c, k, b in tiles)
 
@@ -91,12 +93,21 @@ def test_forward_tiles_of_the_widest_detectors(nu, views):
 def test_detectors_beyond_the_column_offsets_are_refused():
     """32-byte column parameters are addressed by 32-bit offsets: 2^27 columns would wrap."""
     import ctypes
+    import threading
     from paper_2110_13526_amd import _lib
-    vol = _lib.VolumeDesc(8, 8, 8, 1.0, 1.0, 1.0, 0.0, 0.0, 0.0)
-    out = (ctypes.c_int64 * 8)()
-    cone = _lib.ConeDesc(1, 0.0, 6.28, None, 500.0, 1000.0, 2**27, 1, 1e-6, 1.0, 0.0, 0.0)
-    assert _lib.load().kct_test_plan(ctypes.byref(vol), ctypes.byref(cone), 0, _lib.KCT_F32, out) == 1
-    assert b"2^27 columns" in _lib.load().kct_last_error()
+    got = []
+
+    def call():  # in a thread of its own: the message is the calling thread's
+        vol = _lib.VolumeDesc(8, 8, 8, 1.0, 1.0, 1.0, 0.0, 0.0, 0.0)
+        out = (ctypes.c_int64 * 8)()
+        cone = _lib.ConeDesc(1, 0.0, 6.28, None, 500.0, 1000.0, 2**27, 1, 1e-6, 1.0, 0.0, 0.0)
+        got.append(_lib.load().kct_test_plan(ctypes.byref(vol), ctypes.byref(cone), 0, _lib.KCT_F32, out))
+        got.append(_lib.load().kct_last_error())
+
+    t = threading.Thread(target=call)
+    t.start()
+    t.join()
+    assert got[0] == 1 and b"2^27 columns" in got[1]
 
 
 def thin(nx, ny, nz, q, views=8):
