@@ -7,10 +7,11 @@
 A is linear, so the derivative of x -> A x is A itself and its adjoint is
 A^T: the backward of ``project_fn`` is one backprojection and the backward of
 ``backproject_fn`` one projection, both through the C ABI.  Because the two
-kernels evaluate bitwise identical weights, the gradient is the exact adjoint
-of the forward map up to accumulation rounding (with float64 tensors the
-accumulation is double precision, so finite differences in double precision
-see the same matrix).
+kernels evaluate bitwise identical weights (the footprint pair: identical
+factors, whose products the single-precision forward forms after summing over
+z), the gradient is the exact adjoint of the forward map up to accumulation
+rounding (with float64 tensors the accumulation is double precision, so finite
+differences in double precision see the same matrix).
 
 Leading batch dimensions are allowed: ``x`` of shape (..., nz, ny, nx) is
 projected item by item with the one geometry ``g``.

@@ -107,8 +107,7 @@ __host__ __device__ __forceinline__ void fwd_tile(const FwdGrid &f, unsigned w, 
 // gets 8 neighbouring groups.  Measured (us, this order / the one above): 224 x 371 x 274,
 // 13 views, FP64 4519 / 5128; 129 x 214 x 89, 9 views 259 / 371; 390 x 540 x 443, 4 views
 // 4033 / 4595; 191 x 157 x 209, 61 views, bfloat16 1101 / 1299; with more views it loses:
-// 214 x 91 x 142, 78 views 672 / 569; 262 x 143 x 400,
-// 264 views 21490 / 15270.
+// 214 x 91 x 142, 78 views 672 / 569; 262 x 143 x 400, 264 views 21490 / 15270.
 constexpr int FWD_VIEWS_IN_PLACE = 64;
 __host__ __device__ __forceinline__ void fwd_tile_in_place(const FwdGrid &f, unsigned w, int &cg, int &k, int &band)
 {

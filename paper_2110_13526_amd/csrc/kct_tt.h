@@ -1,7 +1,9 @@
 // kct_tt.h -- the weight of the TT footprint projector (separable footprints,
 // trapezoid transaxial x trapezoid axial; Section 3 names footprint methods,
 // the experiments of Section 4 use this variant), shared by its forward and
-// backward kernel so that both evaluate identical weights.
+// backward kernel so that both evaluate identical factors.  (Single-precision forward
+// forms F_u sum_z F_v x, the transpose sum F_u F_v L e: the same matrix up to the
+// rounding of the products, bit for bit where a sum has one term.)
 //
 // Model: a_ij = L_i * F_u(i, j) * F_v(i, j).  F_u is the mean over ray i's
 // detector column of the unit trapezoid whose breakpoints are the detector

@@ -17,15 +17,20 @@
 
 namespace kct {
 
-constexpr int TTB_CAP = 768;   // staged values of a chunk
+// Staged values of a chunk.  512 / 768 / 1024 (us; cube of n voxels, q detector pixels per
+// voxel): n 192, q 2.2, 30 views 1227 / 1055 / 1057; n 96, q 4, 20 views 482 / 384 / 309; n 128, q 0.7, 60
+// views 311 / 308 / 309; n 400, q 0.7, 20 views 2670 / 2646 / 2655; else within 0.5 %.
+constexpr int TTB_CAP = 768;
 constexpr int TTB_COLS = 48;   // most columns of a chunk
 constexpr int TTB_NC = 4;      // detector columns at once
 static_assert(TTB_CAP >= W_SUMS * 64, "the partial sums fit a staging region");
 
 constexpr size_t ttb_lds_bytes(int waves) { return (size_t)waves * (TTB_CAP * sizeof(float) + sizeof(double)); }
 
-// The deepest brick whose shadow is expected to fit one chunk, and view subsets by
-// the number of bricks, as for the Siddon pair's wave form.
+// The deepest brick whose shadow is expected to fit one chunk (see TTB_CAP), and view
+// subsets by the number of bricks, four from 2048 bricks on (the Siddon pair's wave form: from
+// 8192): with the limit at 8192, n 192 (3456 bricks) q 0.7, 60 views 1000 against 901 us, q
+// 1.25, 30 views 784 / 666, q 2.2, 30 views 1061 / 1055; n 256 and 128 the same.
 BwdPlan tt_backward_plan(const GeoDev &g)
 {
     BwdPlan p{};

@@ -25,9 +25,15 @@
 
 namespace kct {
 
-constexpr int TTF_COLS = 8;     // detector columns of a workgroup
+// Detector columns of a workgroup: more share each list and axial sum, fewer keep more
+// wavefronts in flight.  4 / 8 / 16 (us; cube of n voxels, q detector pixels per voxel): n 96,
+// q 4, 20 views 421 / 361 / 541; n 192, q 2.2, 30 views 1891 / 1715 / 2301, q 1.25 1101 / 1092 / 1625, q 0.7, 60
+// views 1997 / 2229 / 3222; n 128, q 0.7, 60 views 584 / 868 / 1262; n 32, q 1.25, 30 views 42 / 68 / 138.
+constexpr int TTF_COLS = 8;
 constexpr int TTF_WAVES = 4;
-constexpr int TTF_SLOTS = 16;   // lanes per slab when the footprints are listed
+// Lanes per slab when the footprints are listed.  8 / 16 / 32: n 96, q 4 345 / 361 / 410; n 192,
+// q 2.2 1642 / 1715 / 1877, q 0.7 2238 / 2229 / 2280; n 128, q 0.83, 180 views 1366 / 1338 / 1384.
+constexpr int TTF_SLOTS = 16;
 constexpr int TTF_SLABS = 64 / TTF_SLOTS;
 
 struct TTFEntry {               // one voxel column that the detector columns see
