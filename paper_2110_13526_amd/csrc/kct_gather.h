@@ -20,11 +20,11 @@
 // What bounds it: at 512^3 x 720, 616 x 480 detector (32-deep bricks) the LDS unit is busy
 // for 0.72 of the cycles (a record's read takes it 8 cycles per wavefront) beside 0.92 VALU
 // wave-instructions per CU-cycle, of the 1.2 that its mix of operations reaches alone.
-// One launch takes 63.7 ms (74.9 ms with a test of every voxel against the brick's top, a
+// One launch takes 62.7 ms (74.9 ms with a test of every voxel against the brick's top, a
 // search for the first and last hit column, an integer clamp made of compares
 // and selects, and the ray parameters of a column read again for each of its pixels;
 // 65.4 ms before the second row's test was skipped where no voxel of the wavefront has
-// one).  The forms for wider shadows read more records per voxel; split records
+// one; 64.1 ms before a group of columns with none hit was passed over).  The forms for wider shadows read more records per voxel; split records
 // (split_records) halve those reads: 256^3 x 360, 384 x 384 detector 10.5 -> 8.7 -> 8.2 ms.
 // EARLY (all but the 32-deep workgroup bricks, whose registers it would spill): 192^3 x 180
 // in the wave form 1.97 -> 1.88 ms, 128^3 x 720 1.48 -> 1.38, 256^3 x 90 at 0.7 pixels per

