@@ -239,8 +239,8 @@ __device__ __forceinline__ void forward_block(const GeoDev &g, int64_t w, const 
     }
 }
 
-// Registers: 7 wavefronts per SIMD with single-precision storage and four rows, 8 with
-// 16-bit storage; fewer rows need fewer.
+// Registers with four rows: 63 with the z-fastest copy (8 wavefronts per SIMD), 65 with a
+// solver's epilogue and 70 to 72 in place (7); fewer rows need fewer.
 template <typename TV, typename TP, int EPI, int R, bool ZFAST>
 __global__ __launch_bounds__(256, sizeof(acc_t<TV>) != 4 ? 1 : (R > 3 ? 7 : 8)) void k_forward(
     GeoDev g, const TV *__restrict__ vol, const TV *__restrict__ vol_z, TP *__restrict__ out, const TP *__restrict__ aux,
